@@ -21,9 +21,10 @@
 // which is exactly where linear probing would continue; the table is the same
 // valid linear-probing table either way.
 //
-// Probe: a tile of probe rows is looked up with one 16-byte load per slot
-// visited; matches become a tile bitmap (ballots) and are compacted in probe
-// order exactly like the filter: block scan + decoupled look-back + LDS stage.
+// Probe: a unit of probe rows is looked up with one 16-byte load per slot
+// visited; matches become a bitmap (ballots), payloads wait in LDS, and after
+// a block scan and a decoupled look-back over units each wave writes its
+// matches at their place in probe order.
 // The partitioned probe (further below) gives the same output with the table
 // reads kept in each XCD's L2.
 #include <algorithm>
@@ -465,39 +466,72 @@ gq_status region_build(gq_ctx *ctx, const int64_t *key, const int32_t *payload, 
                      static_cast<const uint32_t *>(w.ovf_cnt), w.ovf_cap, ctx->status_dev);
 }
 
-constexpr int JP_THREADS = 256;
-constexpr int JP_ITEMS = 16;
-constexpr int JP_TILE = JP_THREADS * JP_ITEMS;    // 4096 probes
-constexpr int JP_WORDS = JP_TILE / 64;
+// Shape of the ordered probe.  A workgroup takes one unit of consecutive rows
+// with one dequeue and one look-back; each wave owns a contiguous stretch of
+// the unit and walks it 64 rows at a time, one row per lane: 32 waves per CU
+// keep enough slot loads in flight, while more rows per lane in flight evict
+// each other's lines from L2 before the next slot of a row is read (4 rows per
+// lane 1.20, 2 rows 1.11, 1 row 1.09 ms on 50M probes of a 268 MB table).
+//
+// A large unit matters because each unit's look-back reads status words that
+// other XCDs write, over the same path as the slot lines: with 4096-row units
+// the same lookups took 1.29-1.50 ms.  16K rows (64 KB of LDS for their
+// payloads, two workgroups per CU) are the most that keep 32 waves per CU;
+// with fewer rows a unit shrinks so that about 512 units (two per CU) remain.
+// Up to JP_TINY_ROWS rows the chip is not full either way and a call is bound
+// by one unit's chain of loads: 256-row units (64K rows: 31 -> 13 us).
+constexpr int64_t JP_TINY_ROWS = 1 << 17;
+constexpr int JP_THREADS = 1024;
+constexpr int JP_TINY_THREADS = 256;
+constexpr int JP_MAX_STEPS = 16;
+
+struct jp_shape {
+    int threads, steps;
+    int64_t unit() const { return static_cast<int64_t>(threads) * steps; }
+};
+
+jp_shape jp_shape_of(int64_t n)
+{
+    if (n <= JP_TINY_ROWS) return {JP_TINY_THREADS, 1};
+    const int64_t steps = n / (JP_THREADS * 512);
+    return {JP_THREADS, static_cast<int>(std::min<int64_t>(std::max<int64_t>(steps, 1), JP_MAX_STEPS))};
+}
 
 struct probe_ws {
-    uint32_t *tile_ctr;
+    uint32_t *unit_ctr;
     uint64_t *status;
 };
 
 probe_ws probe_layout(gq_carver &c, int64_t n)
 {
     probe_ws w;
-    const int64_t tiles = (n + JP_TILE - 1) / JP_TILE;
-    w.tile_ctr = c.take<uint32_t>(64);
-    w.status = c.take<uint64_t>(static_cast<size_t>(tiles > 0 ? tiles : 1));
+    const int64_t rows = jp_shape_of(n).unit();
+    const int64_t units = (n + rows - 1) / rows;
+    w.unit_ctr = c.take<uint32_t>(64);
+    w.status = c.take<uint64_t>(static_cast<size_t>(units > 0 ? units : 1));
     return w;
 }
 
-template <bool HAS_SEL>
-__global__ __launch_bounds__(JP_THREADS) void jt_probe_kernel(const void *table, const int64_t *__restrict__ fk,
-                                                              int64_t n_bound, const int64_t *n_dev,
-                                                              const int32_t *__restrict__ sel,
-                                                              int32_t *__restrict__ prow_out,
-                                                              int32_t *__restrict__ pay_out, int64_t *n_out,
-                                                              uint32_t *tile_ctr, uint64_t *lb_status)
+// Bound by the lines of the table: each probe moves a 128-byte line, and the
+// chip moves about 55 G random lines/s from memory (a bare gather).  50M
+// probes of a 6M-key table (268 MB): 1.49 -> 1.09 ms, 46 G probes/s with the
+// 0.7 GB of keys and outputs streamed beside them.
+template <bool HAS_SEL, int THREADS>
+__global__ __launch_bounds__(THREADS) void jt_probe_kernel(const void *table, const int64_t *__restrict__ fk,
+                                                           int64_t n_bound, const int64_t *n_dev,
+                                                           const int32_t *__restrict__ sel, int steps,
+                                                           int32_t *__restrict__ prow_out,
+                                                           int32_t *__restrict__ pay_out, int64_t *n_out,
+                                                           uint32_t *unit_ctr, uint64_t *lb_status)
 {
-    __shared__ uint64_t bits[JP_WORDS];
-    __shared__ int32_t pay_elem[JP_TILE];
-    __shared__ int32_t stage_row[JP_TILE];
-    __shared__ int32_t stage_pay[JP_TILE];
-    __shared__ uint32_t scan_smem[JP_THREADS / 64];
-    __shared__ uint32_t s_tile;
+    constexpr int WAVES = THREADS / 64;
+    constexpr int MAX_WORDS = WAVES * JP_MAX_STEPS;
+    static_assert(MAX_WORDS <= THREADS, "one word per thread in the scan");
+    extern __shared__ int32_t pay_lds[];              // payload of each row of the unit
+    __shared__ uint64_t bits[MAX_WORDS];              // matches of the unit, one bit per row
+    __shared__ uint32_t wpre[MAX_WORDS];              // matches before each word
+    __shared__ uint32_t scan_smem[WAVES];
+    __shared__ uint32_t s_unit;
     __shared__ uint64_t s_goff;
 
     int64_t n = n_bound;
@@ -505,85 +539,89 @@ __global__ __launch_bounds__(JP_THREADS) void jt_probe_kernel(const void *table,
         const int64_t d = *n_dev;
         n = d < n_bound ? (d > 0 ? d : 0) : n_bound;
     }
-    if (threadIdx.x == 0) s_tile = atomicAdd(tile_ctr, 1u);
+    if (threadIdx.x == 0) s_unit = atomicAdd(unit_ctr, 1u);
     __syncthreads();
-    const uint32_t t = s_tile;
-    const int64_t ntiles = (n + JP_TILE - 1) / JP_TILE;
-    if (static_cast<int64_t>(t) >= ntiles) {
+    const uint32_t t = s_unit;
+    const int64_t unit = static_cast<int64_t>(THREADS) * steps;
+    const int64_t nunits = (n + unit - 1) / unit;
+    if (static_cast<int64_t>(t) >= nunits) {
         if (t == 0 && threadIdx.x == 0) *n_out = 0;
         return;
     }
-    const jt_header *hdr = static_cast<const jt_header *>(table);
-    const int L = static_cast<int>(hdr->log2_slots);
+    const int L = static_cast<int>(static_cast<const jt_header *>(table)->log2_slots);
     const uint64_t mask = (1ull << L) - 1;
     const jt_slot *slots = reinterpret_cast<const jt_slot *>(static_cast<const char *>(table) + JT_HEADER);
-    const int64_t base = static_cast<int64_t>(t) * JP_TILE;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int word0 = wave * steps;                   // the wave's first word
+    const int64_t row0 = static_cast<int64_t>(t) * unit + static_cast<int64_t>(word0) * 64 + lane;
 
-    int64_t k[JP_ITEMS];
-#pragma unroll
-    for (int c = 0; c < JP_ITEMS; ++c) {
-        const int64_t e = base + c * JP_THREADS + wave * 64 + lane;
-        k[c] = JT_EMPTY;
-        if (e < n) k[c] = fk[HAS_SEL ? static_cast<int64_t>(sel[e]) : e];
-    }
-    uint64_t s[JP_ITEMS];
-    int4 v[JP_ITEMS];
-#pragma unroll
-    for (int c = 0; c < JP_ITEMS; ++c) {
-        s[c] = gq_fmix64(static_cast<uint64_t>(k[c])) >> (64 - L);
-        v[c] = *reinterpret_cast<const int4 *>(&slots[s[c]]);
-    }
-#pragma unroll
-    for (int c = 0; c < JP_ITEMS; ++c) {
-        const int64_t e = base + c * JP_THREADS + wave * 64 + lane;
+    // the key of the next step is loaded (and the selection of the one after)
+    // while this step's slot is on its way: issued after the slot's load, which
+    // is waited for first (loads return in order; issued before it, 1.18 ms)
+    int32_t nr = 0;
+    int64_t nk;
+    auto load_row = [&](int i) {
+        const int64_t e = row0 + i * 64;
+        if (HAS_SEL) nr = (i < steps && e < n) ? sel[e] : 0;
+    };
+    auto load_key = [&](int i) {
+        const int64_t e = row0 + i * 64;
+        nk = (i < steps && e < n) ? __builtin_nontemporal_load(&fk[HAS_SEL ? static_cast<int64_t>(nr) : e]) : JT_EMPTY;
+    };
+    load_row(0);
+    load_key(0);
+    load_row(1);
+    for (int i = 0; i < steps; ++i) {
+        const int64_t k = nk;
+        uint64_t s = gq_fmix64(static_cast<uint64_t>(k)) >> (64 - L);
+        int4 v{};
+        if (k != JT_EMPTY) v = *reinterpret_cast<const int4 *>(&slots[s]);
+        load_key(i + 1);
+        load_row(i + 2);
         bool hit = false;
         int32_t pay = 0;
-        if (e < n && k[c] != JT_EMPTY) {
-            int64_t sk = (static_cast<int64_t>(static_cast<uint32_t>(v[c].y)) << 32) | static_cast<uint32_t>(v[c].x);
-            uint64_t probes = 0;
-            while (sk != k[c] && sk != JT_EMPTY && probes < mask) {
-                s[c] = (s[c] + 1) & mask;
-                v[c] = *reinterpret_cast<const int4 *>(&slots[s[c]]);
-                sk = (static_cast<int64_t>(static_cast<uint32_t>(v[c].y)) << 32) | static_cast<uint32_t>(v[c].x);
-                ++probes;
+        if (k != JT_EMPTY) {                          // the marker is no key: it matches nothing
+            for (uint64_t probes = 0; probes <= mask; ++probes) {
+                const int64_t sk =
+                    (static_cast<int64_t>(static_cast<uint32_t>(v.y)) << 32) | static_cast<uint32_t>(v.x);
+                if (sk == k) {
+                    hit = true;
+                    pay = v.z;
+                }
+                if (sk == k || sk == JT_EMPTY) break;
+                s = (s + 1) & mask;
+                v = *reinterpret_cast<const int4 *>(&slots[s]);
             }
-            hit = sk == k[c];
-            pay = v[c].z;
         }
-        const int elem = c * JP_THREADS + wave * 64 + lane;
-        pay_elem[elem] = pay;
         const uint64_t b = gq_ballot(hit);
-        if (lane == 0) bits[c * (JP_THREADS / 64) + wave] = b;
+        if (lane == 0) bits[word0 + i] = b;
+        pay_lds[(word0 + i) * 64 + lane] = pay;
     }
     __syncthreads();
-
-    // thread i owns tile elements [16 i, 16 i + 16)
-    uint32_t mine = static_cast<uint32_t>(bits[threadIdx.x >> 2] >> ((threadIdx.x & 3) * 16)) & 0xffffu;
+    const int words = WAVES * steps;
+    const uint32_t cnt = static_cast<int>(threadIdx.x) < words ? static_cast<uint32_t>(__popcll(bits[threadIdx.x])) : 0u;
     uint32_t total;
-    uint32_t pos = gq_block_exclusive_scan<JP_THREADS>(static_cast<uint32_t>(__popc(mine)), &total, scan_smem);
+    const uint32_t pre = gq_block_exclusive_scan<THREADS>(cnt, &total, scan_smem);
+    if (static_cast<int>(threadIdx.x) < words) wpre[threadIdx.x] = pre;
     if (wave == 0) {
         const uint64_t g = gq_lookback(lb_status, t, total);
-        if (lane == 0) s_goff = g;
-    }
-    const int elem0 = threadIdx.x * JP_ITEMS;
-    while (mine) {
-        const int i = __builtin_ctz(mine);
-        mine &= mine - 1;
-        const int64_t e = base + elem0 + i;
-        stage_row[pos] = HAS_SEL ? sel[e] : static_cast<int32_t>(e);
-        stage_pay[pos] = pay_elem[elem0 + i];
-        ++pos;
+        if (lane == 0) {
+            s_goff = g;
+            if (static_cast<int64_t>(t) == nunits - 1) *n_out = static_cast<int64_t>(g + total);
+        }
     }
     __syncthreads();
     const int64_t goff = static_cast<int64_t>(s_goff);
-    for (uint32_t i = threadIdx.x; i < total; i += JP_THREADS) {
-        prow_out[goff + i] = stage_row[i];
-        pay_out[goff + i] = stage_pay[i];
+    for (int i = 0; i < steps; ++i) {
+        const uint64_t b = bits[word0 + i];
+        if ((b >> lane) & 1u) {
+            const int64_t o = goff + wpre[word0 + i] + gq_mbcnt(b);
+            const int64_t e = row0 + i * 64;
+            prow_out[o] = HAS_SEL ? sel[e] : static_cast<int32_t>(e);
+            pay_out[o] = pay_lds[(word0 + i) * 64 + lane];
+        }
     }
-    if (static_cast<int64_t>(t) == ntiles - 1 && threadIdx.x == 0) *n_out = goff + total;
 }
-
 
 // ------------------------------------------------------------------------
 // Partitioned probe: the probes of one table region are answered from an LDS
@@ -1231,13 +1269,17 @@ gq_status gq_join_probe(gq_ctx *ctx, const void *table, const int64_t *fk, int64
     gq_carver c(ws);
     probe_ws w = probe_layout(c, n);
     GQ_TRY(gq_zero(ctx, ws, c.off / 4, s));
-    const int64_t tiles = (n + JP_TILE - 1) / JP_TILE;
-    const uint32_t grid = static_cast<uint32_t>(tiles > 0 ? tiles : 1);
-    if (sel)
-        return gq_launch(ctx, "gq_join_probe", jt_probe_kernel<true>, dim3(grid), dim3(JP_THREADS), 0, s, table, fk,
-                         n, n_dev, sel, prow_out, payload_out, n_out_dev, w.tile_ctr, w.status);
-    return gq_launch(ctx, "gq_join_probe", jt_probe_kernel<false>, dim3(grid), dim3(JP_THREADS), 0, s, table, fk, n,
-                     n_dev, sel, prow_out, payload_out, n_out_dev, w.tile_ctr, w.status);
+    const jp_shape sh = jp_shape_of(n);
+    const int64_t unit = sh.unit();
+    const uint32_t grid = static_cast<uint32_t>(n > 0 ? (n + unit - 1) / unit : 1);
+    auto launch = [&](auto kernel) {
+        return gq_launch(ctx, "gq_join_probe", kernel, dim3(grid), dim3(static_cast<uint32_t>(sh.threads)),
+                         static_cast<size_t>(unit) * sizeof(int32_t), s, table, fk, n, n_dev, sel, sh.steps, prow_out,
+                         payload_out, n_out_dev, w.unit_ctr, w.status);
+    };
+    if (sh.threads == JP_TINY_THREADS)
+        return sel ? launch(jt_probe_kernel<true, JP_TINY_THREADS>) : launch(jt_probe_kernel<false, JP_TINY_THREADS>);
+    return sel ? launch(jt_probe_kernel<true, JP_THREADS>) : launch(jt_probe_kernel<false, JP_THREADS>);
 }
 
 size_t gq_join_probe_partitioned_workspace_bytes(int64_t n)
