@@ -484,6 +484,7 @@ constexpr int64_t JP_TINY_ROWS = 1 << 17;
 constexpr int JP_THREADS = 1024;
 constexpr int JP_TINY_THREADS = 256;
 constexpr int JP_MAX_STEPS = 16;
+constexpr int64_t JP_MAX_SMALL_UNITS = 1024;          // units while the steps still grow with n: below 512 (s + 1) / s
 
 struct jp_shape {
     int threads, steps;
@@ -506,7 +507,10 @@ probe_ws probe_layout(gq_carver &c, int64_t n)
 {
     probe_ws w;
     const int64_t rows = jp_shape_of(n).unit();
-    const int64_t units = (n + rows - 1) / rows;
+    int64_t units = (n + rows - 1) / rows;
+    // a workspace made for n rows serves every smaller call too: past the tiny
+    // calls, any n below has at most JP_MAX_SMALL_UNITS units or no more than n has
+    if (n > JP_TINY_ROWS) units = std::max(units, JP_MAX_SMALL_UNITS);
     w.unit_ctr = c.take<uint32_t>(64);
     w.status = c.take<uint64_t>(static_cast<size_t>(units > 0 ? units : 1));
     return w;
