@@ -7,8 +7,8 @@
 //
 //  small path (max_groups <= GB_SMALL_GROUPS): a persistent grid; each
 //    workgroup aggregates its share of the rows into a private LDS table and
-//    merges it into one global table at the end (a few atomics per group per
-//    workgroup); a finalize kernel compacts the global table.
+//    writes its groups to the workspace; the last one to finish folds all of
+//    them and writes the answer.
 //
 //  large path: the rows are hash-partitioned by key into P buckets (hist ->
 //    tile offsets -> LDS-staged scatter of narrow 16- or 24-byte records),
@@ -36,9 +36,12 @@ namespace {
 constexpr int GB_THREADS = 256;
 constexpr int GB_SMALL_SLOTS = 1024;
 constexpr int64_t GB_SMALL_GROUPS = 512;
-constexpr int GB_ITEMS = 16;
-constexpr int GB_TILE = GB_THREADS * GB_ITEMS;       // rows per small-path pass
-constexpr int GB_SMALL_BATCH = 8;                    // rows per thread whose loads overlap
+constexpr int GS_THREADS = 512;                      // small path: threads per workgroup
+constexpr int GS_BATCH = 2;                          // rows per thread whose loads overlap
+constexpr int GS_IDS = 32;                           // groups of a workgroup whose sums are kept in copies
+constexpr int GS_COPIES = 32;                        // copies of their sums, one per lane of a half wave
+constexpr int GS_FOLD = 4;                           // partial groups per thread whose loads overlap in the final fold
+constexpr int64_t GS_MIN_ROWS = 8192;                // rows per workgroup below which none is added
 constexpr int GB_BUCKET_THREADS = 1024;
 constexpr int GB_LDS_PROBES = 64;
 
@@ -372,7 +375,10 @@ GQ_DEV int64_t g_find(const gtable &g, bool active, uint64_t h, int64_t k64, int
     bool done = !active;
     while (__any(!done)) {
         if (!done) {
-            const uint32_t st = atomicCAS(&g.state[s], 0u, 1u);
+            // read first: many workgroups merging one group would serialize on
+            // compare-and-swaps of its word
+            uint32_t st = __hip_atomic_load(&g.state[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (st == 0u) st = atomicCAS(&g.state[s], 0u, 1u);
             if (st == 0u) {
                 // the claimer zeroes the sums: only the state words start cleared
                 if (K64) __hip_atomic_store(&g.k64[s], k64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -465,70 +471,318 @@ GQ_DEV void emit_group(const gq_groups &out, int64_t idx, int64_t k64, int32_t k
     out.avg_rev[idx] = gq_i128_to_double(lo, hi) / c;
 }
 
+// A partial group (exact int128 revenue): of one workgroup of the small path,
+// or of one chunk of a split bucket.
+struct gb_part {
+    int64_t k64;
+    int32_t k32;
+    uint32_t cnt;
+    uint64_t sq;
+    uint64_t lo;
+    int64_t hi;
+};
+
 // ------------------------------------------------------------- small path
+// A workgroup's LDS state.  The first GS_IDS groups it meets get an id and
+// GS_COPIES copies of their sums: a lane adds to the copy of its place in the
+// half wave, so the lanes of one instruction never meet on an address or a
+// bank, however few groups there are (with one copy, 64 lanes on 11 groups
+// serialize about six deep on every add).  The other groups' sums, and rows
+// met before their group has its id, use the slot's own sums in T.
+//
+// 60M rows by a date filter into 11 groups: 687 -> 316 us (3.4 TB/s; 4 rows
+// per thread in flight 353, 8 rows 378 us: at 72 KB of LDS two workgroups fit
+// a CU, and the lookups, not the loads, fill their time).  617K rows into 25
+// groups: 110 -> 36 us, bound by a workgroup's passes and the final fold.
+// Workgroups take at least GS_MIN_ROWS rows: with 4096 rows the fold of twice
+// the partial groups costs more than the shorter passes save (43 us).
 template <bool K64, bool K32>
-__global__ __launch_bounds__(GB_THREADS) void gb_small_kernel(gb_args a, gtable g, uint32_t *status)
+struct gs_lds {
+    lds_table<GB_SMALL_SLOTS, K64, K32> T;
+    uint32_t id[GB_SMALL_SLOTS];                     // id of the slot's group, GS_NO_ID until it has one
+    uint32_t slot_of[GS_IDS];
+    uint32_t ids;                                    // ids handed out
+    uint32_t cnt[GS_IDS * GS_COPIES];
+    uint64_t sq[GS_IDS * GS_COPIES];
+    uint64_t lo[GS_IDS * GS_COPIES];                 // the revenue's low 32 bits (unsigned)
+    int64_t hi[GS_IDS * GS_COPIES];                  //   and the rest (signed): hi * 2^32 + lo
+};
+constexpr uint32_t GS_NO_ID = 0xffffffffu;
+constexpr uint32_t GS_ID_CLAIMED = 0xfffffffeu;      // being handed out, or none left
+
+// Hash of a key for the LDS table alone (its top bits pick the home slot).
+GQ_DEV uint64_t gs_hash(int64_t k64, int32_t k32)
 {
-    __shared__ lds_table<GB_SMALL_SLOTS, K64, K32> T;
+    const uint64_t k = static_cast<uint64_t>(k64);
+    uint32_t x = static_cast<uint32_t>(k) + static_cast<uint32_t>(k >> 32) * 0x85EBCA6Bu;
+    x = x * 0x9E3779B1u + static_cast<uint32_t>(k32) * 0x9E3779B1u;
+    return static_cast<uint64_t>(x) << 8;            // where lds_home looks
+}
+
+// price * (scale - disc) of the active lanes, in `wide`; `narrow` tells
+// whether it fits 64 bits.  When every active lane's factors fit 32 bits
+// (one test for the wave), a single 32 x 32 multiplication gives it.
+GQ_DEV bool gs_revenue(bool act, int64_t price, int64_t scale, int64_t disc, int64_t &narrow, gq_i128 &wide)
+{
+    const bool small = scale == static_cast<int32_t>(scale) && price == static_cast<int32_t>(price) &&
+                       disc == static_cast<int32_t>(disc) && scale - disc == static_cast<int32_t>(scale - disc);
+    if (!__any(act && !small)) {
+        narrow = static_cast<int64_t>(static_cast<int32_t>(price)) * static_cast<int32_t>(scale - disc);
+        return true;
+    }
+    wide = gq_revenue(price, scale, disc);
+    narrow = static_cast<int64_t>(wide.lo);
+    return wide.hi == (narrow >> 63);
+}
+
+// Each workgroup adds its share of the rows up in LDS and writes its groups
+// to its own stretch of the workspace (cap groups; the rest, and rows that
+// found no LDS slot, go to the global table).  The last workgroup to finish
+// folds all partial groups in its LDS table and writes the answer out:
+// merging through the global table instead takes a chain of device atomics
+// per group, on the same few addresses for every workgroup.
+template <bool K64, bool K32>
+__global__ __launch_bounds__(GS_THREADS) void gb_small_kernel(gb_args a, gtable g, uint32_t *done,
+                                                              uint32_t *__restrict__ pcnt, gb_part *__restrict__ part,
+                                                              uint32_t cap, gq_groups out, uint32_t *status)
+{
+    __shared__ gs_lds<K64, K32> S;
+    __shared__ uint32_t scan_smem[GS_THREADS / 64];
+    __shared__ uint32_t s_pre[GS_THREADS];
+    __shared__ uint32_t s_last;
+    lds_table<GB_SMALL_SLOTS, K64, K32> &T = S.T;
     lds_init(T);
+    for (int i = threadIdx.x; i < GB_SMALL_SLOTS; i += GS_THREADS) S.id[i] = GS_NO_ID;
+    for (int i = threadIdx.x; i < GS_IDS * GS_COPIES; i += GS_THREADS) {
+        S.cnt[i] = 0;
+        S.sq[i] = S.lo[i] = 0;
+        S.hi[i] = 0;
+    }
+    if (threadIdx.x == 0) S.ids = 0;
     __syncthreads();
     const int64_t n = eff_n(a.n_bound, a.n_dev);
-    const int64_t step = static_cast<int64_t>(gridDim.x) * GB_TILE;
-    for (int64_t j0 = static_cast<int64_t>(blockIdx.x) * GB_TILE; j0 < n; j0 += step) {
-        // groups of 8 rows per thread: row ids, then keys and values, all in
-        // flight together before the LDS work
-        for (int c0 = 0; c0 < GB_ITEMS; c0 += GB_SMALL_BATCH) {
-            int64_t v[GB_SMALL_BATCH];
-            bool act[GB_SMALL_BATCH];
+    constexpr int64_t TILE = GS_THREADS * GS_BATCH;
+    const int64_t step = static_cast<int64_t>(gridDim.x) * TILE;
+    const uint32_t copy = threadIdx.x & (GS_COPIES - 1);
+    // row ids (or, without them, the filter column) of the next pass are
+    // loaded while this pass's rows are added
+    int32_t nv[GS_BATCH];
+    auto load_next = [&](int64_t j0) {
 #pragma unroll
-            for (int c = 0; c < GB_SMALL_BATCH; ++c) {
-                const int64_t j = j0 + (c0 + c) * GB_THREADS + threadIdx.x;
-                act[c] = j < n;
-                v[c] = act[c] ? value_row(a, j) : 0;
+        for (int c = 0; c < GS_BATCH; ++c) {
+            const int64_t j = j0 + c * GS_THREADS + threadIdx.x;
+            nv[c] = 0;
+            if (j < n) {
+                if (a.rowid) nv[c] = a.rowid[j];
+                else if (a.filter) nv[c] = a.filter[j];
             }
-            if (a.filter) {
+        }
+    };
+    int64_t j0 = static_cast<int64_t>(blockIdx.x) * TILE;
+    load_next(j0);
+    for (; j0 < n; j0 += step) {
+        int64_t v[GS_BATCH];
+        bool act[GS_BATCH];
 #pragma unroll
-                for (int c = 0; c < GB_SMALL_BATCH; ++c) act[c] = act[c] && row_pass(a, v[c]);
-            }
-            int64_t k64[GB_SMALL_BATCH], qv[GB_SMALL_BATCH], pv[GB_SMALL_BATCH], dv[GB_SMALL_BATCH];
-            int32_t k32[GB_SMALL_BATCH];
+        for (int c = 0; c < GS_BATCH; ++c) {
+            const int64_t j = j0 + c * GS_THREADS + threadIdx.x;
+            act[c] = j < n;
+            v[c] = a.rowid ? static_cast<int64_t>(nv[c]) : j;
+        }
+        if (a.filter) {
 #pragma unroll
-            for (int c = 0; c < GB_SMALL_BATCH; ++c) {
-                const int64_t j = j0 + (c0 + c) * GB_THREADS + threadIdx.x;
-                k64[c] = qv[c] = pv[c] = dv[c] = 0;
-                k32[c] = 0;
+            for (int c = 0; c < GS_BATCH; ++c) {
                 if (act[c]) {
-                    k64[c] = K64 ? a.key64[a.key64_by_rowid ? v[c] : j] : 0;
-                    k32[c] = K32 ? a.key32[a.key32_by_rowid ? v[c] : j] : 0;
-                    qv[c] = a.qty[v[c]];
-                    pv[c] = a.price[v[c]];
-                    dv[c] = a.disc[v[c]];
+                    const int64_t f = a.rowid ? a.filter[v[c]] : nv[c];
+                    act[c] = a.flo <= f && f < a.fhi;
                 }
             }
+        }
+        int64_t k64[GS_BATCH], qv[GS_BATCH], pv[GS_BATCH], dv[GS_BATCH];
+        int32_t k32[GS_BATCH];
 #pragma unroll
-            for (int c = 0; c < GB_SMALL_BATCH; ++c) {
-                const gq_i128 rev = gq_revenue(pv[c], a.rev_scale, dv[c]);
-                const uint64_t h = gb_hash(k64[c], k32[c]);
-                const int s = lds_find(T, act[c], h, k64[c], k32[c]);
-                if (act[c] && s >= 0) lds_add(T, s, 1u, static_cast<uint64_t>(qv[c]), rev);
-                const bool spill = act[c] && s < 0;
-                const int64_t gs = g_find<K64, K32>(g, spill, h, k64[c], k32[c], status);
-                if (spill && gs >= 0) g_add(g, gs, 1u, static_cast<uint64_t>(qv[c]), rev);
+        for (int c = 0; c < GS_BATCH; ++c) {
+            const int64_t j = j0 + c * GS_THREADS + threadIdx.x;
+            k64[c] = qv[c] = pv[c] = dv[c] = 0;
+            k32[c] = 0;
+            if (act[c]) {
+                k64[c] = K64 ? a.key64[a.key64_by_rowid ? v[c] : j] : 0;
+                k32[c] = K32 ? a.key32[a.key32_by_rowid ? v[c] : j] : 0;
+                qv[c] = a.qty[v[c]];
+                pv[c] = a.price[v[c]];
+                dv[c] = a.disc[v[c]];
+            }
+        }
+        load_next(j0 + step);
+#pragma unroll
+        for (int c = 0; c < GS_BATCH; ++c) {
+            int64_t rev;
+            gq_i128 wide{0, 0};
+            const bool narrow = gs_revenue(act[c], pv[c], a.rev_scale, dv[c], rev, wide);
+            const int s = lds_find(T, act[c], gs_hash(k64[c], k32[c]), k64[c], k32[c]);
+            if (act[c] && s >= 0) {
+                uint32_t id = __hip_atomic_load(&S.id[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (id == GS_NO_ID && atomicCAS(&S.id[s], GS_NO_ID, GS_ID_CLAIMED) == GS_NO_ID) {
+                    const uint32_t x = atomicAdd(&S.ids, 1u);
+                    if (x < GS_IDS) {
+                        S.slot_of[x] = static_cast<uint32_t>(s);
+                        __hip_atomic_store(&S.id[s], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                }
+                if (!narrow) {
+                    lds_add(T, s, 1u, static_cast<uint64_t>(qv[c]), wide);
+                } else if (id < GS_IDS) {
+                    const uint32_t x = id * GS_COPIES + copy;
+                    atomicAdd(&S.cnt[x], 1u);
+                    atomicAdd(reinterpret_cast<unsigned long long *>(&S.sq[x]),
+                              static_cast<unsigned long long>(qv[c]));
+                    atomicAdd(reinterpret_cast<unsigned long long *>(&S.lo[x]),
+                              static_cast<unsigned long long>(static_cast<uint32_t>(static_cast<uint64_t>(rev))));
+                    const int64_t high = rev >> 32;
+                    if (high)
+                        atomicAdd(reinterpret_cast<unsigned long long *>(&S.hi[x]),
+                                  static_cast<unsigned long long>(high));
+                } else {
+                    gq_i128 r;
+                    r.lo = static_cast<uint64_t>(rev);
+                    r.hi = rev >> 63;
+                    lds_add(T, s, 1u, static_cast<uint64_t>(qv[c]), r);
+                }
+            }
+            const bool spill = act[c] && s < 0;
+            if (__any(spill)) {
+                gq_i128 r = wide;
+                if (narrow) {
+                    r.lo = static_cast<uint64_t>(rev);
+                    r.hi = rev >> 63;
+                }
+                const int64_t gs = g_find<K64, K32>(g, spill, gb_hash(k64[c], k32[c]), k64[c], k32[c], status);
+                if (spill && gs >= 0) g_add(g, gs, 1u, static_cast<uint64_t>(qv[c]), r);
             }
         }
     }
     __syncthreads();
-    for (int s = threadIdx.x; s < GB_SMALL_SLOTS; s += GB_THREADS) {
+    // the copies of each id, summed by one wave, go to its slot
+    const int lane = gq_lane();
+    const uint32_t ids = S.ids < GS_IDS ? S.ids : GS_IDS;
+    for (uint32_t i = threadIdx.x >> 6; i < ids; i += GS_THREADS / 64) {
+        const uint32_t x = i * GS_COPIES + static_cast<uint32_t>(lane);
+        const bool in = lane < GS_COPIES;
+        const uint32_t cn = gq_wave_sum<uint32_t>(in ? S.cnt[x] : 0u);
+        const uint64_t sq = gq_wave_sum<uint64_t>(in ? S.sq[x] : 0ull);
+        const uint64_t lo = gq_wave_sum<uint64_t>(in ? S.lo[x] : 0ull);
+        const int64_t hi = gq_wave_sum<int64_t>(in ? S.hi[x] : 0);
+        if (lane == 0) lds_add(T, static_cast<int>(S.slot_of[i]), cn, sq, lds_split_total(lo, hi));
+    }
+    __syncthreads();
+    // the workgroup's groups: to its stretch, the surplus to the global table
+    gb_part *mine = part + static_cast<size_t>(blockIdx.x) * cap;
+    uint32_t total = 0;
+    for (int b = 0; b < GB_SMALL_SLOTS; b += GS_THREADS) {
+        const int s = b + static_cast<int>(threadIdx.x);
         const bool occ = lds_occupied(T, s);
+        uint32_t all;
+        const uint32_t at = total + gq_block_exclusive_scan<GS_THREADS>(occ ? 1u : 0u, &all, scan_smem);
         const int64_t k64 = occ ? lds_key64(T, s) : 0;
         const int32_t k32 = occ ? lds_key32(T, s) : 0;
-        const int64_t gs = g_find<K64, K32>(g, occ, gb_hash(k64, k32), k64, k32, status);
-        if (occ && gs >= 0) {
-            gq_i128 rv;
-            rv.lo = T.lo[s];
-            rv.hi = T.hi[s];
-            g_add(g, gs, T.cnt[s], T.sq[s], rv);
+        if (occ && at < cap) mine[at] = gb_part{k64, k32, T.cnt[s], T.sq[s], T.lo[s], T.hi[s]};
+        const bool over = occ && at >= cap;
+        if (__any(over)) {
+            const int64_t gs = g_find<K64, K32>(g, over, gb_hash(k64, k32), k64, k32, status);
+            if (over && gs >= 0) g_add(g, gs, T.cnt[s], T.sq[s], gq_i128{T.lo[s], T.hi[s]});
         }
+        total += all;
+    }
+    __syncthreads();                                 // every thread's partial groups are written
+    if (threadIdx.x == 0) {
+        pcnt[blockIdx.x] = total < cap ? total : cap;
+        __threadfence();                             // partials, count and global adds before the done count
+        s_last = atomicAdd(done, 1u) + 1 == gridDim.x ? 1u : 0u;
+    }
+    __syncthreads();
+    if (s_last == 0) return;                         // same for the whole workgroup
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    lds_init(T);
+    __syncthreads();
+    // all partial groups as one list, GS_FOLD per thread in flight
+    uint32_t parts;
+    const uint32_t before = gq_block_exclusive_scan<GS_THREADS>(threadIdx.x < gridDim.x ? pcnt[threadIdx.x] : 0u,
+                                                                &parts, scan_smem);
+    s_pre[threadIdx.x] = before;                     // (past the last workgroup: the total)
+    __syncthreads();
+    for (uint32_t i0 = 0; i0 < parts; i0 += GS_THREADS * GS_FOLD) {
+        gb_part pe[GS_FOLD];
+#pragma unroll
+        for (int c = 0; c < GS_FOLD; ++c) {
+            const uint32_t i = i0 + c * GS_THREADS + threadIdx.x;
+            pe[c] = gb_part{};
+            if (i < parts) {
+                uint32_t w = 0;                      // the last workgroup with s_pre[w] <= i
+#pragma unroll
+                for (uint32_t d = GS_THREADS / 2; d; d >>= 1)
+                    if (s_pre[w + d] <= i) w += d;
+                pe[c] = part[static_cast<size_t>(w) * cap + (i - s_pre[w])];
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < GS_FOLD; ++c) {
+            const bool act = i0 + c * GS_THREADS + threadIdx.x < parts;
+            const int sl = lds_find(T, act, gs_hash(pe[c].k64, pe[c].k32), pe[c].k64, pe[c].k32);
+            if (act && sl >= 0) lds_add(T, sl, pe[c].cnt, pe[c].sq, gq_i128{pe[c].lo, pe[c].hi});
+            const bool over = act && sl < 0;
+            if (__any(over)) {
+                const int64_t gs = g_find<K64, K32>(g, over, gb_hash(pe[c].k64, pe[c].k32), pe[c].k64, pe[c].k32, status);
+                if (over && gs >= 0) g_add(g, gs, pe[c].cnt, pe[c].sq, gq_i128{pe[c].lo, pe[c].hi});
+            }
+        }
+    }
+    __threadfence();
+    __syncthreads();
+    auto read32 = [](const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    auto read64 = [](const auto *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    const bool merge = read32(g.used) != 0u;         // same value for every thread
+    int64_t idx = 0;
+    for (int b = 0; b < GB_SMALL_SLOTS; b += GS_THREADS) {
+        const int s = b + static_cast<int>(threadIdx.x);
+        const bool occ = lds_occupied(T, s);
+        uint32_t all;
+        const uint32_t pre = gq_block_exclusive_scan<GS_THREADS>(occ ? 1u : 0u, &all, scan_smem);
+        const int64_t k64 = occ ? lds_key64(T, s) : 0;
+        const int32_t k32 = occ ? lds_key32(T, s) : 0;
+        uint64_t cnt = occ ? T.cnt[s] : 0, sq = occ ? T.sq[s] : 0, lo = occ ? T.lo[s] : 0;
+        int64_t hi = occ ? T.hi[s] : 0;
+        if (merge) {                                 // the key's share in the global table, which then skips it
+            const int64_t gs = g_lookup<K64, K32>(g, occ, gb_hash(k64, k32), k64, k32);
+            if (occ && gs >= 0) {
+                cnt += read64(&g.cnt[gs]);
+                sq += read64(&g.sq[gs]);
+                const uint64_t l2 = lo + read64(&g.lo[gs]);
+                hi += read64(&g.hi[gs]) + (l2 < lo ? 1 : 0);
+                lo = l2;
+                __hip_atomic_store(&g.state[gs], 3u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        if (occ) emit_group(out, idx + pre, k64, k32, cnt, sq, lo, hi, status);
+        idx += all;
+    }
+    if (merge) {
+        __threadfence();
+        __syncthreads();                             // every taken entry is marked
+        for (uint64_t b = 0; b <= g.mask; b += GS_THREADS) {
+            const uint64_t s = b + threadIdx.x;
+            const bool occ = s <= g.mask && read32(&g.state[s]) == 2u;
+            uint32_t all;
+            const uint32_t pre = gq_block_exclusive_scan<GS_THREADS>(occ ? 1u : 0u, &all, scan_smem);
+            if (occ)
+                emit_group(out, idx + pre, K64 ? read64(&g.k64[s]) : 0,
+                           K32 ? __hip_atomic_load(&g.k32[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0,
+                           read64(&g.cnt[s]), read64(&g.sq[s]), read64(&g.lo[s]), read64(&g.hi[s]), status);
+            idx += all;
+        }
+    }
+    if (threadIdx.x == 0) {
+        *out.n_groups = idx;
+        if (static_cast<uint64_t>(idx) > g.mask + 1) gq_raise(status, GQ_ERR_CAPACITY);   // more than max_groups allows
     }
 }
 
@@ -1248,16 +1502,6 @@ struct bucket_slots {
     static constexpr int value = K64 ? 3072 : 4096;
 };
 
-// A partial group of one chunk of a split bucket (exact int128 revenue).
-struct gb_part {
-    int64_t k64;
-    int32_t k32;
-    uint32_t cnt;
-    uint64_t sq;
-    uint64_t lo;
-    int64_t hi;
-};
-
 // Sums of several rows into slot s (the split form of lds_add_split).
 template <int SLOTS, bool K64, bool K32>
 GQ_DEV void lds_add_sums(lds_table<SLOTS, K64, K32> &T, int s, uint32_t cnt, uint64_t qty, uint64_t lo_sum,
@@ -1588,6 +1832,8 @@ uint64_t next_pow2(uint64_t x)
 
 struct gb_plan {
     bool small;
+    uint32_t small_blocks;  // workgroups of the small path
+    uint32_t small_cap;     // partial groups each of them may leave (a power of two)
     int P;                  // buckets of the large path
     bool wide;              // P > GB_MAX_P: two levels (GB_P1 super-buckets, then P / GB_P1 each)
     int P2;                 // sub-buckets per super-bucket (wide)
@@ -1623,6 +1869,10 @@ gb_plan make_plan(int64_t n, int64_t max_groups, bool k64, bool k32)
     pl.chunk_rows = (!pl.small && !k64) ? GL_CHUNK_ROWS : tile;
     pl.ntiles = n > 0 ? (n + pl.chunk_rows - 1) / pl.chunk_rows : 1;
     pl.words = k64 ? 3 : 2;
+    static_assert(2 * GB_CUS <= GS_THREADS, "the final fold holds one workgroup per thread");
+    pl.small_blocks = static_cast<uint32_t>(
+        std::min<int64_t>(std::max<int64_t>((n + GS_MIN_ROWS - 1) / GS_MIN_ROWS, 1), 2 * GB_CUS));
+    pl.small_cap = static_cast<uint32_t>(next_pow2(static_cast<uint64_t>(std::max<int64_t>(max_groups, 64))));
     if (!pl.small) {
         // about 40% of a bucket's LDS table for the expected groups: the
         // bucket pass waits on the longest probe chain of 64 lanes, so short
@@ -1662,8 +1912,8 @@ struct gb_ws {
     uint32_t *sfirst;       // queue position of a split bucket's first chunk
     uint32_t *bdone;        // chunks of each bucket finished
     uint32_t *bspill;       // a chunk of the bucket sent rows to the global table
-    uint32_t *pcnt;         // partial groups of each split chunk
-    void *part;             // the partial groups (split chunks only)
+    uint32_t *pcnt;         // partial groups of each split chunk (small path: of each workgroup)
+    void *part;             // the partial groups
     void *scan_ws;
     uint64_t *recs;         // partitioned rows, narrow records
     uint32_t *side;         // row indices of wide rows
@@ -1696,6 +1946,10 @@ gb_ws gb_layout(gq_carver &c, const gb_plan &pl, int64_t n, bool k64, bool k32)
     w.g.lo = c.take<uint64_t>(S);
     w.g.hi = c.take<int64_t>(S);
     w.g.mask = S - 1;
+    if (pl.small) {
+        w.pcnt = c.take<uint32_t>(pl.small_blocks);
+        w.part = c.take<char>(static_cast<size_t>(pl.small_blocks) * pl.small_cap * sizeof(gb_part));
+    }
     if (!pl.small) {
         const size_t rows = static_cast<size_t>(n > 0 ? n : 1);
         const int P1 = pl.wide ? GB_P1 : pl.P;              // buckets of the tile-staged scatter
@@ -1724,18 +1978,13 @@ template <bool K64, bool K32>
 gq_status run_groupby(gq_ctx *ctx, const gb_args &a, const gb_plan &pl, const gb_ws &w, const gq_groups &out,
                       hipStream_t s)
 {
+    if (pl.small) {
+        return gq_launch(ctx, "gq_groupby_local", gb_small_kernel<K64, K32>, dim3(pl.small_blocks),
+                         dim3(GS_THREADS), 0, s, a, w.g, w.side_cnt, w.pcnt, static_cast<gb_part *>(w.part),
+                         pl.small_cap, out, ctx->status_dev);
+    }
     const uint32_t emit_blocks =
         static_cast<uint32_t>(std::min<uint64_t>((pl.gslots + 255) / 256, 4096));
-    if (pl.small) {
-        int64_t tiles = pl.ntiles;
-        int64_t blocks = static_cast<int64_t>(ctx->num_cus) * 2;
-        if (blocks > tiles) blocks = tiles;
-        if (blocks < 1) blocks = 1;
-        GQ_TRY(gq_launch(ctx, "gq_groupby_local", gb_small_kernel<K64, K32>, dim3(static_cast<uint32_t>(blocks)),
-                         dim3(GB_THREADS), 0, s, a, w.g, ctx->status_dev));
-        return gq_launch(ctx, "gq_groupby_emit", gb_table_emit_kernel<K64, K32>, dim3(emit_blocks), dim3(256), 0, s,
-                         w.g, out, ctx->status_dev);
-    }
     const uint32_t grid = static_cast<uint32_t>(pl.ntiles);
     const int P1 = pl.wide ? GB_P1 : pl.P;              // buckets of the tile-staged scatter
     uint32_t *start1 = pl.wide ? w.startA : w.start;
@@ -1833,7 +2082,7 @@ gq_status gq_groupby_agg(gq_ctx *ctx, const gq_groupby_in *in, int64_t max_group
     gq_carver c(ws);
     gb_ws w = gb_layout(c, pl, n, k64, k32);
     GQ_TRY(gq_zero(ctx, ws, w.zero_bytes / 4, s));
-    GQ_TRY(gq_zero(ctx, out->n_groups, 2, s));
+    if (!pl.small) GQ_TRY(gq_zero(ctx, out->n_groups, 2, s));   // (the small path writes it)
     gb_args a{n,       in->n_dev, in->rowid, in->key64,     in->key64_by_rowid, in->key32, in->key32_by_rowid,
               in->qty, in->price, in->disc,  in->rev_scale, in->filter,         in->filter_lo, in->filter_hi};
     if (k64 && k32) return run_groupby<true, true>(ctx, a, pl, w, *out, s);

@@ -45,3 +45,59 @@ def test_ordered_probe_units(ctx, n, lf):
         k = int(cnt.item())
         assert k == len(ep)
         assert np.array_equal(prow[:k].cpu().numpy(), ep) and np.array_equal(pay[:k].cpu().numpy(), ey)
+
+
+def check_groups(res, exp, key):
+    g = res.host()
+    o = np.argsort(g[key], kind="stable")
+    for f in (key, "count", "sum_qty", "sum_rev_lo", "sum_rev_hi"):
+        assert np.array_equal(g[f][o], exp[f]), f
+    for f in ("avg_qty", "avg_rev"):
+        np.testing.assert_allclose(g[f][o], exp[f], rtol=1e-12, atol=0)
+
+
+# few groups: 32 have copies of their sums; up to 512 bounds stay on this path
+@pytest.mark.parametrize("n", [1, 1023, 8193, 300_007])
+@pytest.mark.parametrize("groups", [1, 32, 33, 512])
+@pytest.mark.parametrize("kind", ["code", "disc"])
+def test_small_groupby_copies(ctx, n, groups, kind):
+    r = np.random.default_rng(n + groups)
+    qty = r.integers(-50, 50, size=n)
+    price = r.integers(0, 10_000_000, size=n)
+    disc = r.integers(0, 11, size=n)
+    wide = r.random(n) < 0.02                                  # factors past 32 bits, revenues past 64
+    price[wide] = r.integers(-(1 << 62), 1 << 62, size=int(wide.sum()))
+    date = r.integers(0, 100, size=n).astype(np.int32)
+    q, p, d, t = dev(qty), dev(price), dev(disc), dev(date)
+    if kind == "code":                                         # keys beside the row ids, with a device count
+        rows = np.flatnonzero(date < 60).astype(np.int32)
+        key = r.integers(0, groups, size=max(n, 1)).astype(np.int32)[:len(rows)]
+        if len(key) and groups < 512:
+            key[0] = np.iinfo(np.int32).min                    # the empty marker of the LDS table is a key too
+        cnt = torch.tensor([len(rows)], dtype=torch.int64, device="cuda")
+        pad = np.zeros(n, dtype=np.int32)
+        pad[:len(rows)] = rows
+        kpad = np.zeros(n, dtype=np.int32)
+        kpad[:len(rows)] = key
+        res = gq.gq_groupby_agg(ctx, q, p, d, n=n, n_dev=cnt, rowid=dev(pad), key32=dev(kpad), max_groups=min(groups + 1, 512))
+        exp = oracle.groupby(len(rows), qty, price, disc, rowid=rows, key32=key)
+        assert ctx.status() == gq.GQ_OK
+        check_groups(res, exp, "key32")
+    else:                                                      # a value column as key, filtered rows
+        key = r.integers(0, groups, size=n) * (1 << 33) - (1 << 40)
+        res = gq.gq_groupby_agg(ctx, q, p, d, n=n, key64=dev(key), max_groups=groups, filter_col=t, filter_lo=10,
+                                filter_hi=70)
+        rows = np.flatnonzero((date >= 10) & (date < 70)).astype(np.int32)
+        exp = oracle.groupby(len(rows), qty, price, disc, rowid=rows, key64=key[rows])
+        assert ctx.status() == gq.GQ_OK
+        check_groups(res, exp, "key64")
+
+
+def test_small_groupby_more_groups_than_the_bound(ctx):
+    """More distinct keys than twice the bound are refused, with room in the outputs or without."""
+    n = 50_000
+    key = dev((np.arange(n) % 300).astype(np.int32))
+    one = dev(np.ones(n, dtype=np.int64))
+    out = gq.alloc_groups(ctx, 400, False, True)
+    gq.gq_groupby_agg(ctx, one, one, one, key32=key, max_groups=64, out=out)
+    assert ctx.status() == gq.GQ_ERR_CAPACITY
