@@ -46,6 +46,7 @@ struct tk_lds {
     uint32_t th_rk;
     uint32_t has_th;
     uint32_t hist[2][256];          // digit counts of the selection, two passes in turn
+    uint64_t diff;                  // bits in which the entries' values differ
     uint32_t sel_bin, sel_need, sel_cnt;
     uint32_t scan[TK_THREADS / 64];
 };
@@ -91,50 +92,58 @@ GQ_DEV void tk_sort_count(tk_lds &L)
     tk_sort(L, size);
 }
 
-// Keep the best k entries of the buffer (in no particular order) and raise
-// the threshold, by radix selection over the 96-bit keys (ok, then rk),
-// eight bits at a time from the top.  A pass counts, among the entries that
-// carry the digits chosen so far, how many take each value of the next digit;
-// the chosen value is the one at which the count of better entries reaches
-// the number still needed.  Once every entry carrying the chosen digits is
-// needed, those entries and all better ones are exactly the best k.  The new
-// threshold is the chosen digits followed by zero bits: no larger than the
-// k-th best key, so no key that belongs in the best k is turned away later.
-// Keys are unique (the row part differs), so the selection always ends.
-// Block-wide; L.count must be the same in every thread on entry.
+// The leading digits of the need-th best of the buffer's entries (ok, rk hold
+// this thread's, `valid` which of them exist; at least `need` exist), by radix
+// selection over the 96-bit keys (ok, then rk), eight bits at a time.  A pass
+// counts, among the entries that carry the digits chosen so far, how many take
+// each value of the next digit; the chosen value is the one at which the count
+// of better entries reaches the number still needed.  Once every entry
+// carrying the chosen digits is needed, those entries and all better ones are
+// exactly the best `need`: the entries whose digits under the masks are at
+// least the prefix.  Keys are unique (the row part differs), so the selection
+// always ends.  The digits that all entries share are skipped: every add of
+// such a pass would meet on one counter, and values far from 64 bits wide
+// (prices in cents) share most of theirs.  Block-wide.
 constexpr int TK_PER = TK_CAP / TK_THREADS;           // buffer entries per thread
 
-GQ_DEV void tk_select(tk_lds &L, int k)
+struct tk_prefix {
+    uint64_t p_ok, m_ok;                              // chosen digits and their mask
+    uint32_t p_rk, m_rk;
+};
+
+GQ_DEV tk_prefix tk_digits(tk_lds &L, const uint64_t (&ok)[TK_PER], const uint32_t (&rk)[TK_PER], uint32_t valid,
+                           uint32_t need)
 {
-    const uint32_t cnt = L.count;
-    if (cnt <= static_cast<uint32_t>(k)) return;
-    uint64_t ok[TK_PER];
-    uint32_t rk[TK_PER];
-    uint32_t valid = 0;
+    const uint64_t ok0 = L.ok[0];
+    uint64_t diff = 0;
 #pragma unroll
-    for (int i = 0; i < TK_PER; ++i) {
-        const uint32_t e = threadIdx.x + i * TK_THREADS;
-        const bool v = e < cnt;
-        ok[i] = v ? L.ok[e] : 0;
-        rk[i] = v ? L.rk[e] : 0;
-        valid |= v ? (1u << i) : 0u;
-    }
-    for (int i = threadIdx.x; i < 256; i += TK_THREADS) L.hist[0][i] = 0;
+    for (int i = 0; i < TK_PER; ++i) diff |= ((valid >> i) & 1u) ? ok[i] ^ ok0 : 0ull;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) diff |= __shfl_xor(diff, d, 64);
+    if (threadIdx.x == 0) L.diff = 0;
+    for (int i = threadIdx.x; i < 2 * 256; i += TK_THREADS) (&L.hist[0][0])[i] = 0;
     gq_lds_barrier();
-    uint64_t p_ok = 0, m_ok = 0;                      // chosen digits and their mask
-    uint32_t p_rk = 0, m_rk = 0;
-    uint32_t need = static_cast<uint32_t>(k);
-    for (int d = 0; d < 12; ++d) {
+    if (gq_lane() == 0 && diff) atomicOr(reinterpret_cast<unsigned long long *>(&L.diff), static_cast<unsigned long long>(diff));
+    gq_lds_barrier();
+    diff = L.diff;
+    const int d0 = diff ? __builtin_clzll(diff) / 8 : 8;          // the first digit that differs
+    tk_prefix x{0, 0, 0, 0};
+    if (d0 > 0) {
+        x.m_ok = d0 == 8 ? ~0ull : ~(~0ull >> (8 * d0));
+        x.p_ok = ok0 & x.m_ok;
+    }
+    for (int d = d0; d < 12; ++d) {
         uint32_t *h = L.hist[d & 1];
         const int sh = d < 8 ? 56 - 8 * d : 24 - 8 * (d - 8);
 #pragma unroll
         for (int i = 0; i < TK_PER; ++i) {
-            if (((valid >> i) & 1u) && (ok[i] & m_ok) == p_ok && (rk[i] & m_rk) == p_rk) {
+            if (((valid >> i) & 1u) && (ok[i] & x.m_ok) == x.p_ok && (rk[i] & x.m_rk) == x.p_rk) {
                 const uint32_t dig = d < 8 ? static_cast<uint32_t>(ok[i] >> sh) & 255u : (rk[i] >> sh) & 255u;
                 atomicAdd(&h[dig], 1u);
             }
         }
-        for (int i = threadIdx.x; i < 256; i += TK_THREADS) L.hist[(d + 1) & 1][i] = 0;
+        if (d > d0)
+            for (int i = threadIdx.x; i < 256; i += TK_THREADS) L.hist[(d + 1) & 1][i] = 0;
         gq_lds_barrier();
         if (threadIdx.x < 64) {                       // one wave finds the digit, from 255 down
             const uint32_t lane = threadIdx.x;
@@ -162,22 +171,51 @@ GQ_DEV void tk_select(tk_lds &L, int k)
         const uint32_t bin = L.sel_bin, c = L.sel_cnt;
         need = L.sel_need;
         if (d < 8) {
-            p_ok |= static_cast<uint64_t>(bin) << sh;
-            m_ok |= 255ull << sh;
+            x.p_ok |= static_cast<uint64_t>(bin) << sh;
+            x.m_ok |= 255ull << sh;
         } else {
-            p_rk |= bin << sh;
-            m_rk |= 255u << sh;
+            x.p_rk |= bin << sh;
+            x.m_rk |= 255u << sh;
         }
         if (c == need) break;                         // same in every thread
     }
-    // the kept entries: chosen digits at least the prefix
+    return x;
+}
+
+// This thread's entries of the buffer.
+GQ_DEV uint32_t tk_entries(const tk_lds &L, uint64_t (&ok)[TK_PER], uint32_t (&rk)[TK_PER])
+{
+    const uint32_t cnt = L.count;
+    uint32_t valid = 0;
+#pragma unroll
+    for (int i = 0; i < TK_PER; ++i) {
+        const uint32_t e = threadIdx.x + i * TK_THREADS;
+        const bool v = e < cnt;
+        ok[i] = v ? L.ok[e] : 0;
+        rk[i] = v ? L.rk[e] : 0;
+        valid |= v ? (1u << i) : 0u;
+    }
+    return valid;
+}
+
+// Keep the best k entries of the buffer (in no particular order) and raise
+// the threshold to the chosen digits followed by zero bits: no larger than the
+// k-th best key, so no key that belongs in the best k is turned away later.
+// Block-wide; L.count must be the same in every thread on entry.
+GQ_DEV void tk_select(tk_lds &L, int k)
+{
+    if (L.count <= static_cast<uint32_t>(k)) return;
+    uint64_t ok[TK_PER];
+    uint32_t rk[TK_PER];
+    const uint32_t valid = tk_entries(L, ok, rk);
+    const tk_prefix x = tk_digits(L, ok, rk, valid, static_cast<uint32_t>(k));
     bool kp[TK_PER];
     uint32_t keep = 0;
 #pragma unroll
     for (int i = 0; i < TK_PER; ++i) {
-        const uint64_t a = ok[i] & m_ok;
-        const uint32_t b = rk[i] & m_rk;
-        kp[i] = ((valid >> i) & 1u) && (a > p_ok || (a == p_ok && b >= p_rk));
+        const uint64_t a = ok[i] & x.m_ok;
+        const uint32_t b = rk[i] & x.m_rk;
+        kp[i] = ((valid >> i) & 1u) && (a > x.p_ok || (a == x.p_ok && b >= x.p_rk));
         keep += kp[i] ? 1u : 0u;
     }
     uint32_t total;
@@ -192,8 +230,8 @@ GQ_DEV void tk_select(tk_lds &L, int k)
     }
     if (threadIdx.x == 0) {
         L.count = total;                              // k
-        L.th_ok = p_ok;
-        L.th_rk = p_rk;
+        L.th_ok = x.p_ok;
+        L.th_rk = x.p_rk;
         L.has_th = 1;
     }
     gq_lds_barrier();
