@@ -252,12 +252,59 @@ GQ_DEV uint64_t tk_order(int64_t v, bool desc)
     return desc ? u : ~u;
 }
 
+// Up to this k the merges take every candidate: recording and ranking the
+// lists' bounds costs more than it saves (128 lists of 100 keys: 33 us in two
+// merges, 39 us in one with bounds, and 5 us more in the scan).  At k = 1000
+// and 512 lists the merges took 126 us without bounds and take 66 with them.
+constexpr int TK_PLAIN_K = 256;
+
+// Candidate lists: list i holds cnt[i] <= k keys from i * k, and a bound that
+// at least `need` of them reach (0, 0 if it has fewer).
+struct tk_lists {
+    uint64_t *ok;
+    uint32_t *rk;
+    uint32_t *cnt;
+    uint64_t *b_ok;
+    uint32_t *b_rk;
+};
+
+// Keys per list whose bound is recorded: with `lists` of them, ceil(k / need)
+// is about half the lists.
+__host__ __device__ inline uint32_t tk_need(int k, int lists)
+{
+    if (k <= TK_PLAIN_K) return 0;
+    const int x = (2 * k + lists - 1) / lists;
+    return static_cast<uint32_t>(x < k ? x : k);
+}
+
+// The buffer's entries (at most k) as list blockIdx.x.
+GQ_DEV void tk_write_list(tk_lds &L, int k, uint32_t need, const tk_lists &out)
+{
+    const uint32_t cnt = L.count;
+    for (uint32_t i = threadIdx.x; i < cnt; i += TK_THREADS) {
+        out.ok[static_cast<int64_t>(blockIdx.x) * k + i] = L.ok[i];
+        out.rk[static_cast<int64_t>(blockIdx.x) * k + i] = L.rk[i];
+    }
+    tk_prefix x{0, 0, 0, 0};
+    if (need != 0 && cnt >= need) {                                // same in every thread
+        uint64_t ok[TK_PER];
+        uint32_t rk[TK_PER];
+        const uint32_t valid = tk_entries(L, ok, rk);
+        x = tk_digits(L, ok, rk, valid, need);
+    }
+    if (threadIdx.x == 0) {
+        out.cnt[blockIdx.x] = cnt;
+        if (need != 0) {
+            out.b_ok[blockIdx.x] = x.p_ok;
+            out.b_rk[blockIdx.x] = x.p_rk;
+        }
+    }
+}
+
 __global__ __launch_bounds__(TK_THREADS) void topk_stage1_kernel(const int64_t *__restrict__ val,
                                                                  const int32_t *__restrict__ sel, int64_t n_bound,
                                                                  const int64_t *n_dev, int k, int desc,
-                                                                 int64_t chunk, uint64_t *__restrict__ cand_ok,
-                                                                 uint32_t *__restrict__ cand_rk,
-                                                                 uint32_t *__restrict__ cand_cnt)
+                                                                 int64_t chunk, uint32_t need, tk_lists out)
 {
     __shared__ tk_lds L;
     int64_t n = n_bound;
@@ -327,119 +374,149 @@ __global__ __launch_bounds__(TK_THREADS) void topk_stage1_kernel(const int64_t *
         }
     }
     tk_select(L, k);
-    const uint32_t cnt = L.count < static_cast<uint32_t>(k) ? L.count : static_cast<uint32_t>(k);
-    for (uint32_t i = threadIdx.x; i < cnt; i += TK_THREADS) {
-        cand_ok[static_cast<int64_t>(blockIdx.x) * k + i] = L.ok[i];
-        cand_rk[static_cast<int64_t>(blockIdx.x) * k + i] = L.rk[i];
-    }
-    if (threadIdx.x == 0) cand_cnt[blockIdx.x] = cnt;
+    tk_write_list(L, k, need, out);
 }
 
 // Merge lists [blockIdx.x * per, +per) of up to k keys each (in any order)
-// into the best k; the last level (out_ok == nullptr) sorts them and writes
-// the answer.
-__global__ __launch_bounds__(TK_THREADS) void topk_merge_kernel(const uint64_t *__restrict__ in_ok,
-                                                                const uint32_t *__restrict__ in_rk,
-                                                                const uint32_t *__restrict__ in_cnt, int nlists,
-                                                                int per, int k, uint64_t *__restrict__ out_ok,
-                                                                uint32_t *__restrict__ out_rk,
-                                                                uint32_t *__restrict__ out_cnt, int desc,
-                                                                int64_t *__restrict__ val_out,
+// into the best k; the last level (LAST) sorts them and writes the answer.
+//
+// First the lists' bounds give a key that the k-th best overall cannot be
+// below: of all the level's lists, each has `need` keys at or above its
+// bound, so the ceil(k / need)-th largest bound has k keys at or above it.
+// With need about 2 k / lists that is near the median bound, and a list of
+// rows in no particular order keeps about `need` of its k keys: the merge
+// selects among about 2 k keys instead of lists * k.
+template <bool LAST>
+__global__ __launch_bounds__(TK_THREADS) void topk_merge_kernel(tk_lists in, int nlists, int per, int k,
+                                                                uint32_t in_need, uint32_t need, tk_lists out,
+                                                                int desc, int64_t *__restrict__ val_out,
                                                                 int32_t *__restrict__ rowid_out, int64_t *n_out)
 {
     __shared__ tk_lds L;
-    if (threadIdx.x == 0) {
+    __shared__ uint32_t pre[TK_THREADS];
+    const int tid = threadIdx.x;
+    const int b0 = static_cast<int>(blockIdx.x) * per;
+    const int lists = nlists - b0 < per ? nlists - b0 : per;       // nlists <= TK_THREADS
+    uint32_t total;
+    pre[tid] = gq_block_exclusive_scan_lds<TK_THREADS>(tid < lists ? in.cnt[b0 + tid] : 0u, &total, L.scan);
+    tk_prefix t{0, 0, 0, 0};
+    if (in_need != 0) {
+        // the bound of rank ceil(k / in_need) among all lists, its leading digits
+        if (tid < nlists) {
+            L.ok[tid] = in.b_ok[tid];
+            L.rk[tid] = in.b_rk[tid];
+        }
+        if (tid == 0) L.count = static_cast<uint32_t>(nlists);
+        gq_lds_barrier();
+        uint64_t ok[TK_PER];
+        uint32_t rk[TK_PER];
+        const uint32_t valid = tk_entries(L, ok, rk);
+        t = tk_digits(L, ok, rk, valid, (static_cast<uint32_t>(k) + in_need - 1) / in_need);
+        gq_lds_barrier();
+    }
+    if (tid == 0) {
         L.count = 0;
         L.has_th = 0;
         L.th_ok = 0;
         L.th_rk = 0;
     }
     gq_lds_barrier();
-    const int b0 = static_cast<int>(blockIdx.x) * per;
-    const int b1 = b0 + per < nlists ? b0 + per : nlists;
-    const int64_t base = static_cast<int64_t>(b0) * k;
-    const int64_t total = b1 > b0 ? static_cast<int64_t>(b1 - b0) * k : 0;
-    for (int64_t s = 0; s < total; s += TK_STEP) {
-        bool valid[TK_STEP_ITEMS];
-        uint64_t ok[TK_STEP_ITEMS];
-        uint32_t rk[TK_STEP_ITEMS];
+    // the lists' keys as one sequence of `total`, a step ahead in flight
+    uint64_t nok[TK_STEP_ITEMS];
+    uint32_t nrk[TK_STEP_ITEMS];
+    auto load = [&](uint32_t s) {
 #pragma unroll
         for (int c = 0; c < TK_STEP_ITEMS; ++c) {
-            const int64_t j = s + c * TK_THREADS + threadIdx.x;
-            valid[c] = false;
-            ok[c] = 0;
-            rk[c] = 0;
-            const uint32_t li = static_cast<uint32_t>(j) / static_cast<uint32_t>(k);    // total < 2^31
-            if (j < total && static_cast<uint32_t>(j) - li * static_cast<uint32_t>(k) < in_cnt[b0 + li]) {
-                valid[c] = true;
-                ok[c] = in_ok[base + j];
-                rk[c] = in_rk[base + j];
+            const uint32_t j = s + c * TK_THREADS + tid;
+            nok[c] = 0;
+            nrk[c] = 0;                                            // (0, 0) is below every key
+            if (j < total) {
+                uint32_t w = 0;                                    // the last list with pre[w] <= j
+#pragma unroll
+                for (uint32_t d = TK_THREADS / 2; d; d >>= 1)
+                    if (pre[w + d] <= j) w += d;
+                const int64_t at = static_cast<int64_t>(b0 + static_cast<int>(w)) * k + (j - pre[w]);
+                nok[c] = in.ok[at];
+                nrk[c] = in.rk[at];
             }
         }
+    };
+    load(0);
+    for (uint32_t s = 0; s < total; s += TK_STEP) {
         const uint64_t th_ok = L.th_ok;
         const uint32_t th_rk = L.th_rk;
         const bool has_th = L.has_th != 0;
 #pragma unroll
-        for (int c = 0; c < TK_STEP_ITEMS; ++c) tk_offer(L, valid[c], ok[c], rk[c], th_ok, th_rk, has_th);
+        for (int c = 0; c < TK_STEP_ITEMS; ++c) {
+            const bool in_reach = (nok[c] | nrk[c]) != 0 && !tk_better(t.p_ok, t.p_rk, nok[c], nrk[c]);
+            tk_offer(L, in_reach, nok[c], nrk[c], th_ok, th_rk, has_th);
+        }
+        load(s + TK_STEP);
         gq_lds_barrier();
         const uint32_t cnt_now = L.count;      // same value in every thread
         gq_lds_barrier();
         if (cnt_now > static_cast<uint32_t>(TK_CAP - TK_STEP)) tk_select(L, k);
     }
     tk_select(L, k);
-    const uint32_t cnt = L.count < static_cast<uint32_t>(k) ? L.count : static_cast<uint32_t>(k);
-    if (out_ok) {
-        for (uint32_t x = threadIdx.x; x < cnt; x += TK_THREADS) {
-            out_ok[static_cast<int64_t>(blockIdx.x) * k + x] = L.ok[x];
-            out_rk[static_cast<int64_t>(blockIdx.x) * k + x] = L.rk[x];
+    if constexpr (!LAST) {
+        tk_write_list(L, k, need, out);
+    } else {
+        const uint32_t cnt = L.count;                              // at most k
+        tk_sort_count(L);                                          // the answer, best first
+        for (uint32_t x = tid; x < cnt; x += TK_THREADS) {
+            const uint64_t o = L.ok[x];
+            const uint64_t u = desc ? o : ~o;
+            val_out[x] = static_cast<int64_t>(u ^ TK_SIGN);
+            rowid_out[x] = static_cast<int32_t>(0x7fffffffu - L.rk[x]);
         }
-        if (threadIdx.x == 0) out_cnt[blockIdx.x] = cnt;
-        return;
+        if (tid == 0) *n_out = cnt;
     }
-    tk_sort_count(L);                                   // the answer, best first
-    for (uint32_t x = threadIdx.x; x < cnt; x += TK_THREADS) {
-        const uint64_t o = L.ok[x];
-        const uint64_t u = desc ? o : ~o;
-        val_out[x] = static_cast<int64_t>(u ^ TK_SIGN);
-        rowid_out[x] = static_cast<int32_t>(0x7fffffffu - L.rk[x]);
-    }
-    if (threadIdx.x == 0) *n_out = cnt;
 }
 
-constexpr int TK_MERGE_PER = 48;                      // lists per first-level merge workgroup
+// Up to TK_ONE_MERGE candidates are merged by one workgroup (16 steps, most
+// of whose keys the lists' bounds turn away); more, first in groups of
+// TK_MERGE_PER lists.
+// Candidates that one workgroup merges alone, and lists per workgroup of a
+// first merge level otherwise (128 lists of 100: 33 us at 16, 36 at 32, 41 at 48).
+int64_t tk_one_merge(int k) { return k <= TK_PLAIN_K ? 8192 : 32768; }
+int tk_merge_per(int k) { return k <= TK_PLAIN_K ? 16 : 8; }
+constexpr int TK_MAX_LISTS = 512;                     // two scan workgroups per CU
+static_assert(TK_MAX_LISTS <= TK_THREADS, "a merge holds one list per thread");
 
 struct tk_ws {
-    uint64_t *ok, *ok2;
-    uint32_t *rk, *rk2;
-    uint32_t *cnt, *cnt2;
+    tk_lists first, second;
     int blocks, groups;
     int64_t chunk;
 };
 
-tk_ws tk_layout(gq_carver &c, int64_t n, int k, int num_cus)
+tk_lists tk_take_lists(gq_carver &c, int64_t lists, int k)
+{
+    tk_lists l;
+    l.ok = c.take<uint64_t>(static_cast<size_t>(lists) * k);
+    l.rk = c.take<uint32_t>(static_cast<size_t>(lists) * k);
+    l.cnt = c.take<uint32_t>(static_cast<size_t>(lists));
+    l.b_ok = c.take<uint64_t>(static_cast<size_t>(lists));
+    l.b_rk = c.take<uint32_t>(static_cast<size_t>(lists));
+    return l;
+}
+
+tk_ws tk_layout(gq_carver &c, int64_t n, int k)
 {
     tk_ws w;
     int64_t blocks = (n + 4 * TK_STEP - 1) / (4 * TK_STEP);     // at least 4 steps per block
-    const int64_t maxb = static_cast<int64_t>(num_cus) * 2;    // two 512-thread workgroups fit a CU (95 VGPRs)
-    if (blocks > maxb) blocks = maxb;
+    if (blocks > TK_MAX_LISTS) blocks = TK_MAX_LISTS;          // two 512-thread workgroups fit a CU (95 VGPRs)
     if (blocks < 1) blocks = 1;
     int64_t chunk = (n + blocks - 1) / blocks;
     chunk = ((chunk + TK_STEP - 1) / TK_STEP) * TK_STEP;
     if (chunk < TK_STEP) chunk = TK_STEP;
     w.blocks = static_cast<int>(blocks);
-    w.groups = blocks > 2 * TK_MERGE_PER ? static_cast<int>((blocks + TK_MERGE_PER - 1) / TK_MERGE_PER) : 0;
+    const int per = tk_merge_per(k);
+    w.groups = blocks * k > tk_one_merge(k) ? static_cast<int>((blocks + per - 1) / per) : 0;
     w.chunk = chunk;
-    w.ok = c.take<uint64_t>(static_cast<size_t>(blocks) * k);
-    w.rk = c.take<uint32_t>(static_cast<size_t>(blocks) * k);
-    w.cnt = c.take<uint32_t>(static_cast<size_t>(blocks));
-    const size_t g = static_cast<size_t>(w.groups > 0 ? w.groups : 1);
-    w.ok2 = c.take<uint64_t>(g * k);
-    w.rk2 = c.take<uint32_t>(g * k);
-    w.cnt2 = c.take<uint32_t>(g);
+    w.first = tk_take_lists(c, blocks, k);
+    if (w.groups > 0) w.second = tk_take_lists(c, w.groups, k);
     return w;
 }
-
-int tk_num_cus_for_layout() { return 256; }
 
 }  // namespace
 
@@ -450,7 +527,7 @@ size_t gq_topk_workspace_bytes(int64_t n, int k)
     if (n < 0) n = 0;
     if (k < 1) k = 1;
     gq_carver c(nullptr);
-    tk_layout(c, n, k, tk_num_cus_for_layout());
+    tk_layout(c, n, k);
     return c.bytes();
 }
 
@@ -469,26 +546,20 @@ gq_status gq_topk(gq_ctx *ctx, const int64_t *val, const int32_t *sel, int64_t n
         return gq_fail(ctx, GQ_ERR_WORKSPACE, "gq_topk: workspace %zu < %zu bytes", ws_bytes, need);
     hipStream_t s = static_cast<hipStream_t>(stream);
     gq_carver c(ws);
-    tk_ws w = tk_layout(c, n, k, tk_num_cus_for_layout());
-    GQ_TRY(gq_launch(ctx, "gq_topk_local", topk_stage1_kernel, dim3(static_cast<uint32_t>(w.blocks)),
-                     dim3(TK_THREADS), 0, s, val, sel, n, n_dev, k, descending ? 1 : 0, w.chunk, w.ok, w.rk, w.cnt));
+    tk_ws w = tk_layout(c, n, k);
     const int d = descending ? 1 : 0;
-    if (w.groups > 0) {
-        GQ_TRY(gq_launch(ctx, "gq_topk_merge", topk_merge_kernel, dim3(static_cast<uint32_t>(w.groups)),
-                         dim3(TK_THREADS), 0, s, static_cast<const uint64_t *>(w.ok),
-                         static_cast<const uint32_t *>(w.rk), static_cast<const uint32_t *>(w.cnt), w.blocks,
-                         TK_MERGE_PER, k, w.ok2, w.rk2, w.cnt2, d, val_out, rowid_out, n_out_dev));
-        return gq_launch(ctx, "gq_topk_merge", topk_merge_kernel, dim3(1), dim3(TK_THREADS), 0, s,
-                         static_cast<const uint64_t *>(w.ok2), static_cast<const uint32_t *>(w.rk2),
-                         static_cast<const uint32_t *>(w.cnt2), w.groups, w.groups, k,
-                         static_cast<uint64_t *>(nullptr), static_cast<uint32_t *>(nullptr),
-                         static_cast<uint32_t *>(nullptr), d, val_out, rowid_out, n_out_dev);
-    }
-    return gq_launch(ctx, "gq_topk_merge", topk_merge_kernel, dim3(1), dim3(TK_THREADS), 0, s,
-                     static_cast<const uint64_t *>(w.ok), static_cast<const uint32_t *>(w.rk),
-                     static_cast<const uint32_t *>(w.cnt), w.blocks, w.blocks, k, static_cast<uint64_t *>(nullptr),
-                     static_cast<uint32_t *>(nullptr), static_cast<uint32_t *>(nullptr), d, val_out, rowid_out,
-                     n_out_dev);
+    const uint32_t need1 = tk_need(k, w.blocks);
+    GQ_TRY(gq_launch(ctx, "gq_topk_local", topk_stage1_kernel, dim3(static_cast<uint32_t>(w.blocks)),
+                     dim3(TK_THREADS), 0, s, val, sel, n, n_dev, k, d, w.chunk, need1, w.first));
+    if (w.groups == 0)
+        return gq_launch(ctx, "gq_topk_merge", topk_merge_kernel<true>, dim3(1), dim3(TK_THREADS), 0, s, w.first,
+                         w.blocks, w.blocks, k, need1, 0u, tk_lists{}, d, val_out, rowid_out, n_out_dev);
+    const uint32_t need2 = tk_need(k, w.groups);
+    GQ_TRY(gq_launch(ctx, "gq_topk_merge", topk_merge_kernel<false>, dim3(static_cast<uint32_t>(w.groups)),
+                     dim3(TK_THREADS), 0, s, w.first, w.blocks, tk_merge_per(k), k, need1, need2, w.second, d, val_out,
+                     rowid_out, n_out_dev));
+    return gq_launch(ctx, "gq_topk_merge", topk_merge_kernel<true>, dim3(1), dim3(TK_THREADS), 0, s, w.second,
+                     w.groups, w.groups, k, need2, 0u, tk_lists{}, d, val_out, rowid_out, n_out_dev);
 }
 
 }  // extern "C"

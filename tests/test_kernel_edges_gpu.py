@@ -101,3 +101,24 @@ def test_small_groupby_more_groups_than_the_bound(ctx):
     out = gq.alloc_groups(ctx, 400, False, True)
     gq.gq_groupby_agg(ctx, one, one, one, key32=key, max_groups=64, out=out)
     assert ctx.status() == gq.GQ_ERR_CAPACITY
+
+
+# one list, one merge, two merge levels (more than 32768 candidates); rows in
+# order (all of the best in one list), ties, and values that share all or none
+# of their leading digits
+@pytest.mark.parametrize("n,k", [(1, 1), (8192, 2048), (8193, 5), (300_000, 2048), (2_000_003, 64), (2_000_003, 2048)])
+@pytest.mark.parametrize("kind", ["cents", "sorted", "ties", "signed", "equal"])
+def test_topk_lists_and_merges(ctx, n, k, kind):
+    r = np.random.default_rng(n + k)
+    val = {"cents": lambda: r.integers(100, 10_000_000, size=n), "sorted": lambda: np.arange(n) * 7 - 1000,
+           "ties": lambda: r.integers(0, 3, size=n),
+           "signed": lambda: r.integers(-(1 << 63), (1 << 63) - 1, size=n, endpoint=True),
+           "equal": lambda: np.full(n, -5)}[kind]().astype(np.int64)
+    sel = np.flatnonzero(r.random(n) < 0.7).astype(np.int32)
+    for desc in (True, False):
+        for s in (None, sel):
+            ev, er = oracle.topk(val, k, sel=s, descending=desc)
+            v, row, cnt = gq.gq_topk(ctx, dev(val), k, sel=None if s is None else dev(s), descending=desc)
+            c = int(cnt.item())
+            assert c == len(ev)
+            assert np.array_equal(v[:c].cpu().numpy(), ev) and np.array_equal(row[:c].cpu().numpy(), er)
