@@ -374,7 +374,8 @@ typedef struct gq_instance {
 
 typedef struct gq_tuning {
     double load_factor;        /* hash-table load factor (0, 0.9]           */
-    int32_t probe_tile;        /* fact rows per probe work item (multiple of 4096) */
+    int32_t probe_tile;        /* fact rows per probe work item (multiple of 4096;
+                                  a batch too small for all CUs is cut finer)  */
     int32_t build_tile;        /* keys per build work item (multiple of 256) */
     int32_t init_tile;         /* slots per table-fill work item            */
     int32_t lag;               /* probe items of instance i follow the build

@@ -31,7 +31,7 @@
 
 namespace {
 
-constexpr int BT_THREADS = 512;               // 84 VGPRs: three workgroups (24 waves) per CU
+constexpr int BT_THREADS = 512;
 constexpr int BT_TILE_GRAIN = 256;            // build and fill tiles are multiples of this
 constexpr int BT_LDS_GROUP_SLOTS = 1024;
 constexpr int BT_REGION_SLOTS = 4096;              // tables up to this size are built in LDS
@@ -86,7 +86,10 @@ GQ_DEV uint32_t load_acquire(const uint32_t *p)
 }
 
 // Wait until *ctr >= target, for at most `limit` polls (each after a short
-// sleep).  Returns false, in every thread, when the bound ran out: the
+// sleep): relaxed polls, then one acquire.  An acquire invalidates cache lines
+// that the running probes use, and a release writes the L2 back: with one per
+// poll, and a fence beside every count, 48 instances of 1K to 100K keys took
+// 1.91 ms against 0.73.  Returns false, in every thread, when the bound ran out: the
 // caller then skips its work (its inputs are incomplete) and reports
 // GQ_ERR_TIMEOUT, so the kernel still drains its queue and exits.  Every
 // wait here is for items dequeued earlier, so the bound is only reached
@@ -95,7 +98,8 @@ GQ_DEV bool wait_for(const uint32_t *ctr, uint32_t target, int64_t limit, uint32
 {
     if (threadIdx.x == 0) {
         uint32_t ok = 1;
-        for (int64_t polls = 0; load_acquire(ctr) < target; ++polls) {
+        for (int64_t polls = 0;
+             __hip_atomic_load(const_cast<uint32_t *>(ctr), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target; ++polls) {
             if (polls >= limit) {
                 ok = 0;
                 break;
@@ -103,6 +107,7 @@ GQ_DEV bool wait_for(const uint32_t *ctr, uint32_t target, int64_t limit, uint32
             __builtin_amdgcn_s_sleep(2);
         }
         *s_ok = ok;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
     return gq_uniform(*s_ok) != 0;
@@ -111,26 +116,39 @@ GQ_DEV bool wait_for(const uint32_t *ctr, uint32_t target, int64_t limit, uint32
 GQ_DEV void signal_done(uint32_t *ctr)
 {
     __syncthreads();                                     // every thread's work is issued
-    if (threadIdx.x == 0) {
-        __threadfence();                                 // ...and visible device-wide
-        __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    // (the table's words were stored through to memory, so the write-back of
+    // this release finds little to do)
+    if (threadIdx.x == 0) __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 GQ_DEV uint64_t key_hash(int64_t k) { return gq_fmix64(static_cast<uint64_t>(k)); }
 
 // ---------------------------------------------------------------- groups
 // LDS group table of a probe tile.  A slot is one 64-bit word, 0 = empty,
-// else (key << 32) | 1, claimed and published by a single compare-and-swap.
+// else (key << 32) | tag, claimed and published by a single compare-and-swap.
 // Revenue sums are kept split: lo[] sums the low 32 bits (unsigned) and hi[]
 // the high 32 bits (signed) of each row's revenue, so no accumulation needs a
 // returned value; the slot's revenue is hi * 2^32 + lo (exact for < 2^31 rows).
+//
+// The first BT_IDS groups of a tile get an id (tag = 2 + id, 1 = none) and
+// BT_COPIES copies of their sums, one per lane modulo BT_COPIES: an instance
+// has a few dozen groups, and with one set of sums the lanes of a wave meet on
+// them.
+constexpr int BT_IDS = 32;
+constexpr int BT_COPIES = 16;
+
 struct bt_lds {
     uint64_t word[BT_LDS_GROUP_SLOTS];
     uint32_t cnt[BT_LDS_GROUP_SLOTS];
     uint64_t sq[BT_LDS_GROUP_SLOTS];
     uint64_t lo[BT_LDS_GROUP_SLOTS];
     int64_t hi[BT_LDS_GROUP_SLOTS];
+    uint32_t ids;
+    uint32_t slot_of[BT_IDS];
+    uint32_t ccnt[BT_IDS * BT_COPIES];
+    uint64_t csq[BT_IDS * BT_COPIES];
+    uint64_t clo[BT_IDS * BT_COPIES];
+    int64_t chi[BT_IDS * BT_COPIES];
 };
 
 GQ_DEV void lds_clear(bt_lds &T)
@@ -142,15 +160,24 @@ GQ_DEV void lds_clear(bt_lds &T)
         T.lo[s] = 0;
         T.hi[s] = 0;
     }
+    for (int i = threadIdx.x; i < BT_IDS * BT_COPIES; i += BT_THREADS) {
+        T.ccnt[i] = 0;
+        T.csq[i] = 0;
+        T.clo[i] = 0;
+        T.chi[i] = 0;
+    }
+    if (threadIdx.x == 0) T.ids = 0;
 }
 
 GQ_DEV uint64_t group_hash(int32_t k) { return gq_fmix64(static_cast<uint64_t>(static_cast<uint32_t>(k)) * 0x9E3779B97F4A7C15ull); }
 
-// find-or-claim in the LDS group table (wave-uniform loop); -1 when 64 probes fail
-GQ_DEV int lds_group(bt_lds &T, bool active, int32_t key)
+// find-or-claim in the LDS group table (wave-uniform loop); -1 when 64 probes
+// fail.  tag: the group's id + 2, or 1 when it has none (yet).
+GQ_DEV int lds_group(bt_lds &T, bool active, int32_t key, uint32_t &tag)
 {
-    uint32_t s = static_cast<uint32_t>(group_hash(key)) & (BT_LDS_GROUP_SLOTS - 1);
-    const unsigned long long want = (static_cast<unsigned long long>(static_cast<uint32_t>(key)) << 32) | 1ull;
+    uint32_t s = (static_cast<uint32_t>(key) * 0x9E3779B1u) >> (32 - 10);
+    static_assert(BT_LDS_GROUP_SLOTS == 1 << 10, "home slots are 10 hash bits");
+    const unsigned long long want = static_cast<unsigned long long>(static_cast<uint32_t>(key)) << 32;
     int probes = 0, found = -1;
     bool done = !active;
     while (__any(!done)) {
@@ -158,11 +185,19 @@ GQ_DEV int lds_group(bt_lds &T, bool active, int32_t key)
             unsigned long long *wp = reinterpret_cast<unsigned long long *>(&T.word[s]);
             unsigned long long w = __hip_atomic_load(wp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             if (w == 0ull) {
-                w = atomicCAS(wp, 0ull, want);            // claim only an empty slot
-                if (w == 0ull) w = want;
+                w = atomicCAS(wp, 0ull, want | 1ull);     // claim only an empty slot
+                if (w == 0ull) {
+                    w = want | 1ull;
+                    const uint32_t id = atomicAdd(&T.ids, 1u);
+                    if (id < BT_IDS) {
+                        T.slot_of[id] = s;
+                        __hip_atomic_store(wp, want | (2u + id), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                }
             }
-            if (w == want) {
+            if ((w & ~0xffffffffull) == want) {
                 found = static_cast<int>(s);
+                tag = static_cast<uint32_t>(w);
                 done = true;
             } else if (++probes >= 64) {
                 done = true;
@@ -174,15 +209,44 @@ GQ_DEV int lds_group(bt_lds &T, bool active, int32_t key)
     return found;
 }
 
-// one row into LDS slot s (revenue known to fit 64 bits)
-GQ_DEV void lds_add_row(bt_lds &T, int s, int64_t qty, int64_t rev)
+// one row into LDS slot s, or its group's copy (revenue known to fit 64 bits)
+GQ_DEV void lds_add_row(bt_lds &T, int s, uint32_t tag, int64_t qty, int64_t rev)
 {
-    atomicAdd(&T.cnt[s], 1u);
-    atomicAdd(reinterpret_cast<unsigned long long *>(&T.sq[s]), static_cast<unsigned long long>(qty));
-    atomicAdd(reinterpret_cast<unsigned long long *>(&T.lo[s]),
+    const bool copy = tag >= 2u;
+    const uint32_t x = copy ? (tag - 2u) * BT_COPIES + (threadIdx.x & (BT_COPIES - 1)) : static_cast<uint32_t>(s);
+    atomicAdd(copy ? &T.ccnt[x] : &T.cnt[x], 1u);
+    atomicAdd(reinterpret_cast<unsigned long long *>(copy ? &T.csq[x] : &T.sq[x]), static_cast<unsigned long long>(qty));
+    atomicAdd(reinterpret_cast<unsigned long long *>(copy ? &T.clo[x] : &T.lo[x]),
               static_cast<unsigned long long>(static_cast<uint32_t>(static_cast<uint64_t>(rev))));
     const int64_t high = rev >> 32;
-    if (high) atomicAdd(reinterpret_cast<unsigned long long *>(&T.hi[s]), static_cast<unsigned long long>(high));
+    if (high)
+        atomicAdd(reinterpret_cast<unsigned long long *>(copy ? &T.chi[x] : &T.hi[x]),
+                  static_cast<unsigned long long>(high));
+}
+
+// The copies of every id into its slot (16 lanes per id).
+GQ_DEV void lds_fold_copies(bt_lds &T)
+{
+    const uint32_t ids = T.ids < BT_IDS ? T.ids : BT_IDS;
+    const uint32_t id = threadIdx.x / BT_COPIES;
+    static_assert(BT_THREADS / BT_COPIES >= BT_IDS, "one pass covers every id");
+    uint32_t cn = T.ccnt[threadIdx.x % (BT_IDS * BT_COPIES)];
+    uint64_t sq = T.csq[threadIdx.x % (BT_IDS * BT_COPIES)], lo = T.clo[threadIdx.x % (BT_IDS * BT_COPIES)];
+    int64_t hi = T.chi[threadIdx.x % (BT_IDS * BT_COPIES)];
+#pragma unroll
+    for (int d = BT_COPIES / 2; d >= 1; d >>= 1) {
+        cn += __shfl_xor(cn, d, 64);
+        sq += __shfl_xor(sq, d, 64);
+        lo += __shfl_xor(lo, d, 64);
+        hi += __shfl_xor(hi, d, 64);
+    }
+    if (id < ids && threadIdx.x % BT_COPIES == 0) {
+        const uint32_t s = T.slot_of[id];
+        T.cnt[s] += cn;
+        T.sq[s] += sq;
+        T.lo[s] += lo;
+        T.hi[s] += hi;
+    }
 }
 
 GQ_DEV gq_i128 split_total(uint64_t lo_sum, int64_t hi_sum)
@@ -211,7 +275,8 @@ GQ_DEV int64_t global_group(const bt_inst &I, bool active, int32_t key, uint32_t
     bool done = !active;
     while (__any(!done)) {
         if (!done) {
-            const uint32_t st = atomicCAS(&I.gstate[s], 0u, 1u);
+            uint32_t st = __hip_atomic_load(&I.gstate[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (st == 0u) st = atomicCAS(&I.gstate[s], 0u, 1u);   // claim only an empty slot
             if (st == 0u) {
                 __hip_atomic_store(&I.gkey[s], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&I.gstate[s], 2u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -273,12 +338,10 @@ __device__ void item_lds_build(const bt_inst &I, uint32_t *status, unsigned long
         }
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < S; j += BT_THREADS) {
-        bt_slot e;
-        e.key = static_cast<int64_t>(sk[j]);
-        e.payload = sp[j];
-        e.unused = 0;
-        I.table[j] = e;
+    uint64_t *w = reinterpret_cast<uint64_t *>(I.table);
+    for (int j = threadIdx.x; j < 2 * S; j += BT_THREADS) {
+        const uint64_t x = (j & 1) ? static_cast<uint64_t>(static_cast<uint32_t>(sp[j >> 1])) : sk[j >> 1];
+        __hip_atomic_store(&w[j], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -286,13 +349,10 @@ __device__ void item_init(const bt_inst &I, int64_t tile, int init_tile)
 {
     const int64_t S = int64_t(1) << I.log2_slots;
     const int64_t a = tile * init_tile, b = (a + init_tile < S) ? a + init_tile : S;
-    for (int64_t j = a + threadIdx.x; j < b; j += BT_THREADS) {
-        bt_slot e;
-        e.key = BT_EMPTY;
-        e.payload = 0;
-        e.unused = 0;
-        I.table[j] = e;
-    }
+    uint64_t *w = reinterpret_cast<uint64_t *>(I.table);
+    for (int64_t j = 2 * a + threadIdx.x; j < 2 * b; j += BT_THREADS)
+        __hip_atomic_store(&w[j], (j & 1) ? uint64_t{0} : static_cast<uint64_t>(BT_EMPTY), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Build tile: keys in groups of BT_BUILD_ITEMS per thread, so their first
@@ -336,7 +396,7 @@ __device__ void item_build(const bt_inst &I, int64_t tile, int build_tile, uint3
             uint64_t p = 0;
             while (true) {
                 if (prev[c] == static_cast<unsigned long long>(BT_EMPTY)) {
-                    I.table[s[c]].payload = pay[c];
+                    __hip_atomic_store(&I.table[s[c]].payload, pay[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     break;
                 }
                 if (prev[c] == static_cast<unsigned long long>(k[c])) {
@@ -363,6 +423,8 @@ __device__ void item_build(const bt_inst &I, int64_t tile, int build_tile, uint3
 // phase's loads are all in flight together.
 constexpr int BT_CHUNK_ITEMS = 4;
 constexpr int BT_CHUNK = BT_THREADS * BT_CHUNK_ITEMS;
+constexpr int BT_MIN_TILE = 2 * BT_CHUNK;      // the finest probe tile a batch is cut into
+constexpr int64_t BT_GRID = 768;               // three workgroups on each of 256 CUs
 
 __device__ void item_probe(const bt_inst &I, int64_t tile, int tile_rows, bt_lds &T, uint32_t *status)
 {
@@ -389,28 +451,44 @@ __device__ void item_probe(const bt_inst &I, int64_t tile, int tile_rows, bt_lds
         }
         uint64_t s[BT_CHUNK_ITEMS];
         int4 v[BT_CHUNK_ITEMS];
+        uint32_t pend = 0;                             // rows still probing, one bit per item
 #pragma unroll
         for (int c = 0; c < BT_CHUNK_ITEMS; ++c) {
             s[c] = key_hash(k[c]) >> (64 - L);
-            if (pass[c]) v[c] = *reinterpret_cast<const int4 *>(&I.table[s[c]]);
+            if (pass[c]) {
+                pend |= 1u << c;
+                v[c] = *reinterpret_cast<const int4 *>(&I.table[s[c]]);
+            }
         }
+        // each step settles the rows whose slot arrived and loads the next
+        // slot of all the others together
         bool hit[BT_CHUNK_ITEMS];
         int32_t g[BT_CHUNK_ITEMS];
 #pragma unroll
         for (int c = 0; c < BT_CHUNK_ITEMS; ++c) {
             hit[c] = false;
             g[c] = 0;
-            if (pass[c]) {
-                int64_t sk = (static_cast<int64_t>(static_cast<uint32_t>(v[c].y)) << 32) | static_cast<uint32_t>(v[c].x);
-                uint64_t p = 0;
-                while (sk != k[c] && sk != BT_EMPTY && p < mask) {
+        }
+        for (uint64_t step = 0;; ++step) {
+#pragma unroll
+            for (int c = 0; c < BT_CHUNK_ITEMS; ++c) {
+                if ((pend >> c) & 1u) {
+                    const int64_t sk =
+                        (static_cast<int64_t>(static_cast<uint32_t>(v[c].y)) << 32) | static_cast<uint32_t>(v[c].x);
+                    if (sk == k[c]) {
+                        hit[c] = true;
+                        g[c] = v[c].z;
+                    }
+                    if (sk == k[c] || sk == BT_EMPTY) pend &= ~(1u << c);
+                }
+            }
+            if (!__any(pend != 0) || step >= mask) break;
+#pragma unroll
+            for (int c = 0; c < BT_CHUNK_ITEMS; ++c) {
+                if ((pend >> c) & 1u) {
                     s[c] = (s[c] + 1) & mask;
                     v[c] = *reinterpret_cast<const int4 *>(&I.table[s[c]]);
-                    sk = (static_cast<int64_t>(static_cast<uint32_t>(v[c].y)) << 32) | static_cast<uint32_t>(v[c].x);
-                    ++p;
                 }
-                hit[c] = sk == k[c];
-                g[c] = v[c].z;
             }
         }
         int64_t q[BT_CHUNK_ITEMS], pr[BT_CHUNK_ITEMS], ds[BT_CHUNK_ITEMS];
@@ -423,16 +501,23 @@ __device__ void item_probe(const bt_inst &I, int64_t tile, int tile_rows, bt_lds
         }
 #pragma unroll
         for (int c = 0; c < BT_CHUNK_ITEMS; ++c) {
-            const gq_i128 rev = hit[c] ? gq_revenue(pr[c], I.rev_scale, ds[c]) : gq_i128{0, 0};
-            const bool fits = rev.hi == (static_cast<int64_t>(rev.lo) >> 63);
-            const int slot = lds_group(T, hit[c] && fits, g[c]);
-            if (hit[c] && fits && slot >= 0) lds_add_row(T, slot, q[c], static_cast<int64_t>(rev.lo));
+            int64_t narrow;
+            gq_i128 wide{0, 0};
+            const bool fits = gq_revenue_narrow(hit[c], pr[c], I.rev_scale, ds[c], narrow, wide);
+            uint32_t tag = 1;
+            const int slot = lds_group(T, hit[c] && fits, g[c], tag);
+            if (hit[c] && fits && slot >= 0) lds_add_row(T, slot, tag, q[c], narrow);
             // a full LDS table or a revenue wider than 64 bits goes to the global table
             const bool spill = hit[c] && (!fits || slot < 0);
-            const int64_t gs = global_group(I, spill, g[c], status);
-            if (spill && gs >= 0) global_add(I, gs, 1, static_cast<uint64_t>(q[c]), rev);
+            if (__any(spill)) {
+                if (fits) wide = gq_i128{static_cast<uint64_t>(narrow), narrow >> 63};
+                const int64_t gs = global_group(I, spill, g[c], status);
+                if (spill && gs >= 0) global_add(I, gs, 1, static_cast<uint64_t>(q[c]), wide);
+            }
         }
     }
+    __syncthreads();
+    lds_fold_copies(T);
     __syncthreads();
     for (int s = threadIdx.x; s < BT_LDS_GROUP_SLOTS; s += BT_THREADS) {
         const uint64_t w = T.word[s];
@@ -533,18 +618,19 @@ __global__ __launch_bounds__(BT_THREADS) void batch_kernel(const bt_inst *__rest
                 item_probe(I, tile, probe_tile, T, status);
             else if (threadIdx.x == 0)
                 inst_raise(I, status, GQ_ERR_TIMEOUT);
+            // Everything a probe item leaves behind is written by device-scope
+            // atomics, and emit_groups reads it by device-scope atomic loads:
+            // each wave waits until its own are performed, and the count then
+            // needs no write-back of the L2, as a release would make.
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
             if (threadIdx.x == 0) {
-                __threadfence();
                 const uint32_t prev =
-                    __hip_atomic_fetch_add(&I.counters[2], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(&I.counters[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 s_last = (prev + 1 == static_cast<uint32_t>(I.probe_items)) ? 1u : 0u;
             }
             __syncthreads();
-            if (gq_uniform(s_last)) {
-                __threadfence();
-                emit_groups(I, status);
-            }
+            if (gq_uniform(s_last)) emit_groups(I, status);
         }
     }
 }
@@ -586,6 +672,7 @@ struct bt_plan {
     int64_t total_items = 0;
     size_t bytes = 0;              // workspace bytes
     size_t zero_bytes = 0;         // prefix to clear (counters, group tables)
+    int probe_tile = 0;            // fact rows per probe item
 };
 
 bool valid_tuning(const gq_tuning &t)
@@ -601,6 +688,15 @@ bool valid_tuning(const gq_tuning &t)
 bt_plan make_plan(const gq_instance *in, int n, const gq_tuning &t, char *base)
 {
     bt_plan pl;
+    // a batch with fewer probe tiles than workgroups is cut finer (8 instances
+    // of up to 200K rows in 131,072-row tiles: 589 -> 178 us)
+    pl.probe_tile = t.probe_tile;
+    while (pl.probe_tile > BT_MIN_TILE) {
+        int64_t tiles = 0;
+        for (int i = 0; i < n; ++i) tiles += (in[i].n + pl.probe_tile - 1) / pl.probe_tile;
+        if (tiles >= BT_GRID) break;
+        pl.probe_tile = std::max(BT_MIN_TILE, pl.probe_tile / 2 / BT_CHUNK * BT_CHUNK);
+    }
     gq_carver c(base);
     uint32_t *work = c.take<uint32_t>(64);
     (void)work;
@@ -646,7 +742,7 @@ bt_plan make_plan(const gq_instance *in, int n, const gq_tuning &t, char *base)
         const bool lds = slots <= BT_REGION_SLOTS;
         I.init_items = lds ? 0 : static_cast<int32_t>((slots + t.init_tile - 1) / t.init_tile);
         I.build_items = lds ? 1 : static_cast<int32_t>((s.m + t.build_tile - 1) / t.build_tile);
-        I.probe_items = static_cast<int32_t>((s.n + t.probe_tile - 1) / t.probe_tile);
+        I.probe_items = static_cast<int32_t>((s.n + pl.probe_tile - 1) / pl.probe_tile);
     }
     // queue order: setup (init + build) of instance i, then probes of instance i - lag
     auto push = [&](int kind, int i, int64_t cnt) {
@@ -763,12 +859,12 @@ gq_status gq_batch_join_agg(gq_ctx *ctx, const gq_instance *inst, int n_inst, co
     GQ_TRY(gq_launch(ctx, "gq_batch_zero", batch_zero_counts_kernel, dim3((n_inst + 255) / 256), dim3(256), 0, s,
                      static_cast<const bt_inst *>(d_insts), n_inst));
     if (pl.total_items > 0) {
-        // three 48 KiB-LDS workgroups fit a CU
+        // three 51 KiB-LDS workgroups fit a CU by LDS, two by registers
         const uint32_t grid = static_cast<uint32_t>(std::min<int64_t>(pl.total_items, int64_t(ctx->num_cus) * 3));
         const int nsegs = static_cast<int>(pl.segs.size());
         GQ_TRY(gq_launch(ctx, "gq_batch", batch_kernel, dim3(grid), dim3(BT_THREADS), 0, s,
                          static_cast<const bt_inst *>(d_insts), static_cast<const bt_seg *>(d_segs), nsegs,
-                         pl.total_items, work, t.init_tile, t.build_tile, t.probe_tile, ctx->wait_limit,
+                         pl.total_items, work, t.init_tile, t.build_tile, pl.probe_tile, ctx->wait_limit,
                          ctx->status_dev));
     }
     if (!inst_status_dev) return GQ_OK;

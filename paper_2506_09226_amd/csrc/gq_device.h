@@ -232,6 +232,22 @@ GQ_DEV gq_i128 gq_revenue(int64_t price, int64_t scale, int64_t disc)
     return out;
 }
 
+// price * (scale - disc) of the active lanes: true if it fits 64 bits, and is
+// then in `narrow`, else it is in `wide`.  When every active lane's factors fit
+// 32 bits (one test for the wave), a single 32 x 32 multiplication gives it.
+GQ_DEV bool gq_revenue_narrow(bool act, int64_t price, int64_t scale, int64_t disc, int64_t &narrow, gq_i128 &wide)
+{
+    const bool small = scale == static_cast<int32_t>(scale) && price == static_cast<int32_t>(price) &&
+                       disc == static_cast<int32_t>(disc) && scale - disc == static_cast<int32_t>(scale - disc);
+    if (!__any(act && !small)) {
+        narrow = static_cast<int64_t>(static_cast<int32_t>(price)) * static_cast<int32_t>(scale - disc);
+        return true;
+    }
+    wide = gq_revenue(price, scale, disc);
+    narrow = static_cast<int64_t>(wide.lo);
+    return wide.hi == (narrow >> 63);
+}
+
 // Correctly rounded (nearest-even) conversion of a 128-bit integer to double:
 // normalize the magnitude to 64 bits, fold the discarded bits into a sticky
 // bit, convert (one rounding), scale by a power of two (exact).

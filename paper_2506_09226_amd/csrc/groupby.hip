@@ -519,22 +519,6 @@ GQ_DEV uint64_t gs_hash(int64_t k64, int32_t k32)
     return static_cast<uint64_t>(x) << 8;            // where lds_home looks
 }
 
-// price * (scale - disc) of the active lanes, in `wide`; `narrow` tells
-// whether it fits 64 bits.  When every active lane's factors fit 32 bits
-// (one test for the wave), a single 32 x 32 multiplication gives it.
-GQ_DEV bool gs_revenue(bool act, int64_t price, int64_t scale, int64_t disc, int64_t &narrow, gq_i128 &wide)
-{
-    const bool small = scale == static_cast<int32_t>(scale) && price == static_cast<int32_t>(price) &&
-                       disc == static_cast<int32_t>(disc) && scale - disc == static_cast<int32_t>(scale - disc);
-    if (!__any(act && !small)) {
-        narrow = static_cast<int64_t>(static_cast<int32_t>(price)) * static_cast<int32_t>(scale - disc);
-        return true;
-    }
-    wide = gq_revenue(price, scale, disc);
-    narrow = static_cast<int64_t>(wide.lo);
-    return wide.hi == (narrow >> 63);
-}
-
 // Each workgroup adds its share of the rows up in LDS and writes its groups
 // to its own stretch of the workspace (cap groups; the rest, and rows that
 // found no LDS slot, go to the global table).  The last workgroup to finish
@@ -618,7 +602,7 @@ __global__ __launch_bounds__(GS_THREADS) void gb_small_kernel(gb_args a, gtable 
         for (int c = 0; c < GS_BATCH; ++c) {
             int64_t rev;
             gq_i128 wide{0, 0};
-            const bool narrow = gs_revenue(act[c], pv[c], a.rev_scale, dv[c], rev, wide);
+            const bool narrow = gq_revenue_narrow(act[c], pv[c], a.rev_scale, dv[c], rev, wide);
             const int s = lds_find(T, act[c], gs_hash(k64[c], k32[c]), k64[c], k32[c]);
             if (act[c] && s >= 0) {
                 uint32_t id = __hip_atomic_load(&S.id[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);

@@ -122,3 +122,33 @@ def test_topk_lists_and_merges(ctx, n, k, kind):
             c = int(cnt.item())
             assert c == len(ev)
             assert np.array_equal(v[:c].cpu().numpy(), ev) and np.array_equal(row[:c].cpu().numpy(), er)
+
+
+# batches of 1..40 groups per instance around the 32 groups with copies, with
+# tiles cut finer than asked for, and instances built in LDS and by device CAS
+@pytest.mark.parametrize("groups,tile", [(1, 8192), (32, 131_072), (33, 4096), (60, 524_288)])
+def test_batch_tiles_and_group_copies(ctx, groups, tile):
+    r = np.random.default_rng(groups)
+    specs, exp = [], []
+    for m, n in [(1, 5), (700, 4095), (3000, 4097), (20_000, 150_001), (60_000, 333_333)]:
+        key = r.permutation(np.arange(m) * 7919 - 12345).astype(np.int64)
+        attr = r.integers(-groups, 0, size=m).astype(np.int32)
+        fk = np.where(r.random(n) < 0.9, key[r.integers(0, m, size=n)], -5)
+        date = r.integers(0, 100, size=n).astype(np.int32)
+        qty, disc = r.integers(-9, 50, size=n), r.integers(0, 11, size=n)
+        price = r.integers(0, 10_000_000, size=n)
+        price[r.random(n) < 0.01] = 1 << 58                    # revenues past 32 bits and past 64
+        sel = np.flatnonzero((date >= 0) & (date < 60)).astype(np.int32)
+        prow, pay = oracle.join(key, attr, fk, sel)
+        exp.append(oracle.groupby(len(prow), qty, price, disc, rowid=prow, key32=pay))
+        specs.append({"dim_key": dev(key), "dim_attr": dev(attr), "fk": dev(fk), "date": dev(date), "qty": dev(qty),
+                      "price": dev(price), "disc": dev(disc), "date_lo": 0, "date_hi": 60,
+                      "out": gq.alloc_groups(ctx, 64, False, True)})
+    inst = gq.make_instances(specs)
+    t = gq.gq_default_tuning()
+    t.probe_tile, t.load_factor = tile, 0.6
+    for _ in range(2):
+        gq.gq_batch_join_agg(ctx, inst, t)
+        assert ctx.status() == gq.GQ_OK
+        for sp, e in zip(specs, exp):
+            check_groups(sp["out"], e, "key32")
