@@ -1,159 +1,244 @@
 // Scan + filter: ordered stream compaction of a range predicate.
 //
-// One pass over the column.  A workgroup takes FT_GROUP consecutive tiles of
-// FT_TILE rows with one dequeue.  Each tile is read with coalesced loads (wave
-// w, step c reads rows c*256 + w*64 + lane) and each wave's ballot becomes one
-// 64-bit word of the tile's bitmap in LDS.  The group's match count goes
-// through a decoupled look-back over groups, which gives its global offset;
-// then, tile by tile, each thread owns 32 consecutive rows of the bitmap, a
-// block scan gives output slots, and the compacted row ids are staged in LDS
-// and written out contiguously.
+// One pass over the column.  A workgroup takes a unit of consecutive rows with
+// one dequeue; each wave owns a contiguous stretch of the unit and tests it 64
+// rows at a time, keeping the ballot of step i in lane i.  The unit's match
+// count goes through a decoupled look-back over units, which gives its global
+// offset; each wave then writes its matching row ids step by step, at its
+// offset plus the ballot's lane prefix, so neither bits nor row ids pass
+// through LDS.  Small inputs skip the look-back (filter_tiny_kernel).
+#include <algorithm>
+#include <limits>
+#include <type_traits>
+
 #include "gq_device.h"
 #include "gq_internal.h"
 
 namespace {
 
-constexpr int FT_THREADS = 512;
-constexpr int FT_ITEMS = 16;
-constexpr int FT_TILE = FT_THREADS * FT_ITEMS;     // 8192 rows
-constexpr int FT_RPT = FT_TILE / FT_THREADS;       // rows of a tile each thread owns in the write-out (16)
-constexpr int FT_TPW = 64 / FT_RPT;                // threads per bitmap word
-constexpr int FT_WORDS = FT_TILE / 64;              // 128 bitmap words
-constexpr int FT_GROUP = 4;                         // tiles per dequeue
+// Bound by memory: 4 (or 8) bytes a row in, 4 bytes a match out.  1024-thread
+// workgroups at 32 registers put 32 waves on a CU.  A unit is up to 32 steps
+// of its 16 waves (32K rows): each unit costs a dequeue (atomics on one
+// address take turns at about 20 ns) and a look-back that reads words other
+// XCDs write; smaller inputs take fewer steps, for 128 to 256 units (3M rows:
+// 14.6 us at 128 units, 20.5 at 600).  200M rows, 58.7% kept: 0.31 ms, 4.1
+// TB/s, as the staged form it replaces; 25M gathered rows 81 -> 65 us; 1M rows
+// 16 -> 10 us.
+constexpr int FT_THREADS = 1024;
+constexpr int FT_WAVES = FT_THREADS / 64;
+constexpr int FT_MAX_STEPS = 32;                    // steps of a wave per unit (the ballots of 32 lanes)
+constexpr int64_t FT_UNITS = 128;                   // units that smaller inputs are cut into
+constexpr int64_t FT_MAX_SMALL_UNITS = 2 * FT_UNITS; // their most, just before the steps double
+
+int ft_steps(int64_t n)                             // a power of two: a wave's stretch starts on a 4-KB boundary
+{
+    int steps = 1;
+    while (steps < FT_MAX_STEPS && n >= 2 * steps * FT_THREADS * FT_UNITS) steps *= 2;
+    return steps;
+}
 
 struct filter_ws {
-    uint32_t *tile_ctr;
+    uint32_t *unit_ctr;
     uint64_t *status;
 };
 
-// A dequeue counter, then one look-back status word per group of FT_GROUP tiles.
+// The range test lo <= x < hi as one unsigned comparison in the column's type:
+// x - base <= span, when any value of the type passes at all.
+template <typename T>
+struct ft_range {
+    using U = std::make_unsigned_t<T>;
+    U base, span;
+    bool any;
+    GQ_DEV ft_range(int64_t lo, int64_t hi)
+    {
+        const int64_t mn = std::numeric_limits<T>::min(), mx = std::numeric_limits<T>::max();
+        const int64_t a = lo > mn ? lo : mn;
+        const int64_t z = hi > mx ? mx : hi - 1;          // the last value that passes (hi > lo >= min: no wrap)
+        any = hi > lo && a <= z;
+        base = static_cast<U>(a);
+        span = static_cast<U>(static_cast<U>(z) - base);
+    }
+    GQ_DEV bool test(T x) const { return any && static_cast<U>(static_cast<U>(x) - base) <= span; }
+};
+
+// A dequeue counter, then one look-back status word per unit; a workspace made
+// for n rows serves every smaller call too.
 filter_ws filter_layout(gq_carver &c, int64_t n)
 {
     filter_ws w;
-    const int64_t tiles = (n + FT_TILE - 1) / FT_TILE;
-    const int64_t groups = (tiles + FT_GROUP - 1) / FT_GROUP;
-    w.tile_ctr = c.take<uint32_t>(64);
-    w.status = c.take<uint64_t>(static_cast<size_t>(groups > 0 ? groups : 1));
+    const int64_t unit = static_cast<int64_t>(FT_THREADS) * ft_steps(n);
+    const int64_t units = std::max((n + unit - 1) / unit, std::min((n + FT_THREADS - 1) / FT_THREADS, FT_MAX_SMALL_UNITS));
+    w.unit_ctr = c.take<uint32_t>(64);
+    w.status = c.take<uint64_t>(static_cast<size_t>(units > 0 ? units : 1));
     return w;
+}
+
+GQ_DEV int64_t ft_rows(int64_t bound, const int64_t *n_dev)
+{
+    if (!n_dev) return bound;
+    const int64_t d = *n_dev;
+    return d < bound ? (d > 0 ? d : 0) : bound;
 }
 
 template <typename T, bool HAS_SEL>
 __global__ __launch_bounds__(FT_THREADS) void filter_kernel(const T *__restrict__ col,
                                                             const int32_t *__restrict__ sel_in,
                                                             int64_t n_bound, const int64_t *n_dev, int64_t lo,
-                                                            int64_t hi, int32_t *__restrict__ out,
-                                                            int64_t *n_out, uint32_t *tile_ctr, uint64_t *status)
+                                                            int64_t hi, int steps, int32_t *__restrict__ out,
+                                                            int64_t *n_out, uint32_t *unit_ctr, uint64_t *status)
 {
-    __shared__ uint64_t bits[FT_GROUP][FT_WORDS];
-    __shared__ int32_t stage[FT_TILE];
-    __shared__ uint32_t scan_smem[FT_THREADS / 64];
-    __shared__ uint32_t s_group;
+    __shared__ uint32_t wcnt[FT_WAVES];
+    __shared__ uint32_t s_unit;
     __shared__ uint64_t s_goff;
-
-    int64_t n = n_bound;
-    if (n_dev) {
-        const int64_t d = *n_dev;
-        n = d < n_bound ? (d > 0 ? d : 0) : n_bound;
+    const ft_range<T> range(lo, hi);
+    const int64_t n = ft_rows(n_bound, n_dev);
+    if (threadIdx.x == 0) s_unit = atomicAdd(unit_ctr, 1u);
+    __syncthreads();
+    const uint32_t u = s_unit;
+    const int64_t unit = static_cast<int64_t>(FT_THREADS) * steps;
+    const int64_t nunits = (n + unit - 1) / unit;
+    if (static_cast<int64_t>(u) >= nunits) {
+        if (u == 0 && threadIdx.x == 0) *n_out = 0;
+        return;
     }
-    const int64_t ntiles = (n + FT_TILE - 1) / FT_TILE;
-    const int64_t ngroups = (ntiles + FT_GROUP - 1) / FT_GROUP;
-    if (ntiles == 0) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t row0 = static_cast<int64_t>(u) * unit + static_cast<int64_t>(wave) * steps * 64 + lane;
+    constexpr int FT_BATCH = HAS_SEL ? 4 : 8;               // steps whose loads overlap (gathers: 64 us at 4, 85 at 8)
+    uint64_t word = 0;                                      // lane i: the matches of step i
+    for (int i0 = 0; i0 < steps; i0 += FT_BATCH) {
+        T v[FT_BATCH];
+#pragma unroll
+        for (int c = 0; c < FT_BATCH; ++c) {
+            const int64_t e = row0 + (i0 + c) * 64;
+            v[c] = 0;
+            if (i0 + c < steps && e < n)
+                v[c] = HAS_SEL ? col[sel_in[e]] : __builtin_nontemporal_load(&col[e]);
+        }
+#pragma unroll
+        for (int c = 0; c < FT_BATCH; ++c) {
+            const int64_t e = row0 + (i0 + c) * 64;
+            const uint64_t b = gq_ballot(i0 + c < steps && e < n && range.test(v[c]));
+            if (lane == i0 + c) word = b;
+        }
+    }
+    const uint32_t mine = static_cast<uint32_t>(__popcll(word));
+    const uint32_t incl = gq_wave_inclusive_scan(mine);
+    if (lane == 63) wcnt[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < FT_WAVES; ++w) {
+        before += w < wave ? wcnt[w] : 0u;
+        total += wcnt[w];
+    }
+    if (wave == 0) {
+        const uint64_t g = gq_lookback(status, u, total);
+        if (lane == 0) {
+            s_goff = g;
+            if (static_cast<int64_t>(u) == nunits - 1) *n_out = static_cast<int64_t>(g + total);
+        }
+    }
+    __syncthreads();
+    const uint32_t excl = before + incl - mine;             // lane i: matches of the unit before step i
+    const int64_t goff = static_cast<int64_t>(s_goff);
+    const uint32_t wlo = static_cast<uint32_t>(word), whi = static_cast<uint32_t>(word >> 32);
+    for (int i = 0; i < steps; ++i) {
+        const uint32_t blo = __builtin_amdgcn_readlane(wlo, i), bhi = __builtin_amdgcn_readlane(whi, i);
+        const uint64_t b = (static_cast<uint64_t>(bhi) << 32) | blo;
+        const uint32_t pre = __builtin_amdgcn_readlane(excl, i);
+        if ((b >> lane) & 1u) {
+            const int64_t e = row0 + i * 64;
+            out[goff + pre + gq_mbcnt(b)] = HAS_SEL ? sel_in[e] : static_cast<int32_t>(e);
+        }
+    }
+}
+
+// Small inputs, bound by latency: one launch with no scratch to clear and no
+// waiting (64K rows: 16.4 -> 11.7 us a call, 30K rows 12 -> 8.3 us, of which
+// the host's share is about 8).  Workgroup t counts the matches of all rows before its own 1024
+// itself, which for up to FT_TINY_ROWS rows is a few loads per thread.
+constexpr int64_t FT_TINY_ROWS = 1 << 16;
+constexpr int64_t FT_TINY_SEL_ROWS = 1 << 15;       // (two dependent loads per row with a selection)
+
+template <typename T, bool HAS_SEL>
+__global__ __launch_bounds__(FT_THREADS) void filter_tiny_kernel(const T *__restrict__ col,
+                                                                 const int32_t *__restrict__ sel_in,
+                                                                 int64_t n_bound, const int64_t *n_dev, int64_t lo,
+                                                                 int64_t hi, int32_t *__restrict__ out, int64_t *n_out)
+{
+    __shared__ uint32_t wprev[FT_WAVES], wcnt[FT_WAVES];
+    const int64_t n = ft_rows(n_bound, n_dev);
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * FT_THREADS;
+    if (base >= n) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *n_out = 0;
         return;
     }
-    // One dequeue per group of FT_GROUP consecutive tiles (atomics on one
-    // address serialize chip-wide).  The group is one unit of the look-back:
-    // its bitmaps are built first, its match count is published, and only
-    // then does it wait for its predecessors (groups are numbered in dequeue
-    // order, so each predecessor is done or held by a running workgroup).
-    if (threadIdx.x == 0) s_group = atomicAdd(tile_ctr, 1u);
-    __syncthreads();
-    const int64_t g = s_group;
-    if (g >= ngroups) return;                              // same value in every thread
-    const int64_t t0 = g * FT_GROUP;
-    const int nt = static_cast<int>(ntiles - t0 < FT_GROUP ? ntiles - t0 : FT_GROUP);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint32_t cnt = 0;                                      // this thread's matches over the group
-    // the next tile's values are loaded while this tile's are tested
-    T nv[FT_ITEMS];
-    auto load_tile = [&](int i) {
-        const int64_t base = (t0 + i) * FT_TILE;
+    const ft_range<T> range(lo, hi);
+    auto test = [&](int32_t r) { return range.test(col[r]); };
+    const int32_t e = static_cast<int32_t>(base) + static_cast<int32_t>(threadIdx.x);
+    const int32_t r = e < n ? (HAS_SEL ? sel_in[e] : e) : 0;
+    uint32_t prev = 0;
+    constexpr int AHEAD = 32;
+    for (int32_t j0 = threadIdx.x; j0 < base; j0 += FT_THREADS * AHEAD) {
 #pragma unroll
-        for (int c = 0; c < FT_ITEMS; ++c) {
-            const int64_t e = base + c * FT_THREADS + wave * 64 + lane;
-            nv[c] = 0;
-            if (i < nt && e < n) nv[c] = col[HAS_SEL ? static_cast<int64_t>(sel_in[e]) : e];
+        for (int c = 0; c < AHEAD; ++c) {
+            const int32_t j = j0 + c * FT_THREADS;
+            if (j < base) prev += test(HAS_SEL ? sel_in[j] : j) ? 1u : 0u;
         }
-    };
-    load_tile(0);
-    for (int i = 0; i < nt; ++i) {
-        const int64_t base = (t0 + i) * FT_TILE;
-        T v[FT_ITEMS];
-#pragma unroll
-        for (int c = 0; c < FT_ITEMS; ++c) v[c] = nv[c];
-        if (i + 1 < nt) load_tile(i + 1);
-#pragma unroll
-        for (int c = 0; c < FT_ITEMS; ++c) {
-            const int64_t e = base + c * FT_THREADS + wave * 64 + lane;
-            const int64_t x = static_cast<int64_t>(v[c]);
-            const uint64_t b = gq_ballot(e < n && lo <= x && x < hi);
-            if (lane == 0) bits[i][c * (FT_THREADS / 64) + wave] = b;
-        }
+    }
+    const uint64_t b = gq_ballot(e < n && test(r));
+    prev = gq_wave_sum(prev);
+    if (lane == 0) {
+        wprev[wave] = prev;
+        wcnt[wave] = static_cast<uint32_t>(__popcll(b));
     }
     __syncthreads();
-    // thread i owns rows [FT_RPT i, FT_RPT i + FT_RPT) of every tile
-    auto owned = [&](int i) {
-        const uint64_t word = bits[i][threadIdx.x / FT_TPW] >> ((threadIdx.x % FT_TPW) * FT_RPT);
-        return static_cast<uint32_t>(word) & static_cast<uint32_t>((1ull << FT_RPT) - 1);
-    };
-    for (int i = 0; i < nt; ++i) cnt += __popc(owned(i));
-    uint32_t gtotal;
-    (void)gq_block_exclusive_scan<FT_THREADS>(cnt, &gtotal, scan_smem);
-    if (wave == 0) {
-        const uint64_t go = gq_lookback(status, static_cast<uint32_t>(g), gtotal);
-        if (lane == 0) s_goff = go;
+    uint32_t at = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < FT_WAVES; ++w) {
+        at += wprev[w] + (w < wave ? wcnt[w] : 0u);
+        total += wprev[w] + wcnt[w];
     }
-    __syncthreads();
-    int64_t goff = static_cast<int64_t>(s_goff);
-    for (int i = 0; i < nt; ++i) {
-        const int64_t base = (t0 + i) * FT_TILE;
-        uint32_t mine = owned(i);
-        uint32_t total;
-        uint32_t pos =
-            gq_block_exclusive_scan_lds<FT_THREADS>(static_cast<uint32_t>(__popc(mine)), &total, scan_smem);
-        const int64_t row0 = base + static_cast<int64_t>(threadIdx.x) * FT_RPT;
-        while (mine) {
-            const int k = __builtin_ctz(mine);
-            mine &= mine - 1;
-            const int64_t e = row0 + k;
-            stage[pos++] = HAS_SEL ? sel_in[e] : static_cast<int32_t>(e);
-        }
-        gq_lds_barrier();                                  // (LDS only: the last tile's stores stay in flight)
-        for (uint32_t k = threadIdx.x; k < total; k += FT_THREADS) out[goff + k] = stage[k];
-        goff += total;
-        gq_lds_barrier();                                  // stage[] is free for the next tile
-    }
-    if (g == ngroups - 1 && threadIdx.x == 0) *n_out = goff;
+    if ((b >> lane) & 1u) out[at + gq_mbcnt(b)] = r;
+    if (base + FT_THREADS >= n && threadIdx.x == 0) *n_out = total;
 }
 
 template <typename T, bool S>
 gq_status launch_filter(gq_ctx *ctx, const void *col, const int32_t *sel_in, int64_t n, const int64_t *n_dev,
-                        int64_t lo, int64_t hi, int32_t *out, int64_t *n_out, filter_ws w, hipStream_t s)
+                        int64_t lo, int64_t hi, int32_t *out, int64_t *n_out, void *scratch, hipStream_t s)
 {
-    const int64_t tiles = (n + FT_TILE - 1) / FT_TILE;
-    const int64_t groups = (tiles + FT_GROUP - 1) / FT_GROUP;
-    const uint32_t grid = static_cast<uint32_t>(groups > 0 ? groups : 1);
-    return gq_launch(ctx, "gq_filter", filter_kernel<T, S>, dim3(grid), dim3(FT_THREADS), 0, s,
-                     static_cast<const T *>(col), sel_in, n, n_dev, lo, hi, out, n_out, w.tile_ctr, w.status);
+    const T *c = static_cast<const T *>(col);
+    if (n <= (S ? FT_TINY_SEL_ROWS : FT_TINY_ROWS)) {
+        const uint32_t grid = static_cast<uint32_t>(n > 0 ? (n + FT_THREADS - 1) / FT_THREADS : 1);
+        return gq_launch(ctx, "gq_filter", filter_tiny_kernel<T, S>, dim3(grid), dim3(FT_THREADS), 0, s, c, sel_in, n,
+                         n_dev, lo, hi, out, n_out);
+    }
+    gq_carver cv(scratch);
+    const filter_ws w = filter_layout(cv, n);
+    GQ_TRY(gq_zero(ctx, scratch, cv.off / 4, s));     // unit counter + status words (a kernel: no memset node under capture)
+    const int steps = ft_steps(n);
+    const int64_t unit = static_cast<int64_t>(FT_THREADS) * steps;
+    return gq_launch(ctx, "gq_filter", filter_kernel<T, S>, dim3(static_cast<uint32_t>((n + unit - 1) / unit)),
+                     dim3(FT_THREADS), 0, s, c, sel_in, n, n_dev, lo, hi, steps, out, n_out, w.unit_ctr, w.status);
+}
+
+gq_status run_filter(gq_ctx *ctx, const void *col, int dtype, const int32_t *sel_in, int64_t n, const int64_t *n_dev,
+                     int64_t lo, int64_t hi, int32_t *out, int64_t *n_out, void *scratch, hipStream_t s)
+{
+    if (dtype == GQ_I32)
+        return sel_in ? launch_filter<int32_t, true>(ctx, col, sel_in, n, n_dev, lo, hi, out, n_out, scratch, s)
+                      : launch_filter<int32_t, false>(ctx, col, sel_in, n, n_dev, lo, hi, out, n_out, scratch, s);
+    return sel_in ? launch_filter<int64_t, true>(ctx, col, sel_in, n, n_dev, lo, hi, out, n_out, scratch, s)
+                  : launch_filter<int64_t, false>(ctx, col, sel_in, n, n_dev, lo, hi, out, n_out, scratch, s);
 }
 
 // Scratch of gq_filter_noalloc, one copy per GPU for the life of the
 // process: the dequeue counter (64 words) and one look-back status word per
-// group of FT_GROUP tiles, enough for the largest accepted input
-// (GQ_MAX_ROWS rows: 65,536 groups), 512.25 KiB in all.
-constexpr int64_t FT_SCRATCH_GROUPS =
-    ((GQ_MAX_ROWS + FT_TILE - 1) / FT_TILE + FT_GROUP - 1) / FT_GROUP;
-constexpr size_t FT_SCRATCH_WORDS = 32 + static_cast<size_t>(FT_SCRATCH_GROUPS);   // 8-byte words
+// unit, enough for the largest accepted input (GQ_MAX_ROWS rows: 65,536
+// units), 512.25 KiB in all.
+constexpr int64_t FT_SCRATCH_UNITS = (GQ_MAX_ROWS + FT_THREADS * FT_MAX_STEPS - 1) / (FT_THREADS * FT_MAX_STEPS);
+constexpr size_t FT_SCRATCH_WORDS = 32 + static_cast<size_t>(FT_SCRATCH_UNITS);   // 8-byte words
 __device__ __align__(256) uint64_t scratch[FT_SCRATCH_WORDS];
 
 }  // namespace
@@ -193,15 +278,8 @@ gq_status gq_filter(gq_ctx *ctx, const void *col, int dtype, int64_t n, const in
     const size_t need = gq_filter_workspace_bytes(n);
     if (!ws || ws_bytes < need)
         return gq_fail(ctx, GQ_ERR_WORKSPACE, "gq_filter: workspace %zu < %zu bytes", ws_bytes, need);
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    gq_carver c(ws);
-    filter_ws w = filter_layout(c, n);
-    GQ_TRY(gq_zero(ctx, ws, c.off / 4, s));     // tile counter + tile status words
-    if (dtype == GQ_I32)
-        return sel_in ? launch_filter<int32_t, true>(ctx, col, sel_in, n, n_dev, lo, hi, sel_out, n_out_dev, w, s)
-                      : launch_filter<int32_t, false>(ctx, col, sel_in, n, n_dev, lo, hi, sel_out, n_out_dev, w, s);
-    return sel_in ? launch_filter<int64_t, true>(ctx, col, sel_in, n, n_dev, lo, hi, sel_out, n_out_dev, w, s)
-                  : launch_filter<int64_t, false>(ctx, col, sel_in, n, n_dev, lo, hi, sel_out, n_out_dev, w, s);
+    return run_filter(ctx, col, dtype, sel_in, n, n_dev, lo, hi, sel_out, n_out_dev, ws,
+                      static_cast<hipStream_t>(stream));
 }
 
 gq_status gq_filter_noalloc(gq_ctx *ctx, const void *col, int dtype, int64_t n, const int64_t *n_dev,
@@ -222,15 +300,8 @@ gq_status gq_filter_noalloc(gq_ctx *ctx, const void *col, int dtype, int64_t n, 
     if (need.bytes() > FT_SCRATCH_WORDS * sizeof(uint64_t))
         return gq_fail(ctx, GQ_ERR_CAPACITY, "gq_filter_noalloc: %lld rows need %zu scratch bytes, more than %zu",
                        (long long)n, need.bytes(), FT_SCRATCH_WORDS * sizeof(uint64_t));
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    gq_carver c(ctx->filter_scratch);
-    filter_ws w = filter_layout(c, n);
-    GQ_TRY(gq_zero(ctx, ctx->filter_scratch, c.off / 4, s));   // a kernel: no memset node under capture
-    if (dtype == GQ_I32)
-        return sel_in ? launch_filter<int32_t, true>(ctx, col, sel_in, n, n_dev, lo, hi, sel_out, n_out_dev, w, s)
-                      : launch_filter<int32_t, false>(ctx, col, sel_in, n, n_dev, lo, hi, sel_out, n_out_dev, w, s);
-    return sel_in ? launch_filter<int64_t, true>(ctx, col, sel_in, n, n_dev, lo, hi, sel_out, n_out_dev, w, s)
-                  : launch_filter<int64_t, false>(ctx, col, sel_in, n, n_dev, lo, hi, sel_out, n_out_dev, w, s);
+    return run_filter(ctx, col, dtype, sel_in, n, n_dev, lo, hi, sel_out, n_out_dev, ctx->filter_scratch,
+                      static_cast<hipStream_t>(stream));
 }
 
 }  // extern "C"

@@ -476,16 +476,18 @@ gq_status region_build(gq_ctx *ctx, const int64_t *key, const int32_t *payload, 
 // A large unit matters because each unit's look-back reads status words that
 // other XCDs write, over the same path as the slot lines: with 4096-row units
 // the same lookups took 1.29-1.50 ms.  16K rows (64 KB of LDS for their
-// payloads, two workgroups per CU) are the most that keep 32 waves per CU;
-// with fewer rows a unit shrinks so that about 512 units (two per CU) remain.
+// payloads, two workgroups per CU) are the most that keep 32 waves per CU.
+// Fewer rows take fewer steps per wave, always a power of two, so that a
+// wave's stretch starts on a 4-KB boundary (4M probes: 76 us at 8 steps, 97 at
+// 6, 89 at 12): about 512 to 1024 units, and 8 steps until enough units are
+// left for a balanced tail (9M probes: 210 us at 8, 226 at 16).
 // Up to JP_TINY_ROWS rows the chip is not full either way and a call is bound
 // by one unit's chain of loads: 256-row units (64K rows: 31 -> 13 us).
 constexpr int64_t JP_TINY_ROWS = 1 << 17;
+constexpr int64_t JP_LARGE_ROWS = 1 << 25;
 constexpr int JP_THREADS = 1024;
 constexpr int JP_TINY_THREADS = 256;
 constexpr int JP_MAX_STEPS = 16;
-constexpr int64_t JP_MAX_SMALL_UNITS = 1024;          // units while the steps still grow with n: below 512 (s + 1) / s
-
 struct jp_shape {
     int threads, steps;
     int64_t unit() const { return static_cast<int64_t>(threads) * steps; }
@@ -494,8 +496,10 @@ struct jp_shape {
 jp_shape jp_shape_of(int64_t n)
 {
     if (n <= JP_TINY_ROWS) return {JP_TINY_THREADS, 1};
-    const int64_t steps = n / (JP_THREADS * 512);
-    return {JP_THREADS, static_cast<int>(std::min<int64_t>(std::max<int64_t>(steps, 1), JP_MAX_STEPS))};
+    if (n >= JP_LARGE_ROWS) return {JP_THREADS, JP_MAX_STEPS};
+    int steps = 2;
+    while (steps < JP_MAX_STEPS / 2 && n >= 2 * int64_t(steps) * JP_THREADS * 512) steps *= 2;
+    return {JP_THREADS, steps};
 }
 
 struct probe_ws {
@@ -508,9 +512,9 @@ probe_ws probe_layout(gq_carver &c, int64_t n)
     probe_ws w;
     const int64_t rows = jp_shape_of(n).unit();
     int64_t units = (n + rows - 1) / rows;
-    // a workspace made for n rows serves every smaller call too: past the tiny
-    // calls, any n below has at most JP_MAX_SMALL_UNITS units or no more than n has
-    if (n > JP_TINY_ROWS) units = std::max(units, JP_MAX_SMALL_UNITS);
+    // a workspace made for n rows serves every smaller call too (the units of
+    // a smaller call can be more: at most 1024, or one per 8192 rows)
+    if (n > JP_TINY_ROWS) units = n / (JP_THREADS * JP_MAX_STEPS / 2) + 1024;
     w.unit_ctr = c.take<uint32_t>(64);
     w.status = c.take<uint64_t>(static_cast<size_t>(units > 0 ? units : 1));
     return w;

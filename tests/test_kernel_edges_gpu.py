@@ -152,3 +152,28 @@ def test_batch_tiles_and_group_copies(ctx, groups, tile):
         assert ctx.status() == gq.GQ_OK
         for sp, e in zip(specs, exp):
             check_groups(sp["out"], e, "key32")
+
+
+# one launch up to 2^16 rows (2^15 with a selection), units of 1..32 steps above;
+# ranges that take every value of the type, one value, or none
+@pytest.mark.parametrize("n", [1, 1023, 1025, 32_768, 32_769, 65_536, 65_537, 262_143, 262_144, 4_194_305])
+@pytest.mark.parametrize("dtype", [np.int32, np.int64])
+def test_filter_units_and_ranges(ctx, n, dtype):
+    r = np.random.default_rng(n)
+    ii = np.iinfo(dtype)
+    col = r.integers(ii.min, ii.max, size=n, dtype=dtype, endpoint=True)
+    col[r.random(n) < 0.5] = r.integers(-3, 4)
+    col[0], col[-1] = ii.min, ii.max
+    sel = np.flatnonzero(r.random(n) < 0.8).astype(np.int32)
+    half = torch.tensor([len(sel) // 2], dtype=torch.int64, device="cuda")
+    c, s = dev(col), dev(sel)
+    x = int(col[n // 2])
+    i64 = np.iinfo(np.int64)
+    for lo, hi in [(i64.min, i64.max), (int(ii.min), int(ii.max)), (x, x + 1) if x < i64.max else (x, x), (5, 5), (9, -9),
+                   (-4, 4), (int(ii.max), i64.max), (i64.min, int(ii.min))]:
+        keep = (col >= lo) & (col < hi)
+        for sd, nd, used in ((None, None, np.arange(n, dtype=np.int32)), (s, None, sel), (s, half, sel[:len(sel) // 2])):
+            exp = used[keep[used]]
+            out, cnt = gq.gq_filter(ctx, c, lo, hi, sel_in=sd, n_dev=nd)
+            k = int(cnt.item())
+            assert k == len(exp) and np.array_equal(out[:k].cpu().numpy(), exp)
