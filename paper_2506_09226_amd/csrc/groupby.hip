@@ -824,6 +824,7 @@ __global__ __launch_bounds__(256) void gb_table_emit_kernel(gtable g, gq_groups 
 constexpr int GB_MAX_P = 1024;                      // buckets of the tile-staged scatter
 constexpr int GB_MAX_P_WIDE = 8192;                 // buckets of the two-level scatter
 constexpr int64_t GB_CUS = 256;                     // compute units of the MI355X
+constexpr int64_t GB_MIN_BUCKET = 4096;             // rows per bucket below which no bucket is added to fill the CUs
 // Records per thread of a bucket-pass step (loaded one step ahead): four
 // 16-byte records, or two of the wider key64 records, which keeps a
 // 1024-thread workgroup's threads within their 128 registers (with four,
@@ -913,11 +914,12 @@ GQ_DEV void load_key(const gb_args &a, int64_t j, int64_t &k64, int32_t &k32)
 // written as the chunk's row hist[chunk * P + b].
 template <bool K64, bool K32, int PMAX>
 __global__ __launch_bounds__(GB_THREADS) void gb_hist_kernel(gb_args a, int P, int64_t chunk_rows,
-                                                             uint32_t *__restrict__ hist)
+                                                             uint32_t *__restrict__ hist, int64_t *n_groups)
 {
     constexpr int ITEMS = gb_fmt<K64, K32>::ITEMS;
     constexpr int TILE = gb_fmt<K64, K32>::TILE;
     __shared__ uint32_t h[PMAX];
+    if (blockIdx.x == 0 && threadIdx.x == 0) *n_groups = 0;  // (the bucket pass counts the groups from here)
     for (int i = threadIdx.x; i < P; i += GB_THREADS) h[i] = 0;
     __syncthreads();
     const int64_t n = eff_n(a.n_bound, a.n_dev);
@@ -1134,7 +1136,7 @@ constexpr int GL_THREADS = 512;
 constexpr int GL_ITEMS = 8;
 constexpr int GL_TILE = GL_THREADS * GL_ITEMS;      // rows per tile
 constexpr int GL_LINE = 8;                          // records per written line (128 bytes)
-constexpr int64_t GL_CHUNK_ROWS = 8 * GL_TILE;      // rows per hist chunk
+constexpr int64_t GL_MAX_CHUNK = 8 * GL_TILE;       // most rows per hist chunk
 
 template <bool K32>
 __global__ __launch_bounds__(GL_THREADS) void gb_scatter_lines_kernel(gb_args a, int P, int64_t chunk_rows,
@@ -1850,7 +1852,14 @@ gb_plan make_plan(int64_t n, int64_t max_groups, bool k64, bool k32)
     // hist chunks: one tile of the tile scatter (key64 records), or a chunk
     // of the region scatter (16-byte records)
     const int64_t tile = static_cast<int64_t>(GB_THREADS) * 8;        // gb_fmt<>::TILE
-    pl.chunk_rows = (!pl.small && !k64) ? GL_CHUNK_ROWS : tile;
+    pl.chunk_rows = tile;
+    if (!pl.small && !k64) {
+        // as many rows as leave four chunks per CU (the scatter gives each of
+        // its workgroups, one per CU, a whole number of chunks; 5M rows in 32K-
+        // row chunks filled 153 CUs: hist 22 -> 9 us, scatter 82 -> 48)
+        const int64_t tiles = n / (4 * GB_CUS * GL_TILE);
+        pl.chunk_rows = std::min<int64_t>(std::max<int64_t>(tiles, 1) * GL_TILE, GL_MAX_CHUNK);
+    }
     pl.ntiles = n > 0 ? (n + pl.chunk_rows - 1) / pl.chunk_rows : 1;
     pl.words = k64 ? 3 : 2;
     static_assert(2 * GB_CUS <= GS_THREADS, "the final fold holds one workgroup per thread");
@@ -1864,6 +1873,11 @@ gb_plan make_plan(int64_t n, int64_t max_groups, bool k64, bool k32)
         // overrides it for measurements)
         const int64_t per_bucket = (k64 ? 3072 : 4096) * groupby_fill_percent() / 100;
         int64_t P = (max_groups + per_bucket - 1) / per_bucket;
+        // fewer buckets than CUs would leave CUs idle in the bucket pass: up
+        // to one bucket per CU while a bucket keeps GB_MIN_BUCKET rows (3M rows
+        // into 100K groups: bucket pass 80 us in 62 buckets, 32 in 256; 600K
+        // rows into 5000 groups: 178 us in 4 buckets, 18 in 244)
+        P = std::max<int64_t>(P, std::min<int64_t>(GB_CUS, n / GB_MIN_BUCKET));
         // one 1024-thread workgroup per bucket and one per CU at a time: a
         // whole number of rounds over the CUs leaves no idle tail
         if (P > GB_CUS) P = (P + GB_CUS - 1) / GB_CUS * GB_CUS;
@@ -1874,16 +1888,26 @@ gb_plan make_plan(int64_t n, int64_t max_groups, bool k64, bool k32)
         const int64_t mean = (n + pl.P - 1) / pl.P;
         pl.bucket_chunk = std::max<int64_t>(4 * mean, 65536);
         pl.bucket_chunk = (pl.bucket_chunk + 4095) / 4096 * 4096;
-        pl.bucket_grid = pl.P + n / pl.bucket_chunk;
+        // n / bucket_chunk as a bound that grows with n, as every size here
+        // does: a workspace made for n rows serves every smaller call
+        const int64_t extra = std::min<int64_t>((pl.P + 3) / 4, n / 65536);
+        pl.bucket_grid = pl.P + extra;
         // a split bucket has more than bucket_chunk rows and at most
         // 2 rows / bucket_chunk chunks
-        pl.split_max = 2 * (n / pl.bucket_chunk) + 1;
+        pl.split_max = 2 * extra + 1;
         if (pl.wide) {                      // P is a multiple of GB_CUS, so of GB_P1
             pl.P2 = pl.P / GB_P1;
             pl.tiles2 = (n + GB_T2 - 1) / GB_T2 + GB_P1;
         }
     }
     return pl;
+}
+
+// The most hist chunks that a call of up to n rows has (their size doubles
+// with n, so a smaller call can have more: up to 8 per CU).
+int64_t gb_tiles_bound(const gb_plan &pl, int64_t n)
+{
+    return std::max(pl.ntiles, std::min<int64_t>(n / GL_TILE + 1, 8 * GB_CUS));
 }
 
 struct gb_ws {
@@ -1937,7 +1961,8 @@ gb_ws gb_layout(gq_carver &c, const gb_plan &pl, int64_t n, bool k64, bool k32)
     if (!pl.small) {
         const size_t rows = static_cast<size_t>(n > 0 ? n : 1);
         const int P1 = pl.wide ? GB_P1 : pl.P;              // buckets of the tile-staged scatter
-        w.hist = c.take<uint32_t>(static_cast<size_t>(pl.ntiles) * static_cast<size_t>(P1));
+        const int64_t ntiles = gb_tiles_bound(pl, n);
+        w.hist = c.take<uint32_t>(static_cast<size_t>(ntiles) * static_cast<size_t>(P1));
         w.start = c.take<uint32_t>(static_cast<size_t>(pl.P) + 1);
         w.cstart = c.take<uint32_t>(static_cast<size_t>(pl.P) + 1);
         w.order = c.take<uint32_t>(static_cast<size_t>(pl.bucket_grid));
@@ -1945,7 +1970,7 @@ gb_ws gb_layout(gq_carver &c, const gb_plan &pl, int64_t n, bool k64, bool k32)
         w.pcnt = c.take<uint32_t>(static_cast<size_t>(pl.split_max));
         w.part = c.take<char>(static_cast<size_t>(pl.split_max) * static_cast<size_t>(k64 ? 3072 : 4096) *
                               sizeof(gb_part));
-        w.scan_ws = c.take<char>(gq_tile_offsets_workspace(pl.ntiles, P1));
+        w.scan_ws = c.take<char>(gq_tile_offsets_workspace(ntiles, P1));
         w.recs = c.take<uint64_t>(rows * static_cast<size_t>(pl.words));
         w.side = c.take<uint32_t>(rows);
         if (pl.wide) {
@@ -1974,7 +1999,7 @@ gq_status run_groupby(gq_ctx *ctx, const gb_args &a, const gb_plan &pl, const gb
     uint32_t *start1 = pl.wide ? w.startA : w.start;
     uint64_t *recs1 = pl.wide ? w.recs1 : w.recs;
     GQ_TRY(gq_launch(ctx, "gq_groupby_hist", gb_hist_kernel<K64, K32, GB_MAX_P>, dim3(grid), dim3(GB_THREADS), 0, s,
-                     a, P1, pl.chunk_rows, w.hist));
+                     a, P1, pl.chunk_rows, w.hist, out.n_groups));
     const gq_tile_count live{a.n_dev, a.n_bound, pl.chunk_rows};     // tiles past the device row count are idle
     GQ_TRY(gq_tile_offsets(ctx, w.hist, pl.ntiles, P1, start1, w.scan_ws, s, "gq_groupby_scan", &live));
     // XCD x scatters the x-th eighth of the tiles with the workgroups b of
@@ -2066,7 +2091,6 @@ gq_status gq_groupby_agg(gq_ctx *ctx, const gq_groupby_in *in, int64_t max_group
     gq_carver c(ws);
     gb_ws w = gb_layout(c, pl, n, k64, k32);
     GQ_TRY(gq_zero(ctx, ws, w.zero_bytes / 4, s));
-    if (!pl.small) GQ_TRY(gq_zero(ctx, out->n_groups, 2, s));   // (the small path writes it)
     gb_args a{n,       in->n_dev, in->rowid, in->key64,     in->key64_by_rowid, in->key32, in->key32_by_rowid,
               in->qty, in->price, in->disc,  in->rev_scale, in->filter,         in->filter_lo, in->filter_hi};
     if (k64 && k32) return run_groupby<true, true>(ctx, a, pl, w, *out, s);

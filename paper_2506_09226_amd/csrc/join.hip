@@ -440,8 +440,7 @@ gq_status region_build(gq_ctx *ctx, const int64_t *key, const int32_t *payload, 
     build_ws w = build_layout(c, m);
     const int g = L - JR_BITS;
     const int32_t pbytes = 4;
-    static const gq_part_names nm{"gq_join_build_part_hist", "gq_join_build_part_scan", "gq_join_build_part_offsets",
-                                  "gq_join_build_part_scatter"};
+    static const gq_part_names nm{"gq_join_build_part_hist", "gq_join_build_part_scan", "gq_join_build_part_scatter"};
     GQ_TRY(gq_zero(ctx, w.ovf_cnt, 64, s));
     void *in[1] = {const_cast<int32_t *>(payload)};
     if (g <= JS_HIGH) {                             // one pass: its bucket starts are the region starts

@@ -1,6 +1,8 @@
 // Device-wide exclusive scan of uint32 counts (single pass, decoupled
 // look-back).  Used to turn per-(bucket, tile) histograms laid out
 // bucket-major into global output offsets.
+#include <algorithm>
+
 #include "gq_device.h"
 #include "gq_internal.h"
 #include "gq_ops.h"
@@ -193,12 +195,12 @@ __global__ __launch_bounds__(TO_THREADS) void to_final_kernel(uint32_t *__restri
 
 }  // namespace
 
+// (The chunk count for up to ntiles tiles, as a bound that grows with ntiles.)
 size_t gq_tile_offsets_workspace(int64_t ntiles, int P)
 {
     gq_carver c(nullptr);
-    const int64_t chunk = to_chunk_tiles(ntiles);
-    const int64_t nchunks = (ntiles + chunk - 1) / chunk;
-    c.take<uint32_t>(static_cast<size_t>((nchunks > 0 ? nchunks : 1) * P));
+    const int64_t nchunks = std::max(std::min<int64_t>(ntiles / 32, 192), ntiles / 256) + 1;
+    c.take<uint32_t>(static_cast<size_t>(nchunks * P));
     c.take<uint32_t>(static_cast<size_t>(P));
     return c.bytes();
 }

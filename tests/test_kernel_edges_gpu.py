@@ -177,3 +177,39 @@ def test_filter_units_and_ranges(ctx, n, dtype):
             out, cnt = gq.gq_filter(ctx, c, lo, hi, sel_in=sd, n_dev=nd)
             k = int(cnt.item())
             assert k == len(exp) and np.array_equal(out[:k].cpu().numpy(), exp)
+
+
+# the large path around its bucket rules: fewer rows than one bucket per CU
+# needs, just enough, and a chunk size of one to several scatter tiles
+@pytest.mark.parametrize("n", [4097, 100_001, 1_048_577, 5_000_011])
+@pytest.mark.parametrize("groups", [513, 20_000])
+@pytest.mark.parametrize("kind", ["code", "composite"])
+def test_large_groupby_buckets(ctx, n, groups, kind):
+    r = np.random.default_rng(n + groups)
+    qty, disc = r.integers(-50, 50, size=n), r.integers(0, 11, size=n)
+    price = r.integers(0, 10_000_000, size=n)
+    date = r.integers(0, 100, size=n).astype(np.int32)
+    rows = np.flatnonzero(date < 60).astype(np.int32)
+    code = r.integers(0, groups // 2, size=n).astype(np.int32)
+    args = dict(n=n, max_groups=groups, filter_col=dev(date), filter_lo=20, filter_hi=100)
+    used = rows[date[rows] >= 20]
+    pad = np.zeros(n, dtype=np.int32)
+    pad[:len(rows)] = rows
+    args.update(rowid=dev(pad), n_dev=torch.tensor([len(rows)], dtype=torch.int64, device="cuda"))
+    q, p, d = dev(qty), dev(price), dev(disc)
+    if kind == "code":
+        res = gq.gq_groupby_agg(ctx, q, p, d, key32=dev(code), key32_by_rowid=True, **args)
+        exp = oracle.groupby(len(used), qty, price, disc, rowid=used, key32=code[used])
+        assert ctx.status() == gq.GQ_OK
+        check_groups(res, exp, "key32")
+    else:
+        k64 = (code.astype(np.int64) // 2) * (1 << 40) - 7
+        k32 = (code % 2).astype(np.int32)
+        res = gq.gq_groupby_agg(ctx, q, p, d, key64=dev(k64), key64_by_rowid=True, key32=dev(k32), key32_by_rowid=True,
+                                **args)
+        exp = oracle.groupby(len(used), qty, price, disc, rowid=used, key64=k64[used], key32=k32[used])
+        assert ctx.status() == gq.GQ_OK
+        g = res.host()
+        o = np.lexsort((g["key32"], g["key64"]))
+        for f in ("key64", "key32", "count", "sum_qty", "sum_rev_lo", "sum_rev_hi"):
+            assert np.array_equal(g[f][o], exp[f]), f

@@ -22,7 +22,8 @@ def sizes():
 def test_workspace_grows_with_rows(what):
     L = gq.lib()
     for arg in {"partition": (0, 4, 6, 8), "topk": (1, 100, 2048),
-                "groupby": ((1, 0, 0), (25, 0, 1), (64, 1, 0), (512, 0, 1), (512, 1, 1))}.get(what, (None,)):
+                "groupby": ((1, 0, 0), (25, 0, 1), (64, 1, 0), (512, 0, 1), (512, 1, 1), (513, 0, 1),
+                            (100_000, 0, 1), (300_000, 1, 1), (1_500_000, 0, 1), (4_000_000, 1, 1))}.get(what, (None,)):
         last = 0
         for n in sizes():
             b = {"filter": lambda: L.gq_filter_workspace_bytes(n), "probe": lambda: L.gq_join_probe_workspace_bytes(n),
