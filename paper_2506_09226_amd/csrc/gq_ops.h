@@ -14,7 +14,7 @@ gq_status gq_scan_u32(gq_ctx *ctx, uint32_t *data, int64_t n, void *ws, hipStrea
 size_t gq_partition_bits_workspace(int64_t n, int log2p);
 // Kernel names of one use of the partition (for per-kernel timing).
 struct gq_part_names {
-    const char *hist, *scan, *offsets, *scatter;
+    const char *hist, *scan, *scatter;
 };
 gq_status gq_partition_bits(gq_ctx *ctx, const int64_t *key, int64_t n, int log2p, int shift, int ncols,
                             void *const *cols, const int32_t *col_bytes, int64_t *key_out, void *const *cols_out,
@@ -22,7 +22,7 @@ gq_status gq_partition_bits(gq_ctx *ctx, const int64_t *key, int64_t n, int log2
 
 // In place: per-tile bucket counts cnt[t*P + b] (tile-major) become the output
 // offsets of each (tile, bucket) run; start[0..P] receives the bucket starts
-// (start[P] = total).  P <= 8192.  ws: gq_tile_offsets_workspace(ntiles, P).
+// (start[P] = total), and start64, if given, the same as int64.  P <= 8192.  ws: gq_tile_offsets_workspace(ntiles, P).
 size_t gq_tile_offsets_workspace(int64_t ntiles, int P);
 // Optional: only the first ceil(min(*n_dev, n_bound) / tile_rows) of the
 // ntiles tiles hold counts (the rows arrive as a device count); the rest are
@@ -33,7 +33,8 @@ struct gq_tile_count {
     int64_t tile_rows;
 };
 gq_status gq_tile_offsets(gq_ctx *ctx, uint32_t *cnt, int64_t ntiles, int P, uint32_t *start, void *ws,
-                          hipStream_t s, const char *name, const gq_tile_count *live = nullptr);
+                          hipStream_t s, const char *name, const gq_tile_count *live = nullptr,
+                          int64_t *start64 = nullptr);
 
 // Look up, on the current device (the context's), the device address of the
 // filter's static scratch array used by gq_filter_noalloc.

@@ -87,11 +87,6 @@ __global__ __launch_bounds__(PT_THREADS) void part_hist_kernel(const int64_t *__
     for (int b = threadIdx.x; b < P; b += PT_THREADS) hist[static_cast<int64_t>(blockIdx.x) * P + b] = h[b];
 }
 
-__global__ void part_offsets_kernel(const uint32_t *__restrict__ start, int P, int64_t *__restrict__ offsets)
-{
-    for (int b = threadIdx.x; b <= P; b += blockDim.x) offsets[b] = static_cast<int64_t>(start[b]);
-}
-
 template <int LOG2P, int ITEMS>
 __global__ __launch_bounds__(PT_THREADS) void part_scatter_kernel(const int64_t *__restrict__ key, int64_t n,
                                                                   int shift, const uint32_t *__restrict__ gofs,
@@ -279,9 +274,7 @@ gq_status run_partition_items(gq_ctx *ctx, const int64_t *key, int64_t n, int sh
     const uint32_t grid = static_cast<uint32_t>(ntiles);
     GQ_TRY(gq_launch(ctx, nm.hist, part_hist_kernel<LOG2P, ITEMS>, dim3(grid), dim3(PT_THREADS), 0, s, key, n,
                      shift, w.hist));
-    GQ_TRY(gq_tile_offsets(ctx, w.hist, ntiles, P, w.start, w.scan_ws, s, nm.scan));
-    GQ_TRY(gq_launch(ctx, nm.offsets, part_offsets_kernel, dim3(1), dim3(256), 0, s,
-                     static_cast<const uint32_t *>(w.start), P, offsets));
+    GQ_TRY(gq_tile_offsets(ctx, w.hist, ntiles, P, w.start, w.scan_ws, s, nm.scan, nullptr, offsets));
     if (n == 0) return GQ_OK;
     return gq_launch(ctx, nm.scatter, part_scatter_kernel<LOG2P, ITEMS>, dim3(grid), dim3(PT_THREADS),
                      0, s, key, n, shift, static_cast<const uint32_t *>(w.hist), ntiles, key_out, rowid_out,
@@ -384,8 +377,7 @@ gq_status gq_radix_partition(gq_ctx *ctx, const int64_t *key, int64_t n, int log
     hipStream_t s = static_cast<hipStream_t>(stream);
     gq_carver c(ws);
     part_ws w = part_layout(c, n, log2_fanout);
-    static const gq_part_names names{"gq_partition_hist", "gq_partition_scan", "gq_partition_offsets",
-                                     "gq_partition_scatter"};
+    static const gq_part_names names{"gq_partition_hist", "gq_partition_scan", "gq_partition_scatter"};
     return dispatch_partition(ctx, key, n, log2_fanout, 64 - log2_fanout, pc, key_out, rowid_out, offsets_dev, w, s,
                               names);
 }

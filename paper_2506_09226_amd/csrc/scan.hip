@@ -152,7 +152,8 @@ __global__ __launch_bounds__(TO_THREADS) void to_chunk_scan_kernel(uint32_t *__r
 // Exclusive scan of the P bucket totals (one workgroup; each thread owns
 // P / 1024 consecutive buckets).
 __global__ __launch_bounds__(TO_START_THREADS) void to_bucket_start_kernel(const uint32_t *__restrict__ total, int P,
-                                                                           uint32_t *__restrict__ start)
+                                                                           uint32_t *__restrict__ start,
+                                                                           int64_t *__restrict__ start64)
 {
     __shared__ uint32_t smem[TO_START_THREADS / 64];
     const int per = (P + TO_START_THREADS - 1) / TO_START_THREADS;
@@ -165,9 +166,13 @@ __global__ __launch_bounds__(TO_START_THREADS) void to_bucket_start_kernel(const
     for (int i = 0; i < per; ++i)
         if (b0 + i < P) {
             start[b0 + i] = run;
+            if (start64) start64[b0 + i] = static_cast<int64_t>(run);
             run += total[b0 + i];
         }
-    if (threadIdx.x == 0) start[P] = all;
+    if (threadIdx.x == 0) {
+        start[P] = all;
+        if (start64) start64[P] = static_cast<int64_t>(all);
+    }
 }
 
 __global__ __launch_bounds__(TO_THREADS) void to_final_kernel(uint32_t *__restrict__ cnt, int64_t ntiles, int P,
@@ -206,7 +211,7 @@ size_t gq_tile_offsets_workspace(int64_t ntiles, int P)
 }
 
 gq_status gq_tile_offsets(gq_ctx *ctx, uint32_t *cnt, int64_t ntiles, int P, uint32_t *start, void *ws,
-                          hipStream_t s, const char *name, const gq_tile_count *live)
+                          hipStream_t s, const char *name, const gq_tile_count *live, int64_t *start64)
 {
     const gq_tile_count lv = live ? *live : gq_tile_count{nullptr, 0, 1};
     if (live && live->tile_rows < 1) return gq_fail(ctx, GQ_ERR_INVALID_ARG, "gq_tile_offsets: bad tile rows");
@@ -222,7 +227,7 @@ gq_status gq_tile_offsets(gq_ctx *ctx, uint32_t *cnt, int64_t ntiles, int P, uin
                      static_cast<const uint32_t *>(cnt), ntiles, P, chunk, csum, lv));
     GQ_TRY(gq_launch(ctx, name, to_chunk_scan_kernel, grid1, dim3(TO_THREADS), 0, s, csum, nchunks, P, total));
     GQ_TRY(gq_launch(ctx, name, to_bucket_start_kernel, dim3(1), dim3(TO_START_THREADS), 0, s,
-                     static_cast<const uint32_t *>(total), P, start));
+                     static_cast<const uint32_t *>(total), P, start, start64));
     return gq_launch(ctx, name, to_final_kernel, grid2, dim3(TO_THREADS), 0, s, cnt, ntiles, P, chunk,
                      static_cast<const uint32_t *>(csum), static_cast<const uint32_t *>(start), lv);
 }
