@@ -59,13 +59,12 @@ def algorithmic_bytes(n: int, m: int, s_n: int, groups: int, k: int, partition: 
 
 # kernels of each operator (HIP-event names); an operator's time is their sum
 OP_KERNELS = {
-    "partition": ["gq_partition_hist", "gq_partition_scan", "gq_partition_offsets", "gq_partition_scatter"],
+    "partition": ["gq_partition_hist", "gq_partition_scan", "gq_partition_scatter"],
     "filter": ["gq_filter"],
     "join_build": ["gq_join_build_init", "gq_join_build_insert", "gq_join_build_part_hist",
-                   "gq_join_build_part_scan", "gq_join_build_part_offsets", "gq_join_build_part_scatter",
+                   "gq_join_build_part_scan", "gq_join_build_part_scatter",
                    "gq_join_build_split", "gq_join_build_regions", "gq_join_build_overflow"],
-    "join_probe": ["gq_join_probe", "gq_join_probe_split", "gq_join_probe_plan", "gq_join_probe_regions",
-                   "gq_join_probe_compact"],
+    "join_probe": ["gq_join_probe"],
     "groupby": ["gq_groupby_hist", "gq_groupby_scan", "gq_groupby_scatter", "gq_groupby_tiles2", "gq_groupby_hist2",
                 "gq_groupby_scan2", "gq_groupby_scatter2", "gq_groupby_side", "gq_groupby_chunks", "gq_groupby_bucket",
                 "gq_groupby_emit", "gq_groupby_local"],

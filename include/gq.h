@@ -232,20 +232,14 @@ gq_status gq_join_probe(gq_ctx *ctx, const void *table, const int64_t *fk,
                         int32_t *prow_out, int32_t *payload_out, int64_t *n_out_dev,
                         void *ws, size_t ws_bytes, gq_stream stream);
 
-/* Workspace for gq_join_probe_partitioned of at most n rows (about 18 bytes
- * per row plus about 530 bytes per 4096 rows). */
+/* Workspace for gq_join_probe_partitioned of at most n rows. */
 size_t gq_join_probe_partitioned_workspace_bytes(int64_t n);
 
-/* The same join as gq_join_probe, computed as a partitioned (radix) join:
- * the probes of each table region (4096 slots) are answered from an LDS copy
- * of that region.  Each tile of 4096 probe rows is split, stably, by the
- * region of its keys (fmix64 bits below the top log2_fanout, up to 256 ways);
- * one workgroup per region then loads the region into LDS and looks up that
- * region's rows of every tile; the results are put back in probe order tile
- * by tile.  Fast when the probe stream is in the order of a radix partition
- * by the top log2_fanout bits of the same hash (the output of
- * gq_radix_partition on fk), since then a tile's rows share those bits;
- * rows that do not are probed in device memory, so any order is correct.
+/* The same join as gq_join_probe for a probe stream that is in the order of a
+ * radix partition by the top log2_fanout bits of the same hash (the output of
+ * gq_radix_partition on fk): the slots of nearby rows then lie in one slice
+ * of the table.  Any order is correct.  In addition to gq_join_probe, the
+ * size of a table of 2^20 to 2^(min(log2_fanout, 8) + 20) slots is checked.
  * Paper: Sec. 2.2 (a local join of inputs partitioned on the key) and the
  * Related Work section (single-GPU query processing, which cites
  * partitioned radix joins).
@@ -255,9 +249,6 @@ size_t gq_join_probe_partitioned_workspace_bytes(int64_t n);
  *                the output undefined)
  *   log2_fanout  radix bits of the partition the probe stream is in (0..16;
  *                0 when it is in no such order)
- * Tables with fewer than 2^20 slots (cache resident), or too large for 256
- * regions per partition bucket (more than 2^(log2_fanout + 20) slots), are
- * probed by gq_join_probe instead.
  * Output: identical to gq_join_probe's (pairs in probe order, *n_out_dev
  * their number).
  * Other arguments, errors and capacities as gq_join_probe; additionally

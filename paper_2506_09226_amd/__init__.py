@@ -345,8 +345,8 @@ def gq_join_probe(ctx: Context, table, fk, sel=None, n: int | None = None, n_dev
 
 def gq_join_probe_partitioned(ctx: Context, table, fk, sel=None, n: int | None = None, n_dev=None,
                               log2_fanout: int = 0, prow=None, payload=None, n_out=None, ws=None):
-    """Partitioned (LDS region) probe; returns (prow_out, payload_out, n_out),
-    identical to gq_join_probe's output.  log2_fanout: radix bits of the hash
+    """The probe of a radix-partitioned stream, with the table's size checked;
+    returns (prow_out, payload_out, n_out), identical to gq_join_probe's output.  log2_fanout: radix bits of the hash
     partition the probe stream is in (0 if none)."""
     if n is None:
         n = sel.numel() if sel is not None else fk.numel()

@@ -4,14 +4,10 @@
     ->  probe(partitioned fk via the selection)  ->  group-by(dim attribute)
     ->  float64 averages  [->  top-k of price over the selection]
 
-The probe is the single-pass one (gq_join_probe) or the partitioned one
-(gq_join_probe_partitioned: table regions probed from LDS); both give the
-same output.  "auto" takes the partitioned probe when the fact table was
-radix-partitioned (then the probe stream is in region order), otherwise the
-single-pass one.  "tune" times both on the first step's data (HIP events, one
-host wait) and keeps the faster: a heavy key concentrates its table region's
-probes on one workgroup of the partitioned form, while the single-pass form
-reads a hot slot from cache.
+The probe is gq_join_probe, or gq_join_probe_partitioned, which also checks
+the table's size; both give the same output.  "auto" takes the partitioned
+form when the fact table was radix-partitioned, "tune" times both on the first
+step's data (HIP events, one host wait) and keeps the faster.
 
 All buffers and workspaces are allocated once, so a step allocates nothing and
 never waits for the host: every count travels on the device.
