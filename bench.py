@@ -61,7 +61,7 @@ def algorithmic_bytes(n: int, m: int, s_n: int, groups: int, k: int, partition: 
 OP_KERNELS = {
     "partition": ["gq_partition_hist", "gq_partition_scan", "gq_partition_scatter"],
     "filter": ["gq_filter"],
-    "join_build": ["gq_join_build_init", "gq_join_build_insert", "gq_join_build_part_hist",
+    "join_build": ["gq_join_build_lds", "gq_join_build_init", "gq_join_build_insert", "gq_join_build_part_hist",
                    "gq_join_build_part_scan", "gq_join_build_part_scatter",
                    "gq_join_build_split", "gq_join_build_regions", "gq_join_build_overflow"],
     "join_probe": ["gq_join_probe"],

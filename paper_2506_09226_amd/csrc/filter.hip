@@ -154,8 +154,8 @@ __global__ __launch_bounds__(FT_THREADS) void filter_kernel(const T *__restrict_
 }
 
 // Small inputs, bound by latency: one launch with no scratch to clear and no
-// waiting (64K rows: 16.4 -> 11.7 us a call, 30K rows 12 -> 8.3 us, of which
-// the host's share is about 8).  Workgroup t counts the matches of all rows before its own 1024
+// waiting (64K rows: 16.5 -> 8.6 us a call, of which the host's share is about
+// 8; with 4-byte loads 11.7).  Workgroup t counts the matches of all rows before its own 1024
 // itself, which for up to FT_TINY_ROWS rows is a few loads per thread.
 constexpr int64_t FT_TINY_ROWS = 1 << 16;
 constexpr int64_t FT_TINY_SEL_ROWS = 1 << 15;       // (two dependent loads per row with a selection)
@@ -164,7 +164,8 @@ template <typename T, bool HAS_SEL>
 __global__ __launch_bounds__(FT_THREADS) void filter_tiny_kernel(const T *__restrict__ col,
                                                                  const int32_t *__restrict__ sel_in,
                                                                  int64_t n_bound, const int64_t *n_dev, int64_t lo,
-                                                                 int64_t hi, int32_t *__restrict__ out, int64_t *n_out)
+                                                                 int64_t hi, int vec, int32_t *__restrict__ out,
+                                                                 int64_t *n_out)
 {
     __shared__ uint32_t wprev[FT_WAVES], wcnt[FT_WAVES];
     const int64_t n = ft_rows(n_bound, n_dev);
@@ -179,12 +180,35 @@ __global__ __launch_bounds__(FT_THREADS) void filter_tiny_kernel(const T *__rest
     const int32_t e = static_cast<int32_t>(base) + static_cast<int32_t>(threadIdx.x);
     const int32_t r = e < n ? (HAS_SEL ? sel_in[e] : e) : 0;
     uint32_t prev = 0;
-    constexpr int AHEAD = 32;
-    for (int32_t j0 = threadIdx.x; j0 < base; j0 += FT_THREADS * AHEAD) {
+    if (!HAS_SEL && vec) {                              // 16-byte loads (the column's start is 16-byte aligned)
+        constexpr int PER = 16 / sizeof(T);
+        constexpr int AHEAD = 8;
+        typedef T vec_t __attribute__((ext_vector_type(PER)));
+        const vec_t *cv = reinterpret_cast<const vec_t *>(col);
+        const int32_t nv = static_cast<int32_t>(base) / PER;   // base is a multiple of 1024
+        for (int32_t j0 = threadIdx.x; j0 < nv; j0 += FT_THREADS * AHEAD) {
+            vec_t v[AHEAD];
 #pragma unroll
-        for (int c = 0; c < AHEAD; ++c) {
-            const int32_t j = j0 + c * FT_THREADS;
-            if (j < base) prev += test(HAS_SEL ? sel_in[j] : j) ? 1u : 0u;
+            for (int c = 0; c < AHEAD; ++c) {
+                const int32_t j = j0 + c * FT_THREADS;
+                v[c] = cv[j < nv ? j : j0];
+            }
+#pragma unroll
+            for (int c = 0; c < AHEAD; ++c) {
+                uint32_t m = 0;
+#pragma unroll
+                for (int i = 0; i < PER; ++i) m += range.test(v[c][i]) ? 1u : 0u;
+                prev += j0 + c * FT_THREADS < nv ? m : 0u;
+            }
+        }
+    } else {
+        constexpr int AHEAD = 16;
+        for (int32_t j0 = threadIdx.x; j0 < base; j0 += FT_THREADS * AHEAD) {
+#pragma unroll
+            for (int c = 0; c < AHEAD; ++c) {
+                const int32_t j = j0 + c * FT_THREADS;
+                if (j < base) prev += test(HAS_SEL ? sel_in[j] : j) ? 1u : 0u;
+            }
         }
     }
     const uint64_t b = gq_ballot(e < n && test(r));
@@ -212,7 +236,7 @@ gq_status launch_filter(gq_ctx *ctx, const void *col, const int32_t *sel_in, int
     if (n <= (S ? FT_TINY_SEL_ROWS : FT_TINY_ROWS)) {
         const uint32_t grid = static_cast<uint32_t>(n > 0 ? (n + FT_THREADS - 1) / FT_THREADS : 1);
         return gq_launch(ctx, "gq_filter", filter_tiny_kernel<T, S>, dim3(grid), dim3(FT_THREADS), 0, s, c, sel_in, n,
-                         n_dev, lo, hi, out, n_out);
+                         n_dev, lo, hi, reinterpret_cast<uintptr_t>(col) % 16 == 0 ? 1 : 0, out, n_out);
     }
     gq_carver cv(scratch);
     const filter_ws w = filter_layout(cv, n);

@@ -6,8 +6,10 @@
 // partition, so a probe stream that was partitioned by that hash touches one
 // contiguous slice of the table at a time.  Linear probing, wrapping.
 //
-// Build, small tables: a fill kernel writes header and EMPTY slots; an insert
-// kernel claims slots with a 64-bit compare-and-swap in device memory and then
+// Build, tables of up to 8192 slots: one workgroup builds the table in LDS.
+//
+// Build, other small tables: a fill kernel writes header and EMPTY slots; an
+// insert kernel claims slots with a 64-bit compare-and-swap in device memory and then
 // stores the payload (the probe runs in a later kernel, so it sees the store).
 //
 // Build, large tables (device-memory CAS runs at only ~10 G/s on MI355X): the
@@ -119,6 +121,94 @@ __global__ __launch_bounds__(256) void jt_insert_kernel(void *table, int log2_sl
             s = (s + 1) & mask;
         }
         if (probes > mask) gq_raise(status, GQ_ERR_CAPACITY);
+    }
+}
+
+// Tables of at most JB_LDS_SLOTS slots, bound by latency: one workgroup builds
+// the table in LDS and writes it out, in one launch with no device
+// compare-and-swaps (4096 keys with a probe of 64K rows: 27.5 -> 24.7 us; 1000
+// keys with 10K rows: 32.6 -> 20, of which the host's share is most).
+constexpr int JB_LDS_SLOTS = 8192;                  // 96 KB of keys and payloads
+constexpr int JB_THREADS = 1024;
+constexpr int JB_BATCH = 4;                         // keys per thread loaded together
+
+__global__ __launch_bounds__(JB_THREADS) void jt_lds_build_kernel(void *table, int log2_slots,
+                                                                  const int64_t *__restrict__ key,
+                                                                  const int32_t *__restrict__ payload, int64_t m_bound,
+                                                                  const int64_t *n_dev, const int32_t *__restrict__ sel,
+                                                                  uint32_t *status)
+{
+    extern __shared__ unsigned long long jb_keys[];
+    const int slots = 1 << log2_slots;
+    int32_t *jb_pay = reinterpret_cast<int32_t *>(jb_keys + slots);
+    int64_t m = m_bound;
+    if (n_dev) {
+        const int64_t d = *n_dev;
+        m = d < m_bound ? (d > 0 ? d : 0) : m_bound;
+    }
+    int64_t k[JB_BATCH];
+    int32_t p[JB_BATCH];
+    auto load = [&](int64_t i0) {
+#pragma unroll
+        for (int c = 0; c < JB_BATCH; ++c) {
+            const int64_t i = i0 + c * JB_THREADS + threadIdx.x;
+            k[c] = 0;
+            p[c] = 0;
+            if (i < m) {
+                const int64_t r = sel ? static_cast<int64_t>(sel[i]) : i;
+                k[c] = key[r];
+                p[c] = payload[r];
+            }
+        }
+    };
+    load(0);
+    for (int j = threadIdx.x; j < slots; j += JB_THREADS) {
+        jb_keys[j] = static_cast<unsigned long long>(JT_EMPTY);
+        jb_pay[j] = 0;
+    }
+    __syncthreads();
+    for (int64_t i0 = 0; i0 < m; i0 += JB_THREADS * JB_BATCH) {
+        if (i0 > 0) load(i0);
+#pragma unroll
+        for (int c = 0; c < JB_BATCH; ++c) {
+            if (i0 + c * JB_THREADS + threadIdx.x >= m) continue;
+            if (k[c] == JT_EMPTY) {
+                gq_raise(status, GQ_ERR_INVALID_KEY);
+                continue;
+            }
+            uint32_t s = static_cast<uint32_t>(gq_fmix64(static_cast<uint64_t>(k[c])) >> (64 - log2_slots));
+            int probes = 0;
+            for (; probes < slots; ++probes) {
+                const unsigned long long prev = atomicCAS(&jb_keys[s], static_cast<unsigned long long>(JT_EMPTY),
+                                                          static_cast<unsigned long long>(k[c]));
+                if (prev == static_cast<unsigned long long>(JT_EMPTY)) {
+                    jb_pay[s] = p[c];
+                    break;
+                }
+                if (prev == static_cast<unsigned long long>(k[c])) {
+                    gq_raise(status, GQ_ERR_DUPLICATE_KEY);
+                    break;
+                }
+                s = (s + 1) & static_cast<uint32_t>(slots - 1);
+            }
+            if (probes == slots) gq_raise(status, GQ_ERR_CAPACITY);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        jt_header *h = static_cast<jt_header *>(table);
+        h->magic = JT_MAGIC;
+        h->log2_slots = static_cast<uint32_t>(log2_slots);
+        h->unused = 0;
+        h->slots = static_cast<uint64_t>(slots);
+    }
+    jt_slot *out = reinterpret_cast<jt_slot *>(static_cast<char *>(table) + JT_HEADER);
+    for (int j = threadIdx.x; j < slots; j += JB_THREADS) {
+        jt_slot e;
+        e.key = static_cast<int64_t>(jb_keys[j]);
+        e.payload = jb_pay[j];
+        e.unused = 0;
+        out[j] = e;
     }
 }
 
@@ -478,11 +568,12 @@ gq_status region_build(gq_ctx *ctx, const int64_t *key, const int32_t *payload, 
 // 6, 89 at 12): about 512 to 1024 units, and 8 steps until enough units are
 // left for a balanced tail (9M probes: 210 us at 8, 226 at 16).
 // Up to JP_TINY_ROWS rows the chip is not full either way and a call is bound
-// by one unit's chain of loads: 256-row units (64K rows: 31 -> 13 us).
+// by one unit's chain of loads and the look-back: 512-row units (64K rows:
+// 31 -> 12 us; 100K rows 18 us at 256 rows, 13 at 512 and at 1024).
 constexpr int64_t JP_TINY_ROWS = 1 << 17;
 constexpr int64_t JP_LARGE_ROWS = 1 << 25;
 constexpr int JP_THREADS = 1024;
-constexpr int JP_TINY_THREADS = 256;
+constexpr int JP_TINY_THREADS = 512;
 constexpr int JP_MAX_STEPS = 16;
 struct jp_shape {
     int threads, steps;
@@ -708,6 +799,10 @@ gq_status gq_join_build(gq_ctx *ctx, const int64_t *key, const int32_t *payload,
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (region) return region_build(ctx, key, payload, m, table, L, ws, s);
     const uint64_t slots = 1ull << L;
+    if (slots <= JB_LDS_SLOTS)
+        return gq_launch(ctx, "gq_join_build_lds", jt_lds_build_kernel, dim3(1), dim3(JB_THREADS),
+                         static_cast<size_t>(slots) * (sizeof(int64_t) + sizeof(int32_t)), s, table, L, key, payload, m,
+                         n_dev, sel, ctx->status_dev);
     uint64_t blocks = (slots + 255) / 256;
     if (blocks > 8192) blocks = 8192;
     GQ_TRY(gq_launch(ctx, "gq_join_build_init", jt_init_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s, table,

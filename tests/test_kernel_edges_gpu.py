@@ -24,7 +24,7 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
-# 256-row units up to 2^17 rows; 1024-row units above, of 1..16 steps per wave
+# 512-row units up to 2^17 rows; 1024-row units above, of 1..16 steps per wave
 @pytest.mark.parametrize("n", [255, 257, 131_072, 131_073, 1_048_575, 2 * 1024 * 512 + 1, 17 * 1024 * 512 + 777])
 @pytest.mark.parametrize("lf", [0.5, 0.9])
 def test_ordered_probe_units(ctx, n, lf):
@@ -213,3 +213,50 @@ def test_large_groupby_buckets(ctx, n, groups, kind):
         o = np.lexsort((g["key32"], g["key64"]))
         for f in ("key64", "key32", "count", "sum_qty", "sum_rev_lo", "sum_rev_hi"):
             assert np.array_equal(g[f][o], exp[f]), f
+
+
+# tables built in LDS (up to 8192 slots) and just above, with a selection and a
+# device count, keys that wrap past the last slot, and the error cases
+@pytest.mark.parametrize("m,lf", [(1, 0.5), (57, 0.9), (4096, 0.5), (7372, 0.9), (7373, 0.9), (9000, 0.5)])
+def test_lds_build(ctx, m, lf):
+    r = np.random.default_rng(m)
+    key = r.permutation(np.arange(2 * m) - m).astype(np.int64)
+    pay = r.integers(-(1 << 31), 1 << 31, size=2 * m).astype(np.int32)
+    sel = np.sort(r.choice(2 * m, size=m, replace=False)).astype(np.int32)
+    cnt = max(1, m - 3)
+    fk = r.integers(-2 * m, 2 * m, size=20_011)
+    fk[5] = np.iinfo(np.int64).min
+    k, p, f, s = dev(key), dev(pay), dev(fk), dev(sel)
+    n_dev = torch.tensor([cnt], dtype=torch.int64, device="cuda")
+    whole = (k[:m].contiguous(), p[:m].contiguous())
+    for table, bk, bp in (
+            (gq.gq_join_build(ctx, *whole, load_factor=lf), key[:m], pay[:m]),
+            (gq.gq_join_build(ctx, k, p, sel=s, load_factor=lf), key[sel], pay[sel]),
+            (gq.gq_join_build(ctx, k, p, sel=s, n_dev=n_dev, load_factor=lf), key[sel[:cnt]], pay[sel[:cnt]])):
+        assert ctx.status() == gq.GQ_OK
+        ep, ey = oracle.join(bk, bp, fk, None)
+        prow, out, c = gq.gq_join_probe(ctx, table, f)
+        c = int(c.item())
+        assert c == len(ep)
+        assert np.array_equal(prow[:c].cpu().numpy(), ep) and np.array_equal(out[:c].cpu().numpy(), ey)
+    if m > 1:
+        bad = key[:m].copy()
+        bad[-1] = bad[0]
+        gq.gq_join_build(ctx, dev(bad), whole[1], load_factor=lf)
+        assert ctx.status() == gq.GQ_ERR_DUPLICATE_KEY
+        bad[-1] = np.iinfo(np.int64).min
+        gq.gq_join_build(ctx, dev(bad), whole[1], load_factor=lf)
+        assert ctx.status() == gq.GQ_ERR_INVALID_KEY
+
+
+def test_filter_of_a_misaligned_column(ctx):
+    """A column that does not start on 16 bytes takes the scalar loads."""
+    r = np.random.default_rng(5)
+    for dtype in (np.int32, np.int64):
+        col = r.integers(0, 100, size=50_001).astype(dtype)
+        d = dev(col)
+        for o in range(1, 4):
+            out, cnt = gq.gq_filter(ctx, d[o:], 20, 70)
+            exp = np.flatnonzero((col[o:] >= 20) & (col[o:] < 70)).astype(np.int32)
+            k = int(cnt.item())
+            assert k == len(exp) and np.array_equal(out[:k].cpu().numpy(), exp)
