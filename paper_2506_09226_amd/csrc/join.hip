@@ -532,11 +532,11 @@ gq_status region_build(gq_ctx *ctx, const int64_t *key, const int32_t *payload, 
     void *in[1] = {const_cast<int32_t *>(payload)};
     if (g <= JS_HIGH) {                             // one pass: its bucket starts are the region starts
         void *out[1] = {w.p2};
-        GQ_TRY(gq_partition_bits(ctx, key, m, g, 64 - g, 1, in, &pbytes, w.k2, out, w.roff, w.part_ws, s, nm, 8));
+        GQ_TRY(gq_partition_bits(ctx, key, m, g, 64 - g, 1, in, &pbytes, w.k2, out, w.roff, w.part_ws, s, nm, 16));
     } else {                                        // the top JS_HIGH bits, then each bucket by the rest
         void *out[1] = {w.p1};
         GQ_TRY(gq_partition_bits(ctx, key, m, JS_HIGH, 64 - JS_HIGH, 1, in, &pbytes, w.k1, out, w.offsets, w.part_ws,
-                                 s, nm, 8));
+                                 s, nm, 16));
         GQ_TRY(gq_launch(ctx, "gq_join_build_split", jt_split_kernel, dim3(1u << JS_HIGH), dim3(JS_THREADS), 0, s,
                          static_cast<const int64_t *>(w.k1), static_cast<const int32_t *>(w.p1),
                          static_cast<const int64_t *>(w.offsets), m, g, w.k2, w.p2, w.roff));

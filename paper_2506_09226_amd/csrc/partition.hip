@@ -21,7 +21,8 @@
 
 namespace {
 
-constexpr int PT_THREADS = 256;
+constexpr int PT_HIST_THREADS = 256;
+constexpr int PT_THREADS = 1024;                    // of the scatter
 constexpr int PT_WAVES = PT_THREADS / 64;
 constexpr int PT_MAX_LOG2P = 8;
 constexpr int PT_MAX_COLS = 8;
@@ -62,32 +63,42 @@ GQ_DEV uint32_t bucket_of(int64_t key, int shift)
 }
 
 // LDS histogram of one tile, written as the tile's row hist[t * P + b].
-template <int LOG2P, int ITEMS>
-__global__ __launch_bounds__(PT_THREADS) void part_hist_kernel(const int64_t *__restrict__ key, int64_t n,
+template <int LOG2P, int TILE>
+__global__ __launch_bounds__(PT_HIST_THREADS) void part_hist_kernel(const int64_t *__restrict__ key, int64_t n,
                                                                int shift, uint32_t *__restrict__ hist)
 {
     constexpr int P = 1 << LOG2P;
-    constexpr int TILE = PT_THREADS * ITEMS;
+    constexpr int ITEMS = TILE / PT_HIST_THREADS;
     __shared__ uint32_t h[P];
-    for (int i = threadIdx.x; i < P; i += PT_THREADS) h[i] = 0;
+    for (int i = threadIdx.x; i < P; i += PT_HIST_THREADS) h[i] = 0;
     __syncthreads();
     const int64_t base = static_cast<int64_t>(blockIdx.x) * TILE;
     int64_t k[ITEMS];
 #pragma unroll
     for (int c = 0; c < ITEMS; ++c) {
-        const int64_t e = base + c * PT_THREADS + threadIdx.x;
+        const int64_t e = base + c * PT_HIST_THREADS + threadIdx.x;
         k[c] = (e < n) ? key[e] : 0;
     }
 #pragma unroll
     for (int c = 0; c < ITEMS; ++c) {
-        const int64_t e = base + c * PT_THREADS + threadIdx.x;
+        const int64_t e = base + c * PT_HIST_THREADS + threadIdx.x;
         if (e < n) atomicAdd(&h[bucket_of<LOG2P>(k[c], shift)], 1u);
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < P; b += PT_THREADS) hist[static_cast<int64_t>(blockIdx.x) * P + b] = h[b];
+    for (int b = threadIdx.x; b < P; b += PT_HIST_THREADS) hist[static_cast<int64_t>(blockIdx.x) * P + b] = h[b];
 }
 
-template <int LOG2P, int ITEMS>
+// The scatter moves its columns one after another through one LDS stage, with
+// two barriers a column, so it is waves in flight that hide the memory: 1024
+// threads of TILE / 1024 rows hold a few registers per column (two workgroups,
+// 32 waves a CU), where 256 threads of 16 rows left 12 waves.  Each thread
+// keeps the output index of the rows that it writes, the same for all columns.
+// 20M rows, 256 buckets, 28 B in and 32 B out a row: 327 -> 290 us (4.1 TB/s);
+// 200M rows, 64 buckets, 36 and 40 B: 3.32 -> 3.11 ms (4.9 TB/s, where a copy
+// reaches 4.8); 1M rows, 64 buckets: 33 -> 20 us.  512 threads of 8 rows: 323 us
+// at 256 buckets; 1024 of 8 (tiles of 8192): 357; two stages and one barrier a
+// column, or 16-bit counters: the same.
+template <int LOG2P, int TILE>
 __global__ __launch_bounds__(PT_THREADS) void part_scatter_kernel(const int64_t *__restrict__ key, int64_t n,
                                                                   int shift, const uint32_t *__restrict__ gofs,
                                                                   int64_t ntiles,
@@ -95,7 +106,7 @@ __global__ __launch_bounds__(PT_THREADS) void part_scatter_kernel(const int64_t 
                                                                   int32_t *__restrict__ rowid_out, part_cols cols)
 {
     constexpr int P = 1 << LOG2P;
-    constexpr int TILE = PT_THREADS * ITEMS;
+    constexpr int ITEMS = TILE / PT_THREADS;
     constexpr int WROWS = TILE / PT_WAVES;            // rows per wave
     __shared__ uint32_t wcnt[PT_WAVES][P];            // per-wave running counts, then per-wave prefixes
     __shared__ uint32_t lstart[P];
@@ -194,12 +205,23 @@ __global__ __launch_bounds__(PT_THREADS) void part_scatter_kernel(const int64_t 
         }
     };
     uint64_t cur[ITEMS], nxt[ITEMS];
+    uint32_t dest[ITEMS];                             // of tile-local position c * PT_THREADS + threadIdx.x
     load_col(0, cur);
+    gq_lds_barrier();                                 // lbucket is complete
+#pragma unroll
+    for (int c = 0; c < ITEMS; ++c) {
+        const uint32_t q = c * PT_THREADS + threadIdx.x;
+        dest[c] = 0;
+        if (q < count) {
+            const uint32_t b = lbucket[q];
+            dest[c] = gstart[b] + (q - lstart[b]);
+        }
+    }
     for (int ci = 0; ci < ncol_total; ++ci) {
         const bool is_key = ci == 0;
         const bool is_rowid = ci == 1 + cols.n;
         const int width = is_key ? 8 : (is_rowid ? 4 : cols.bytes[ci - 1]);
-        gq_lds_barrier();                             // stage free (and lbucket ready)
+        if (ci > 0) gq_lds_barrier();                 // stage free
         if (width == 8) {
 #pragma unroll
             for (int c = 0; c < ITEMS; ++c)
@@ -214,16 +236,18 @@ __global__ __launch_bounds__(PT_THREADS) void part_scatter_kernel(const int64_t 
         gq_lds_barrier();
         if (width == 8) {
             uint64_t *dst = is_key ? reinterpret_cast<uint64_t *>(key_out) : static_cast<uint64_t *>(cols.out[ci - 1]);
-            for (uint32_t q = threadIdx.x; q < count; q += PT_THREADS) {
-                const uint32_t b = lbucket[q];
-                dst[gstart[b] + (q - lstart[b])] = stage[q];
+#pragma unroll
+            for (int c = 0; c < ITEMS; ++c) {
+                const uint32_t q = c * PT_THREADS + threadIdx.x;
+                if (q < count) dst[dest[c]] = stage[q];
             }
         } else {
             const uint32_t *st32 = reinterpret_cast<const uint32_t *>(stage);
             uint32_t *dst = is_rowid ? reinterpret_cast<uint32_t *>(rowid_out) : static_cast<uint32_t *>(cols.out[ci - 1]);
-            for (uint32_t q = threadIdx.x; q < count; q += PT_THREADS) {
-                const uint32_t b = lbucket[q];
-                dst[gstart[b] + (q - lstart[b])] = st32[q];
+#pragma unroll
+            for (int c = 0; c < ITEMS; ++c) {
+                const uint32_t q = c * PT_THREADS + threadIdx.x;
+                if (q < count) dst[dest[c]] = st32[q];
             }
         }
 #pragma unroll
@@ -231,19 +255,24 @@ __global__ __launch_bounds__(PT_THREADS) void part_scatter_kernel(const int64_t 
     }
 }
 
-// Rows per thread in the scatter (tile = 256 * items).  16 by default; the
-// GQ_PARTITION_ITEMS environment variable (8, 16 or 32) overrides it.
-int part_items()
+// Rows of a tile, in units of 256.  Tiles of 4096 rows write the longest runs
+// that leave two workgroups to a CU; below 512 of them (one workgroup a CU or
+// less at a time) tiles of 2048 put twice as many CUs to work (1M rows: 20.4
+// against 19.0 us; 20M rows: 290 against 311).  The GQ_PARTITION_ITEMS
+// environment variable (8, 16 or 32) overrides the rule.
+constexpr int64_t PT_SMALL_ROWS = int64_t(512) * 4096;
+
+int part_items(int64_t n)
 {
     static int v = [] {
         const char *e = getenv("GQ_PARTITION_ITEMS");
-        const int x = e ? atoi(e) : 16;
-        return (x == 8 || x == 16 || x == 32) ? x : 16;
+        const int x = e ? atoi(e) : 0;
+        return (x == 8 || x == 16 || x == 32) ? x : 0;
     }();
-    return v;
+    return v ? v : (n < PT_SMALL_ROWS ? 8 : 16);
 }
 
-constexpr int PT_MIN_TILE = PT_THREADS * 8;
+constexpr int PT_MIN_TILE = 256 * 8;
 
 struct part_ws {
     uint32_t *hist;
@@ -263,20 +292,19 @@ part_ws part_layout(gq_carver &c, int64_t n, int log2p)
     return w;
 }
 
-template <int LOG2P, int ITEMS>
-gq_status run_partition_items(gq_ctx *ctx, const int64_t *key, int64_t n, int shift, const part_cols &cols,
+template <int LOG2P, int TILE>
+gq_status run_partition_tile(gq_ctx *ctx, const int64_t *key, int64_t n, int shift, const part_cols &cols,
                               int64_t *key_out, int32_t *rowid_out, int64_t *offsets, part_ws w, hipStream_t s,
                               const gq_part_names &nm)
 {
     constexpr int P = 1 << LOG2P;
-    constexpr int TILE = PT_THREADS * ITEMS;
     const int64_t ntiles = n > 0 ? (n + TILE - 1) / TILE : 1;
     const uint32_t grid = static_cast<uint32_t>(ntiles);
-    GQ_TRY(gq_launch(ctx, nm.hist, part_hist_kernel<LOG2P, ITEMS>, dim3(grid), dim3(PT_THREADS), 0, s, key, n,
+    GQ_TRY(gq_launch(ctx, nm.hist, part_hist_kernel<LOG2P, TILE>, dim3(grid), dim3(PT_HIST_THREADS), 0, s, key, n,
                      shift, w.hist));
     GQ_TRY(gq_tile_offsets(ctx, w.hist, ntiles, P, w.start, w.scan_ws, s, nm.scan, nullptr, offsets));
     if (n == 0) return GQ_OK;
-    return gq_launch(ctx, nm.scatter, part_scatter_kernel<LOG2P, ITEMS>, dim3(grid), dim3(PT_THREADS),
+    return gq_launch(ctx, nm.scatter, part_scatter_kernel<LOG2P, TILE>, dim3(grid), dim3(PT_THREADS),
                      0, s, key, n, shift, static_cast<const uint32_t *>(w.hist), ntiles, key_out, rowid_out,
                      cols);
 }
@@ -286,10 +314,10 @@ gq_status run_partition(gq_ctx *ctx, const int64_t *key, int64_t n, int shift, c
                         int64_t *key_out, int32_t *rowid_out, int64_t *offsets, part_ws w, hipStream_t s,
                         const gq_part_names &nm, int items)
 {
-    switch (items > 0 ? items : part_items()) {
-    case 8: return run_partition_items<LOG2P, 8>(ctx, key, n, shift, cols, key_out, rowid_out, offsets, w, s, nm);
-    case 32: return run_partition_items<LOG2P, 32>(ctx, key, n, shift, cols, key_out, rowid_out, offsets, w, s, nm);
-    default: return run_partition_items<LOG2P, 16>(ctx, key, n, shift, cols, key_out, rowid_out, offsets, w, s, nm);
+    switch (items > 0 ? items : part_items(n)) {
+    case 8: return run_partition_tile<LOG2P, 2048>(ctx, key, n, shift, cols, key_out, rowid_out, offsets, w, s, nm);
+    case 32: return run_partition_tile<LOG2P, 8192>(ctx, key, n, shift, cols, key_out, rowid_out, offsets, w, s, nm);
+    default: return run_partition_tile<LOG2P, 4096>(ctx, key, n, shift, cols, key_out, rowid_out, offsets, w, s, nm);
     }
 }
 

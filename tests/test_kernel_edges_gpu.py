@@ -260,3 +260,21 @@ def test_filter_of_a_misaligned_column(ctx):
             exp = np.flatnonzero((col[o:] >= 20) & (col[o:] < 70)).astype(np.int32)
             k = int(cnt.item())
             assert k == len(exp) and np.array_equal(out[:k].cpu().numpy(), exp)
+
+
+# partition tiles of 2048 rows below 2^21 rows, of 4096 from there on; a wave's
+# and a workgroup's remainder in the last tile
+@pytest.mark.parametrize("n", [63, 2047, 2049, 33 * 2048 + 1025, (1 << 21) - 1, 1 << 21])
+@pytest.mark.parametrize("log2p", [2, 8])
+def test_partition_tiles(ctx, n, log2p):
+    r = np.random.default_rng(n + log2p)
+    key = r.integers(-(1 << 62), 1 << 62, size=n)
+    key[r.random(n) < 0.3] = 7                                 # one heavy bucket
+    cols = [r.integers(0, 1 << 31, size=n).astype(np.int32), r.integers(-(1 << 62), 1 << 62, size=n)]
+    ek, ec, erow, eoff = oracle.partition(key, log2p, cols)
+    for rowid in (True, False):
+        k, c, row, off = gq.gq_radix_partition(ctx, dev(key), log2p, [dev(x) for x in cols], rowid=rowid)
+        assert ctx.status() == gq.GQ_OK
+        assert np.array_equal(off.cpu().numpy(), eoff) and np.array_equal(k.cpu().numpy(), ek)
+        assert all(np.array_equal(x.cpu().numpy(), e) for x, e in zip(c, ec))
+        assert (row is None) if not rowid else np.array_equal(row.cpu().numpy(), erow)
