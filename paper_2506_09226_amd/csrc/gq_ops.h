@@ -3,11 +3,6 @@
 
 #include "gq_internal.h"
 
-// In-place exclusive scan of n uint32 values (n >= 0); ws must hold
-// gq_scan_u32_workspace(n) bytes and is zeroed by the call.
-size_t gq_scan_u32_workspace(int64_t n);
-gq_status gq_scan_u32(gq_ctx *ctx, uint32_t *data, int64_t n, void *ws, hipStream_t s, const char *name);
-
 // Stable partition of n rows by the log2p (0..8) bits of fmix64(key) that
 // start at bit `shift` (no row ids), with tiles of 256 * items rows (items 8,
 // 16 or 32; 0 = the operator's default).  ws: gq_partition_bits_workspace(n, log2p).
@@ -22,7 +17,8 @@ gq_status gq_partition_bits(gq_ctx *ctx, const int64_t *key, int64_t n, int log2
 
 // In place: per-tile bucket counts cnt[t*P + b] (tile-major) become the output
 // offsets of each (tile, bucket) run; start[0..P] receives the bucket starts
-// (start[P] = total), and start64, if given, the same as int64.  P <= 8192.  ws: gq_tile_offsets_workspace(ntiles, P).
+// (start[P] = total), and start64, if given, the same as int64.  P <= 1024.
+// ws: gq_tile_offsets_workspace(ntiles, P).
 size_t gq_tile_offsets_workspace(int64_t ntiles, int P);
 // Optional: only the first ceil(min(*n_dev, n_bound) / tile_rows) of the
 // ntiles tiles hold counts (the rows arrive as a device count); the rest are

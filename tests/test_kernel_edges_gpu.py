@@ -278,3 +278,39 @@ def test_partition_tiles(ctx, n, log2p):
         assert np.array_equal(off.cpu().numpy(), eoff) and np.array_equal(k.cpu().numpy(), ek)
         assert all(np.array_equal(x.cpu().numpy(), e) for x, e in zip(c, ec))
         assert (row is None) if not rowid else np.array_equal(row.cpu().numpy(), erow)
+
+
+# run offsets: one chunk of tiles and several, shares that are loaded once and
+# in batches (tiles of 2048 rows; 32 tiles a chunk, so 32 and 33, and 64 a chunk)
+@pytest.mark.parametrize("n", [32 * 2048, 32 * 2048 + 1, 100 * 2048 + 5])
+@pytest.mark.parametrize("log2p", [0, 5, 7])
+def test_partition_offsets(ctx, n, log2p):
+    r = np.random.default_rng(n)
+    key = r.integers(0, 1 << 20, size=n)
+    ek, _, erow, eoff = oracle.partition(key, log2p)
+    k, _, row, off = gq.gq_radix_partition(ctx, dev(key), log2p)
+    assert ctx.status() == gq.GQ_OK
+    assert np.array_equal(off.cpu().numpy(), eoff) and np.array_equal(row.cpu().numpy(), erow)
+    assert np.array_equal(k.cpu().numpy(), ek)
+
+
+# more tiles than 192 chunks of 32 (shares longer than one load): the invariants of a partition
+def test_partition_offsets_many_tiles(ctx):
+    n = 6200 * 4096 + 3
+    key = torch.randint(0, 1 << 40, (n,), dtype=torch.int64, device="cuda", generator=torch.Generator("cuda").manual_seed(3))
+    for log2p in (1, 8):
+        k, _, row, off = gq.gq_radix_partition(ctx, key, log2p)
+        assert ctx.status() == gq.GQ_OK
+        assert torch.equal(k, key[row.long()])
+        off = off.cpu().numpy()
+        assert off[0] == 0 and off[-1] == n
+        b = np.repeat(np.arange(1 << log2p), np.diff(off))
+        h = k.cpu().numpy().view(np.uint64)                    # fmix64 of the keys
+        for mul in (0xff51afd7ed558ccd, 0xc4ceb9fe1a85ec53):
+            h = (h ^ (h >> np.uint64(33))) * np.uint64(mul)
+        h = (h ^ (h >> np.uint64(33))) >> np.uint64(64 - log2p)
+        assert np.array_equal(h.astype(np.int64), b)
+        d = torch.diff(row.long())
+        edges = torch.zeros(n - 1, dtype=torch.bool, device="cuda")
+        edges[torch.from_numpy(off[1:-1] - 1).cuda()] = True
+        assert bool(((d > 0) | edges).all())                   # stable inside each bucket
