@@ -83,6 +83,13 @@ __global__ void jt_init_kernel(void *table, int log2_slots)
     }
 }
 
+// Keys beyond the region build's reach (too few, a selection or a device
+// count), one per thread.  A small build is bound by the longest walk of any
+// key, a chain of compare-and-swaps through the fabric (25 slots and more in
+// a table half full): 64K keys 23.2 -> 16.7 us with JT_AHEAD slots looked at
+// in one trip (8: the same).
+constexpr int JT_AHEAD = 4;
+
 __global__ __launch_bounds__(256) void jt_insert_kernel(void *table, int log2_slots, const int64_t *__restrict__ key,
                                                         const int32_t *__restrict__ payload, int64_t m_bound,
                                                         const int64_t *n_dev, const int32_t *__restrict__ sel,
@@ -105,22 +112,36 @@ __global__ __launch_bounds__(256) void jt_insert_kernel(void *table, int log2_sl
             continue;
         }
         uint64_t s = gq_fmix64(static_cast<uint64_t>(k)) >> (64 - log2_slots);
+        // the home slot is tried at once; a walk on from there reads
+        // JT_AHEAD slots together and tries those found empty
+        const unsigned long long want = static_cast<unsigned long long>(k);
+        const unsigned long long none = static_cast<unsigned long long>(JT_EMPTY);
+        unsigned long long prev = atomicCAS(reinterpret_cast<unsigned long long *>(&slots[s].key), none, want);
+        bool done = prev == none || prev == want;
         uint64_t probes = 0;
-        for (; probes <= mask; ++probes) {
-            unsigned long long *kp = reinterpret_cast<unsigned long long *>(&slots[s].key);
-            const unsigned long long prev =
-                atomicCAS(kp, static_cast<unsigned long long>(JT_EMPTY), static_cast<unsigned long long>(k));
-            if (prev == static_cast<unsigned long long>(JT_EMPTY)) {
-                slots[s].payload = p;
-                break;
+        while (!done && probes < mask) {
+            unsigned long long w[JT_AHEAD];
+#pragma unroll
+            for (int i = 0; i < JT_AHEAD; ++i)
+                w[i] = __hip_atomic_load(reinterpret_cast<unsigned long long *>(&slots[(s + 1 + i) & mask].key),
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            int at = JT_AHEAD;                       // the first slot that is empty or holds this key
+#pragma unroll
+            for (int i = JT_AHEAD - 1; i >= 0; --i)
+                if (w[i] == none || w[i] == want) at = i;
+            if (at == JT_AHEAD) {
+                s = (s + JT_AHEAD) & mask;
+                probes += JT_AHEAD;
+                continue;
             }
-            if (prev == static_cast<unsigned long long>(k)) {
-                gq_raise(status, GQ_ERR_DUPLICATE_KEY);
-                break;
-            }
-            s = (s + 1) & mask;
+            s = (s + 1 + at) & mask;
+            probes += 1 + at;
+            prev = atomicCAS(reinterpret_cast<unsigned long long *>(&slots[s].key), none, want);
+            done = prev == none || prev == want;
         }
-        if (probes > mask) gq_raise(status, GQ_ERR_CAPACITY);
+        if (!done) gq_raise(status, GQ_ERR_CAPACITY);
+        else if (prev == want) gq_raise(status, GQ_ERR_DUPLICATE_KEY);
+        else slots[s].payload = p;
     }
 }
 

@@ -314,3 +314,45 @@ def test_partition_offsets_many_tiles(ctx):
         edges = torch.zeros(n - 1, dtype=torch.bool, device="cuda")
         edges[torch.from_numpy(off[1:-1] - 1).cuda()] = True
         assert bool(((d > 0) | edges).all())                   # stable inside each bucket
+
+
+# answers that are ranked by counting (up to 256 keys) and sorted (more), from
+# scans of one step, two and many workgroups
+@pytest.mark.parametrize("n", [1, 255, 4096, 4097, 300_001])
+@pytest.mark.parametrize("k", [1, 255, 256, 257])
+def test_topk_ranked(ctx, n, k):
+    r = np.random.default_rng(n + k)
+    val = r.integers(-50, 50, size=n).astype(np.int64)             # ties go to the smaller row id
+    for desc in (True, False):
+        v, row, cnt = gq.gq_topk(ctx, dev(val), k, descending=desc)
+        c = int(cnt.item())
+        exp = np.lexsort((np.arange(n), -val if desc else val))[:k]
+        assert c == len(exp)
+        assert np.array_equal(row[:c].cpu().numpy(), exp) and np.array_equal(v[:c].cpu().numpy(), val[exp])
+
+
+# keys that walk far from their home slot: one cluster at load factor 0.9, past
+# the table's end, and a second copy of a key at the end of the walk
+def test_insert_walks(ctx):
+    slots = 1 << 14
+    def unmix(h):                                                  # the inverse of fmix64
+        h = h ^ (h >> np.uint64(33))
+        h = h * np.uint64(0x9cb4b2f8129337db)
+        h = h ^ (h >> np.uint64(33))
+        h = h * np.uint64(0x4f74430c22a54005)
+        return h ^ (h >> np.uint64(33))
+    home = np.concatenate([np.full(200, slots - 20), np.full(57, 77), np.arange(1000, 9000)]).astype(np.uint64)
+    h = (home << np.uint64(64 - 14)) | np.arange(len(home), dtype=np.uint64)
+    key = unmix(h).view(np.int64)
+    assert len(np.unique(key)) == len(key)
+    pay = np.arange(len(key), dtype=np.int32)
+    fk = np.concatenate([key, key + 1])
+    table = torch.empty(256 + slots * 16, dtype=torch.uint8, device="cuda")
+    gq.gq_join_build(ctx, dev(key), dev(pay), table=table)
+    assert ctx.status() == gq.GQ_OK
+    prow, out, cnt = gq.gq_join_probe(ctx, table, dev(fk))
+    ep, ey = oracle.join(key, pay, fk, None)
+    c = int(cnt.item())
+    assert c == len(ep) and np.array_equal(prow[:c].cpu().numpy(), ep) and np.array_equal(out[:c].cpu().numpy(), ey)
+    gq.gq_join_build(ctx, dev(np.append(key, key[199])), dev(np.append(pay, 0).astype(np.int32)), table=table)
+    assert ctx.status() == gq.GQ_ERR_DUPLICATE_KEY
