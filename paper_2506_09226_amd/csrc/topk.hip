@@ -27,6 +27,8 @@ constexpr int TK_STEP = TK_THREADS * TK_STEP_ITEMS;  // rows per step
 constexpr int TK_CAP = 4096;                          // LDS candidates
 constexpr int TK_MAX_K = TK_CAP - TK_STEP;            // 2048
 constexpr uint64_t TK_SIGN = 0x8000000000000000ull;
+constexpr uint32_t TK_RANKED = 256;                   // keys of an answer that are ranked by counting
+static_assert(TK_RANKED <= TK_THREADS, "one key per thread");
 
 struct tk_entry {
     uint64_t ok;
@@ -462,12 +464,26 @@ __global__ __launch_bounds__(TK_THREADS) void topk_merge_kernel(tk_lists in, int
         tk_write_list(L, k, need, out);
     } else {
         const uint32_t cnt = L.count;                              // at most k
-        tk_sort_count(L);                                          // the answer, best first
-        for (uint32_t x = tid; x < cnt; x += TK_THREADS) {
-            const uint64_t o = L.ok[x];
+        auto put = [&](uint32_t at, uint64_t o, uint32_t r) {
             const uint64_t u = desc ? o : ~o;
-            val_out[x] = static_cast<int64_t>(u ^ TK_SIGN);
-            rowid_out[x] = static_cast<int32_t>(0x7fffffffu - L.rk[x]);
+            val_out[at] = static_cast<int64_t>(u ^ TK_SIGN);
+            rowid_out[at] = static_cast<int32_t>(0x7fffffffu - r);
+        };
+        if (cnt <= TK_RANKED) {
+            // a few keys: each thread counts those better than its own (keys
+            // are unique), with no barrier, where a sort has one for each of
+            // its log2(cnt)^2 / 2 stages (k = 100 of 3M rows 37.5 -> 34.2 us,
+            // k = 10 of 200K rows 21.9 -> 17.9)
+            if (tid < static_cast<int>(cnt)) {
+                const uint64_t o = L.ok[tid];
+                const uint32_t r = L.rk[tid];
+                uint32_t at = 0;
+                for (uint32_t j = 0; j < cnt; ++j) at += tk_better(L.ok[j], L.rk[j], o, r) ? 1u : 0u;
+                put(at, o, r);
+            }
+        } else {
+            tk_sort_count(L);                                      // the answer, best first
+            for (uint32_t x = tid; x < cnt; x += TK_THREADS) put(x, L.ok[x], L.rk[x]);
         }
         if (tid == 0) *n_out = cnt;
     }
@@ -503,7 +519,10 @@ tk_lists tk_take_lists(gq_carver &c, int64_t lists, int k)
 tk_ws tk_layout(gq_carver &c, int64_t n, int k)
 {
     tk_ws w;
-    int64_t blocks = (n + 4 * TK_STEP - 1) / (4 * TK_STEP);     // at least 4 steps per block
+    // at least 2 steps per block: a small scan is a chain of steps, and the
+    // merge takes more lists more easily (1M rows, k = 100: 166 us for the
+    // pipeline around it at 2, 174 at 4, 168 at 1; 3M rows 37 at 2, 41 at 4)
+    int64_t blocks = (n + 2 * TK_STEP - 1) / (2 * TK_STEP);
     if (blocks > TK_MAX_LISTS) blocks = TK_MAX_LISTS;          // two 512-thread workgroups fit a CU (95 VGPRs)
     if (blocks < 1) blocks = 1;
     int64_t chunk = (n + blocks - 1) / blocks;
