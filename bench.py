@@ -66,7 +66,7 @@ OP_KERNELS = {
                    "gq_join_build_split", "gq_join_build_regions", "gq_join_build_overflow"],
     "join_probe": ["gq_join_probe"],
     "groupby": ["gq_groupby_hist", "gq_groupby_scan", "gq_groupby_scatter", "gq_groupby_tiles2", "gq_groupby_hist2",
-                "gq_groupby_scan2", "gq_groupby_scatter2", "gq_groupby_side", "gq_groupby_chunks", "gq_groupby_bucket",
+                "gq_groupby_scan2", "gq_groupby_scatter2", "gq_groupby_chunks", "gq_groupby_bucket",
                 "gq_groupby_emit", "gq_groupby_local"],
     "topk": ["gq_topk_local", "gq_topk_merge"],
 }

@@ -1282,24 +1282,6 @@ __global__ __launch_bounds__(GL_THREADS) void gb_scatter_lines_kernel(gb_args a,
     }
 }
 
-// Full values of the wide rows into the global table (count 0: their rows
-// were counted by their narrow records).
-template <bool K64, bool K32>
-__global__ __launch_bounds__(256) void gb_side_kernel(gb_args a, const uint32_t *__restrict__ side,
-                                                      const uint32_t *side_cnt, gtable g, uint32_t *status)
-{
-    const uint32_t cnt = *side_cnt;
-    for (uint32_t i0 = blockIdx.x * 256u; i0 < cnt; i0 += gridDim.x * 256u) {
-        const uint32_t i = i0 + threadIdx.x;
-        const bool active = i < cnt;
-        gb_row<K64, K32> r{};
-        if (active) r = load_row<K64, K32>(a, side[i]);
-        const uint64_t h = gb_hash(r.k64, r.k32);
-        const int64_t gs = g_find<K64, K32>(g, active, h, r.k64, r.k32, status);
-        if (active && gs >= 0) g_add(g, gs, 0u, static_cast<uint64_t>(r.qty), r.rev);
-    }
-}
-
 // Large fan-outs (P > GB_MAX_P buckets, up to GB_MAX_P_WIDE) in two levels,
 // each a tile-staged scatter with runs long enough to fill cache lines:
 //   level 1  the rows go to P1 = GB_P1 super-buckets (the scatter above, with
@@ -1499,22 +1481,56 @@ GQ_DEV void lds_add_sums(lds_table<SLOTS, K64, K32> &T, int s, uint32_t cnt, uin
     if (hi_sum) atomicAdd(reinterpret_cast<unsigned long long *>(&T.hi[s]), static_cast<unsigned long long>(hi_sum));
 }
 
-// Chunks of the bucket pass.  A bucket of at most chunk_rows rows is one
-// chunk; a larger one (a bucket holding a heavy key) is cut into
-// ceil(rows / chunk_rows) chunks, each aggregated by its own workgroup.
-// cstart[b] = number of chunks before bucket b.  order[] lists the chunks in
-// the order the bucket pass takes them: the chunks of split buckets first
-// (the longest work, so none of it is left for the end), then the buckets of
-// one chunk.  One workgroup of GB_BUCKET_THREADS threads; P <= GB_MAX_P_WIDE.
-__global__ __launch_bounds__(GB_BUCKET_THREADS) void gb_chunks_kernel(const uint32_t *__restrict__ start, int P,
-                                                                      int64_t chunk_rows, uint32_t *__restrict__ cstart,
-                                                                      uint32_t *__restrict__ order,
-                                                                      uint32_t *__restrict__ sfirst)
+// What the bucket pass needs beyond the partitioned rows, in one launch.
+//
+// Workgroup 0 cuts the chunks of the bucket pass.  A bucket of at most
+// chunk_rows rows is one chunk; a larger one (a bucket holding a heavy key)
+// is cut into ceil(rows / chunk_rows) chunks, each aggregated by its own
+// workgroup.  order[] lists the chunks in the order the bucket pass takes
+// them: the chunks of split buckets first (the longest work, so none of it is
+// left for the end), then the buckets of one chunk; *n_items counts them.  An
+// entry names its bucket and its place in the bucket, so that the bucket pass
+// finds a chunk's rows in two dependent loads.  (A binary search over the
+// buckets for them, and a launch of its own for the side rows, cost 3 us of
+// 168 over 5M rows in 256 buckets and 12 us of 3095 over 50M in 3328.)
+// P <= GB_MAX_P_WIDE.
+//
+// The other workgroups add the full values of the wide rows to the global
+// table (count 0: their rows were counted by their narrow records).
+struct gb_item {
+    uint32_t bucket;
+    uint32_t chunk;                                  // in the bucket; GB_WHOLE: all its rows
+};
+constexpr uint32_t GB_WHOLE = 0xffffffffu;
+constexpr uint32_t GB_SIDE_BLOCKS = 16;
+
+template <bool K64, bool K32>
+__global__ __launch_bounds__(GB_BUCKET_THREADS) void gb_chunks_kernel(gb_args a, const uint32_t *__restrict__ start,
+                                                                      int P, int64_t chunk_rows,
+                                                                      gb_item *__restrict__ order,
+                                                                      uint32_t *__restrict__ n_items,
+                                                                      uint32_t *__restrict__ sfirst,
+                                                                      const uint32_t *__restrict__ side,
+                                                                      const uint32_t *side_cnt, gtable g,
+                                                                      uint32_t *status)
 {
+    if (blockIdx.x > 0) {
+        const uint32_t cnt = *side_cnt;
+        for (uint32_t i0 = (blockIdx.x - 1) * GB_BUCKET_THREADS; i0 < cnt; i0 += GB_SIDE_BLOCKS * GB_BUCKET_THREADS) {
+            const uint32_t i = i0 + threadIdx.x;
+            const bool active = i < cnt;
+            gb_row<K64, K32> r{};
+            if (active) r = load_row<K64, K32>(a, side[i]);
+            const uint64_t h = gb_hash(r.k64, r.k32);
+            const int64_t gs = g_find<K64, K32>(g, active, h, r.k64, r.k32, status);
+            if (active && gs >= 0) g_add(g, gs, 0u, static_cast<uint64_t>(r.qty), r.rev);
+        }
+        return;
+    }
     __shared__ uint32_t scan_smem[GB_BUCKET_THREADS / 64];
     constexpr int PER = GB_MAX_P_WIDE / GB_BUCKET_THREADS;
     uint32_t nch[PER];
-    uint32_t mine = 0, msplit = 0, mone = 0;
+    uint32_t msplit = 0, mone = 0;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         const int b = threadIdx.x * PER + i;
@@ -1523,31 +1539,25 @@ __global__ __launch_bounds__(GB_BUCKET_THREADS) void gb_chunks_kernel(const uint
             const int64_t rows = static_cast<int64_t>(start[b + 1]) - static_cast<int64_t>(start[b]);
             nch[i] = rows > chunk_rows ? static_cast<uint32_t>((rows + chunk_rows - 1) / chunk_rows) : 1u;
         }
-        mine += nch[i];
         msplit += nch[i] > 1 ? nch[i] : 0u;
         mone += nch[i] == 1 ? 1u : 0u;
     }
-    uint32_t total, nsplit, none;
-    uint32_t run = gq_block_exclusive_scan<GB_BUCKET_THREADS>(mine, &total, scan_smem);
+    uint32_t nsplit, none;
     uint32_t srun = gq_block_exclusive_scan<GB_BUCKET_THREADS>(msplit, &nsplit, scan_smem);
     uint32_t orun = gq_block_exclusive_scan<GB_BUCKET_THREADS>(mone, &none, scan_smem);
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        const int b = threadIdx.x * PER + i;
-        if (b < P) {
-            cstart[b] = run;
-            if (nch[i] > 1) {
-                for (uint32_t j = 0; j < nch[i]; ++j) order[srun + j] = run + j;
-                sfirst[b] = srun;
-                srun += nch[i];
-            } else if (nch[i] == 1) {
-                order[nsplit + orun] = run;
-                ++orun;
-            }
+        const uint32_t b = threadIdx.x * PER + i;
+        if (nch[i] > 1) {
+            for (uint32_t j = 0; j < nch[i]; ++j) order[srun + j] = gb_item{b, j};
+            sfirst[b] = srun;
+            srun += nch[i];
+        } else if (nch[i] == 1) {
+            order[nsplit + orun] = gb_item{b, GB_WHOLE};
+            ++orun;
         }
-        run += nch[i];
     }
-    if (threadIdx.x == 0) cstart[P] = total;
+    if (threadIdx.x == 0) *n_items = nsplit + none;
 }
 
 // Persistent: one workgroup per CU takes chunks from a queue (order[], via a
@@ -1568,9 +1578,9 @@ __global__ __launch_bounds__(GB_BUCKET_THREADS) void gb_chunks_kernel(const uint
 template <bool K64, bool K32>
 __global__ __launch_bounds__(GB_BUCKET_THREADS) void gb_bucket_kernel(const uint64_t *__restrict__ recs,
                                                                       const uint32_t *__restrict__ start,
-                                                                      const uint32_t *__restrict__ cstart,
-                                                                      const uint32_t *__restrict__ order,
-                                                                      const uint32_t *__restrict__ sfirst, int P,
+                                                                      const gb_item *__restrict__ order,
+                                                                      const uint32_t *__restrict__ n_items,
+                                                                      const uint32_t *__restrict__ sfirst,
                                                                       int64_t chunk_rows, const uint32_t *side_cnt,
                                                                       uint32_t *qctr, uint32_t *bdone, uint32_t *bspill,
                                                                       uint32_t *pcnt, gb_part *part, gtable g,
@@ -1581,20 +1591,15 @@ __global__ __launch_bounds__(GB_BUCKET_THREADS) void gb_bucket_kernel(const uint
     __shared__ uint32_t scan_smem[GB_BUCKET_THREADS / 64];
     __shared__ unsigned long long s_base;
     __shared__ uint32_t s_item, s_spill, s_last;
-    const uint32_t total = cstart[P];
-    // rows [r0, r1) of queue item `item`, its bucket, and whether that is split
-    auto geom = [&](uint32_t item, int64_t &r0, int64_t &r1, int &bk, bool &split) {
-        const uint32_t ch = order[item];
-        int b = 0;                                   // the bucket of chunk ch: last b with cstart[b] <= ch
-        for (int hi = P - 1; b < hi;) {
-            const int mid = (b + hi + 1) >> 1;
-            if (cstart[mid] <= ch) b = mid;
-            else hi = mid - 1;
-        }
-        split = cstart[b + 1] - cstart[b] > 1;
-        bk = b;
-        const int64_t b0 = start[b], b1 = start[b + 1];
-        r0 = split ? b0 + static_cast<int64_t>(ch - cstart[b]) * chunk_rows : b0;
+    const uint32_t total = *n_items;
+    // rows [r0, r1) of queue item `item`, its bucket, and the bucket's chunks
+    auto geom = [&](uint32_t item, int64_t &r0, int64_t &r1, int &bk, uint32_t &nch) {
+        const gb_item it = order[item];
+        bk = static_cast<int>(it.bucket);
+        const int64_t b0 = start[bk], b1 = start[bk + 1];
+        const bool split = it.chunk != GB_WHOLE;
+        nch = split ? static_cast<uint32_t>((b1 - b0 + chunk_rows - 1) / chunk_rows) : 1u;
+        r0 = split ? b0 + static_cast<int64_t>(it.chunk) * chunk_rows : b0;
         r1 = split ? (r0 + chunk_rows < b1 ? r0 + chunk_rows : b1) : b1;
     };
     constexpr int ITEMS = bucket_items<K64>::value;
@@ -1617,8 +1622,8 @@ __global__ __launch_bounds__(GB_BUCKET_THREADS) void gb_bucket_kernel(const uint
     if (item >= total) return;                       // same for the whole workgroup
     int64_t r0, r1;
     int bk;
-    bool split;
-    geom(item, r0, r1, bk, split);
+    uint32_t nch;                                    // more than one: a split bucket
+    geom(item, r0, r1, bk, nch);
     bool have = false;                               // n*[] hold the first step of this item
     const bool merge = *side_cnt != 0u;              // same value for every thread
     lds_init(T);                                     // once: each chunk leaves the table empty
@@ -1631,8 +1636,8 @@ __global__ __launch_bounds__(GB_BUCKET_THREADS) void gb_bucket_kernel(const uint
         const uint32_t nitem = s_item;
         int64_t nr0 = 0, nr1 = 0;
         int nbk = 0;
-        bool nsplit = false;
-        if (nitem < total) geom(nitem, nr0, nr1, nbk, nsplit);
+        uint32_t nnch = 0;
+        if (nitem < total) geom(nitem, nr0, nr1, nbk, nnch);
         bool have_next = false;
         for (int64_t i0 = r0; i0 < r1; i0 += STEP) {
             int64_t k64[ITEMS], q[ITEMS], rv[ITEMS];
@@ -1687,8 +1692,8 @@ __global__ __launch_bounds__(GB_BUCKET_THREADS) void gb_bucket_kernel(const uint
             }
         }
         __syncthreads();
-        bool emit = !split;
-        if (split) {
+        bool emit = nch == 1;
+        if (nch > 1) {
             // this chunk's partial groups to its stretch of the workspace
             constexpr int PER = SLOTS / GB_BUCKET_THREADS;
             uint32_t mine = 0;
@@ -1710,14 +1715,12 @@ __global__ __launch_bounds__(GB_BUCKET_THREADS) void gb_bucket_kernel(const uint
                 pcnt[item] = all;
                 if (s_spill) atomicOr(&bspill[bk], 1u);
                 __threadfence();                     // partials, count and spill flag before the done count
-                const uint32_t nch = cstart[bk + 1] - cstart[bk];
                 s_last = (atomicAdd(&bdone[bk], 1u) + 1 == nch) ? 1u : 0u;
             }
             __syncthreads();
             if (s_last) {                            // the bucket's last chunk: every other chunk is done
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 const bool to_global = __hip_atomic_load(&bspill[bk], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u;
-                const uint32_t nch = cstart[bk + 1] - cstart[bk];
                 const uint32_t first = sfirst[bk];
                 for (uint32_t j = 0; j < nch; ++j) {
                     const uint32_t it = first + j;
@@ -1802,7 +1805,7 @@ __global__ __launch_bounds__(GB_BUCKET_THREADS) void gb_bucket_kernel(const uint
         r0 = nr0;
         r1 = nr1;
         bk = nbk;
-        split = nsplit;
+        nch = nnch;
         have = have_next;
         __syncthreads();                             // the table is read out before it is cleared
     }
@@ -1915,8 +1918,8 @@ struct gb_ws {
     uint32_t *side_cnt;
     uint32_t *hist;
     uint32_t *start;
-    uint32_t *cstart;       // chunks of the bucket pass before each bucket
-    uint32_t *order;        // the bucket pass's chunk queue
+    gb_item *order;         // the bucket pass's chunk queue
+    uint32_t *n_items;      // its length
     uint32_t *sfirst;       // queue position of a split bucket's first chunk
     uint32_t *bdone;        // chunks of each bucket finished
     uint32_t *bspill;       // a chunk of the bucket sent rows to the global table
@@ -1964,8 +1967,8 @@ gb_ws gb_layout(gq_carver &c, const gb_plan &pl, int64_t n, bool k64, bool k32)
         const int64_t ntiles = gb_tiles_bound(pl, n);
         w.hist = c.take<uint32_t>(static_cast<size_t>(ntiles) * static_cast<size_t>(P1));
         w.start = c.take<uint32_t>(static_cast<size_t>(pl.P) + 1);
-        w.cstart = c.take<uint32_t>(static_cast<size_t>(pl.P) + 1);
-        w.order = c.take<uint32_t>(static_cast<size_t>(pl.bucket_grid));
+        w.order = c.take<gb_item>(static_cast<size_t>(pl.bucket_grid));
+        w.n_items = c.take<uint32_t>(1);
         w.sfirst = c.take<uint32_t>(static_cast<size_t>(pl.P));
         w.pcnt = c.take<uint32_t>(static_cast<size_t>(pl.split_max));
         w.part = c.take<char>(static_cast<size_t>(pl.split_max) * static_cast<size_t>(k64 ? 3072 : 4096) *
@@ -2035,18 +2038,17 @@ gq_status run_groupby(gq_ctx *ctx, const gb_args &a, const gb_plan &pl, const gb
                          static_cast<const uint32_t *>(w.tpre), static_cast<const uint32_t *>(w.hist2), GB_P1, pl.P,
                          pl.P2, w.recs));
     }
-    GQ_TRY(gq_launch(ctx, "gq_groupby_side", gb_side_kernel<K64, K32>, dim3(64), dim3(256), 0, s, a,
-                     static_cast<const uint32_t *>(w.side), static_cast<const uint32_t *>(w.side_cnt), w.g,
-                     ctx->status_dev));
-    GQ_TRY(gq_launch(ctx, "gq_groupby_chunks", gb_chunks_kernel, dim3(1), dim3(GB_BUCKET_THREADS), 0, s,
-                     static_cast<const uint32_t *>(w.start), pl.P, pl.bucket_chunk, w.cstart, w.order, w.sfirst));
+    GQ_TRY(gq_launch(ctx, "gq_groupby_chunks", gb_chunks_kernel<K64, K32>, dim3(1 + GB_SIDE_BLOCKS),
+                     dim3(GB_BUCKET_THREADS), 0, s, a, static_cast<const uint32_t *>(w.start), pl.P, pl.bucket_chunk,
+                     w.order, w.n_items, w.sfirst, static_cast<const uint32_t *>(w.side),
+                     static_cast<const uint32_t *>(w.side_cnt), w.g, ctx->status_dev));
     // one workgroup per CU (its LDS table takes most of a CU), each taking
     // chunks from the queue
     const int64_t bgrid = std::min<int64_t>(pl.bucket_grid, static_cast<int64_t>(ctx->num_cus));
     GQ_TRY(gq_launch(ctx, "gq_groupby_bucket", gb_bucket_kernel<K64, K32>, dim3(static_cast<uint32_t>(bgrid)),
                      dim3(GB_BUCKET_THREADS), 0, s, static_cast<const uint64_t *>(w.recs),
-                     static_cast<const uint32_t *>(w.start), static_cast<const uint32_t *>(w.cstart),
-                     static_cast<const uint32_t *>(w.order), static_cast<const uint32_t *>(w.sfirst), pl.P,
+                     static_cast<const uint32_t *>(w.start), static_cast<const gb_item *>(w.order),
+                     static_cast<const uint32_t *>(w.n_items), static_cast<const uint32_t *>(w.sfirst),
                      pl.bucket_chunk, static_cast<const uint32_t *>(w.side_cnt), w.side_cnt + 32 * (GQ_NUM_XCD + 1),
                      w.bdone, w.bspill, w.pcnt, static_cast<gb_part *>(w.part), w.g, out, ctx->status_dev));
     return gq_launch(ctx, "gq_groupby_emit", gb_table_emit_kernel<K64, K32>, dim3(emit_blocks), dim3(256), 0, s, w.g,
