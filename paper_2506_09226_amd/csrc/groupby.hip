@@ -976,7 +976,7 @@ template <bool K64, bool K32>
 __global__ __launch_bounds__(GB_THREADS) void gb_scatter_kernel(gb_args a, int P, const uint32_t *__restrict__ gofs,
                                                                 uint64_t *__restrict__ recs,
                                                                 uint32_t *__restrict__ side, uint32_t *side_cnt,
-                                                                uint32_t *xctr)
+                                                                uint32_t *xctr, int P2, uint8_t *__restrict__ sub)
 {
     constexpr int ITEMS = gb_fmt<K64, K32>::ITEMS;
     constexpr int TILE = gb_fmt<K64, K32>::TILE;
@@ -986,6 +986,7 @@ __global__ __launch_bounds__(GB_THREADS) void gb_scatter_kernel(gb_args a, int P
     __shared__ uint32_t lpos[GB_MAX_P];          // counts -> local starts -> (global - local) starts
     __shared__ uint32_t scan_smem[GB_THREADS / 64];
     __shared__ uint16_t lbucket[TILE];
+    __shared__ uint8_t lsub[TILE];               // two levels: the sub-buckets
     __shared__ uint64_t stage[TILE * W];
     const int64_t n = eff_n(a.n_bound, a.n_dev);
     const int64_t nt = (n + TILE - 1) / TILE;
@@ -1051,9 +1052,10 @@ __global__ __launch_bounds__(GB_THREADS) void gb_scatter_kernel(gb_args a, int P
         const int64_t tn = r0 + static_cast<int64_t>(gq_uniform(s_next));
         prefetch(tn, nv, nk64, nk32, ngo);              // the next tile: in flight meanwhile
         uint64_t w[ITEMS][W];
-        uint32_t pos[ITEMS];
+        uint32_t pos[ITEMS], psub[ITEMS];
 #pragma unroll
         for (int c = 0; c < ITEMS; ++c) {
+            psub[c] = 0;
             if (keep[c]) {
                 const int64_t j = base + c * GB_THREADS + threadIdx.x;
                 const gq_i128 rev = gq_revenue(pv[c], a.rev_scale, dv[c]);
@@ -1061,8 +1063,10 @@ __global__ __launch_bounds__(GB_THREADS) void gb_scatter_kernel(gb_args a, int P
                 if (!nar) side[atomicAdd(side_cnt, 1u)] = static_cast<uint32_t>(j);
                 make_words<K64, K32>(w[c], k64[c], k32[c], nar ? static_cast<int32_t>(qv[c]) : 0,
                                      nar ? static_cast<int64_t>(rev.lo) : 0);
-                const uint32_t b = gb_bucket(gb_hash(k64[c], k32[c]), P);
+                const uint64_t h = gb_hash(k64[c], k32[c]);
+                const uint32_t b = gb_bucket(h, P);
                 pos[c] = (b << 16) | atomicAdd(&lpos[b], 1u);
+                if (sub) psub[c] = gb_bucket(h, P * P2) - b * static_cast<uint32_t>(P2);
             }
         }
         gq_lds_barrier();
@@ -1089,6 +1093,7 @@ __global__ __launch_bounds__(GB_THREADS) void gb_scatter_kernel(gb_args a, int P
                 const uint32_t b = pos[c] >> 16;
                 const uint32_t q = lpos[b] + (pos[c] & 0xffffu);
                 lbucket[q] = static_cast<uint16_t>(b);
+                if (sub) lsub[q] = static_cast<uint8_t>(psub[c]);
 #pragma unroll
                 for (int x = 0; x < W; ++x) stage[q * W + x] = w[c][x];
             }
@@ -1106,6 +1111,8 @@ __global__ __launch_bounds__(GB_THREADS) void gb_scatter_kernel(gb_args a, int P
             const uint32_t row = q + lpos[lbucket[q]];  // global row position in the bucket array
             recs[static_cast<int64_t>(row) * W + x] = stage[e];
         }
+        if (sub)
+            for (uint32_t q = threadIdx.x; q < all; q += GB_THREADS) sub[q + lpos[lbucket[q]]] = lsub[q];
 #pragma unroll
         for (int c = 0; c < ITEMS; ++c) {
             v[c] = nv[c];
@@ -1325,14 +1332,21 @@ GQ_DEV int gb_super_of(const uint32_t *tpre, int P1, uint32_t g)
     return lo;
 }
 
-// Per level-2 tile: its records counted by sub-bucket -> hist2[g * P2 + sub].
+// Per level-2 tile: its records counted by sub-bucket -> hist2[g * P2 + s].
+// The tile scatter of key64 records leaves each record's sub-bucket in a byte
+// of its own, so this pass reads that byte and not 24 again (50M records: 279
+// -> 75 us here, and 35 more there).  The region scatter writes lines as they
+// fill, where the bytes cost more than they save (20M records: 40 us more
+// there, 18 less here): 16-byte records are read again.
 // Grid: an upper bound on the tile count; surplus workgroups exit.
 template <bool K64, bool K32>
 __global__ __launch_bounds__(GB_THREADS) void gb_hist2_kernel(const uint64_t *__restrict__ recs1,
+                                                              const uint8_t *__restrict__ subs,
                                                               const uint32_t *__restrict__ startA,
                                                               const uint32_t *__restrict__ tpre, int P1, int P,
                                                               int P2, uint32_t *__restrict__ hist2)
 {
+    constexpr int ITEMS = GB_T2 / GB_THREADS;
     __shared__ uint32_t h[GB_MAX_P2];
     const uint32_t g = blockIdx.x;
     if (g >= tpre[P1]) return;                          // same value for the whole workgroup
@@ -1341,13 +1355,23 @@ __global__ __launch_bounds__(GB_THREADS) void gb_hist2_kernel(const uint64_t *__
     const int sb = gb_super_of(tpre, P1, g);
     const int64_t r0 = static_cast<int64_t>(startA[sb]) + static_cast<int64_t>(g - tpre[sb]) * GB_T2;
     const int64_t r1 = r0 + GB_T2 < static_cast<int64_t>(startA[sb + 1]) ? r0 + GB_T2 : startA[sb + 1];
-    for (int64_t i = r0 + threadIdx.x; i < r1; i += GB_THREADS) {
-        int64_t k64, q, rv;
-        int32_t k32;
-        read_words<K64, K32>(recs1, i, k64, k32, q, rv);
-        const uint32_t b = gb_bucket(gb_hash(k64, k32), P);
-        atomicAdd(&h[b - static_cast<uint32_t>(sb) * P2], 1u);
+    uint32_t v[ITEMS];
+#pragma unroll
+    for (int c = 0; c < ITEMS; ++c) {
+        const int64_t i = r0 + c * GB_THREADS + threadIdx.x;
+        v[c] = 0;
+        if constexpr (K64) {
+            if (i < r1) v[c] = subs[i];
+        } else if (i < r1) {
+            int64_t k64, q, rv;
+            int32_t k32;
+            read_words<K64, K32>(recs1, i, k64, k32, q, rv);
+            v[c] = gb_bucket(gb_hash(k64, k32), P) - static_cast<uint32_t>(sb) * P2;
+        }
     }
+#pragma unroll
+    for (int c = 0; c < ITEMS; ++c)
+        if (r0 + c * GB_THREADS + threadIdx.x < r1) atomicAdd(&h[v[c]], 1u);
     __syncthreads();
     for (int i = threadIdx.x; i < P2; i += GB_THREADS) hist2[static_cast<int64_t>(g) * P2 + i] = h[i];
 }
@@ -1933,6 +1957,7 @@ struct gb_ws {
     uint32_t *tpre;         //   level-2 tiles before each super-bucket
     uint32_t *hist2;        //   level-2 counts, then run positions, per (tile, sub-bucket)
     uint64_t *recs1;        //   level-1 records, in super-bucket order
+    uint8_t *sub;           //   their sub-buckets (key64 records)
     size_t zero_bytes;      // prefix of the workspace to clear (table, side count)
 };
 
@@ -1982,6 +2007,7 @@ gb_ws gb_layout(gq_carver &c, const gb_plan &pl, int64_t n, bool k64, bool k32)
             w.tpre = c.take<uint32_t>(GB_P1 + 1);
             w.hist2 = c.take<uint32_t>(static_cast<size_t>(pl.tiles2) * static_cast<size_t>(pl.P2));
             w.recs1 = c.take<uint64_t>(rows * static_cast<size_t>(pl.words));
+            if (k64) w.sub = c.take<uint8_t>(rows);
         }
     }
     return w;
@@ -2015,7 +2041,7 @@ gq_status run_groupby(gq_ctx *ctx, const gb_args &a, const gb_plan &pl, const gb
         sgrid = (sgrid + GQ_NUM_XCD - 1) / GQ_NUM_XCD * GQ_NUM_XCD;
         GQ_TRY(gq_launch(ctx, "gq_groupby_scatter", gb_scatter_kernel<K64, K32>, dim3(static_cast<uint32_t>(sgrid)),
                          dim3(GB_THREADS), 0, s, a, P1, static_cast<const uint32_t *>(w.hist), recs1, w.side,
-                         w.side_cnt, w.side_cnt + 32));
+                         w.side_cnt, w.side_cnt + 32, pl.wide ? pl.P2 : 1, pl.wide ? w.sub : nullptr));
     } else {
         // one region per CU (a workgroup takes most of a CU's LDS)
         const int64_t rgrid = std::min<int64_t>(grid, static_cast<int64_t>(ctx->num_cus));
@@ -2029,8 +2055,9 @@ gq_status run_groupby(gq_ctx *ctx, const gb_args &a, const gb_plan &pl, const gb
                          static_cast<const uint32_t *>(w.startA), GB_P1, w.tpre));
         const uint32_t g2 = static_cast<uint32_t>(pl.tiles2);
         GQ_TRY(gq_launch(ctx, "gq_groupby_hist2", gb_hist2_kernel<K64, K32>, dim3(g2), dim3(GB_THREADS), 0, s,
-                         static_cast<const uint64_t *>(w.recs1), static_cast<const uint32_t *>(w.startA),
-                         static_cast<const uint32_t *>(w.tpre), GB_P1, pl.P, pl.P2, w.hist2));
+                         static_cast<const uint64_t *>(w.recs1), static_cast<const uint8_t *>(w.sub),
+                         static_cast<const uint32_t *>(w.startA), static_cast<const uint32_t *>(w.tpre), GB_P1, pl.P,
+                         pl.P2, w.hist2));
         GQ_TRY(gq_launch(ctx, "gq_groupby_scan2", gb_scan2_kernel, dim3(GB_P1), dim3(256), 0, s, w.hist2,
                          static_cast<const uint32_t *>(w.startA), static_cast<const uint32_t *>(w.tpre), GB_P1, pl.P2,
                          w.start));

@@ -356,3 +356,29 @@ def test_insert_walks(ctx):
     assert c == len(ep) and np.array_equal(prow[:c].cpu().numpy(), ep) and np.array_equal(out[:c].cpu().numpy(), ey)
     gq.gq_join_build(ctx, dev(np.append(key, key[199])), dev(np.append(pay, 0).astype(np.int32)), table=table)
     assert ctx.status() == gq.GQ_ERR_DUPLICATE_KEY
+
+
+# two scatter levels (1280 buckets): key64 records carry their sub-bucket in a
+# byte, key32 records do not; ragged last tiles, and a filter that drops rows
+@pytest.mark.parametrize("n", [1, 2047, 2049, 200_003])
+@pytest.mark.parametrize("kind", ["key64", "both", "key32"])
+def test_two_level_groupby(ctx, n, kind):
+    r = np.random.default_rng(n)
+    domain = 50_000
+    qty, price, disc = (r.integers(lo, hi, size=n).astype(np.int64) for lo, hi in ((1, 51), (100, 10_000_001), (0, 11)))
+    key64 = r.integers(-(1 << 62), 1 << 62, size=domain)[r.integers(0, domain, size=n)] if kind != "key32" else None
+    key32 = r.integers(0, 2 if kind == "both" else domain, size=n).astype(np.int32) if kind != "key64" else None
+    used = np.flatnonzero(disc < 7)
+    cap = 1_400_000 if kind != "key32" else 2_000_000
+    sub = lambda x: None if x is None else x[used]
+    exp = oracle.groupby(len(used), qty[used], price[used], disc[used], key64=sub(key64), key32=sub(key32))
+    d = lambda x: None if x is None else dev(x)
+    res = gq.gq_groupby_agg(ctx, dev(qty), dev(price), dev(disc), key64=d(key64), key32=d(key32), max_groups=cap,
+                            filter_col=dev(disc.astype(np.int32)), filter_lo=0, filter_hi=7)
+    assert ctx.status() == gq.GQ_OK
+    g = res.host()
+    o = np.lexsort((g["key32"] if key32 is not None else np.zeros(len(g["count"])),
+                    g["key64"] if key64 is not None else np.zeros(len(g["count"]))))
+    for f in ("key64", "key32", "count", "sum_qty", "sum_rev_lo", "sum_rev_hi"):
+        if g[f] is not None:
+            assert np.array_equal(g[f][o], exp[f]), f
