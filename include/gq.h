@@ -388,7 +388,9 @@ gq_tuning gq_default_tuning(void);
 size_t gq_batch_workspace_bytes(const gq_instance *inst, int n_inst, const gq_tuning *tuning);
 
 /* Run every instance of the host array inst[0..n_inst) in one persistent
- * kernel.  tuning NULL = gq_default_tuning() (autotuning is the separate,
+ * kernel (hash tables of 2^15 to 2^24 slots are built by three short kernels
+ * before it, so build_tile, init_tile and lag matter to the others only).
+ * tuning NULL = gq_default_tuning() (autotuning is the separate,
  * timed and cached gq_batch_autotune below, so that a plain call never
  * spends seconds searching).  Each instance's out receives its groups
  * (unordered) and n_groups, exactly as gq_groupby_agg would.  ws must be

@@ -5,8 +5,10 @@
 // by that attribute; per group count, sum(qty), exact 128-bit sum of
 // price * (rev_scale - disc) and the float64 averages.
 //
-// Work queue (built on the host, consumed in order through one atomic
-// counter by a persistent grid):
+// Tables of 2^15 slots or more are built before the persistent launch, by
+// regions of slots and without device compare-and-swaps (see "Region builds").
+// The rest is one work queue (built on the host, consumed in order through
+// one atomic counter by a persistent grid):
 //   L_i  instance whose table fits one LDS region: build the whole table in
 //        LDS and write it out (one item)
 //   I_i  table-initialisation tiles of a larger instance (fill EMPTY)
@@ -17,7 +19,7 @@
 //        until the instance's table is complete.  The last P_i item to finish
 //        compacts the instance's groups into its output.
 // Queue order interleaves instances (the build items of instance i+1 come
-// before the probe items of instance i), so device-CAS builds overlap the
+// before the probe items of instance i), so its builds overlap the
 // bandwidth-bound probes of other instances.  An item only ever waits for
 // items that were dequeued before it, which are held by running workgroups
 // that never wait on later items: the wait always ends.
@@ -62,6 +64,9 @@ struct bt_inst {                   // device copy of one instance
     uint64_t *gcnt, *gsq, *glo;
     int64_t *ghi;
     uint64_t gmask;
+    int32_t regions;               // of a table that is built by regions, else 0
+    int32_t first_tile, first_region;   // bin tiles and regions of the instances before this one
+    uint32_t *cursor;              // keys in each region's bin
     uint32_t *counters;            // [0] init done, [1] build done, [2] probe done,
                                    // [3] this instance's error bits (1 << gq_status)
     gq_groups out;
@@ -635,6 +640,198 @@ __global__ __launch_bounds__(BT_THREADS) void batch_kernel(const bt_inst *__rest
     }
 }
 
+// ---------------------------------------------------------- region builds
+// A table of 2^BR_MIN_LOG2 slots or more is built in three small launches
+// ahead of the persistent one:
+//   bin       each tile of keys is counted by table region (BR_SLOTS slots),
+//             takes its places in the regions' bins with one atomic per region,
+//             and moves its keys there.  A region's bin is the region's own
+//             memory, so binning needs no space of its own.
+//   regions   one workgroup per region loads its bin, inserts the keys into a
+//             copy of the region in LDS and writes the whole region, empty
+//             slots included.
+//   overflow  keys whose walk runs past their region, or whose bin was full,
+//             wait in a list and are inserted one by one.
+// Device compare-and-swaps run at the fabric's 9.6 G/s whatever is in flight,
+// and each key needs one and a store of its payload: 19M keys of 64 instances
+// took 2.0 ms of 5.85 (4.63 now: bin 0.17, regions 0.35), 48 of 1K to 100K keys
+// 727 us (620).  The line lies where a build of its own begins to pay for the
+// launches: 64 instances of 3K to 20K keys 443 us from no line, 452 from 2^16,
+// 411 from 2^15, 416 from 2^14; above BR_MAX_LOG2 a tile has few keys per region.
+constexpr int BR_BITS = 13;
+constexpr int BR_SLOTS = 1 << BR_BITS;
+constexpr int BR_THREADS = 1024;
+constexpr int BR_ITEMS = 8;
+constexpr int BR_TILE = BR_THREADS * BR_ITEMS;
+constexpr int BR_MIN_LOG2 = 15;
+constexpr int BR_MAX_LOG2 = 24;
+constexpr int BR_MAX_REGIONS = 1 << (BR_MAX_LOG2 - BR_BITS);
+constexpr int32_t BR_MAX_GRID = 1 << 30;            // regions (and so bin tiles) of all instances: 32-bit counts
+
+struct bt_ovf {
+    int64_t key;
+    int32_t payload;
+    int32_t inst;
+};
+
+// The instance that element g of the concatenated tiles (or regions) is of:
+// the last whose first one is at most g (those with none share the next one's).
+template <typename F>
+GQ_DEV int inst_of(int n, int32_t g, F first)
+{
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (first(mid) <= g) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+GQ_DEV void ovf_push(bt_ovf *ovf, uint32_t *ovf_cnt, int64_t key, int32_t payload, int inst)
+{
+    ovf[atomicAdd(ovf_cnt, 1u)] = bt_ovf{key, payload, inst};      // room for every key
+}
+
+__global__ __launch_bounds__(BR_THREADS) void batch_bin_kernel(const bt_inst *__restrict__ insts, int n,
+                                                               bt_ovf *__restrict__ ovf, uint32_t *ovf_cnt,
+                                                               uint32_t *status)
+{
+    __shared__ uint32_t cnt[BR_MAX_REGIONS], base[BR_MAX_REGIONS];
+    const int32_t g = static_cast<int32_t>(blockIdx.x);
+    const int ii = inst_of(n, g, [&](int i) { return insts[i].first_tile; });
+    const bt_inst &I = insts[ii];
+    const int64_t a = static_cast<int64_t>(g - I.first_tile) * BR_TILE;
+    const int shift = 64 - (I.log2_slots - BR_BITS);
+    int64_t k[BR_ITEMS];
+    int32_t pay[BR_ITEMS];
+    bool valid[BR_ITEMS];
+#pragma unroll
+    for (int c = 0; c < BR_ITEMS; ++c) {
+        const int64_t i = a + c * BR_THREADS + threadIdx.x;
+        valid[c] = i < I.m;
+        k[c] = valid[c] ? __builtin_nontemporal_load(&I.dim_key[i]) : 0;
+        pay[c] = valid[c] ? __builtin_nontemporal_load(&I.dim_attr[i]) : 0;
+    }
+    for (int r = threadIdx.x; r < I.regions; r += BR_THREADS) cnt[r] = 0;
+    __syncthreads();
+    uint32_t reg[BR_ITEMS], rank[BR_ITEMS];
+#pragma unroll
+    for (int c = 0; c < BR_ITEMS; ++c) {
+        reg[c] = rank[c] = 0;
+        if (valid[c] && k[c] == BT_EMPTY) {
+            inst_raise(I, status, GQ_ERR_INVALID_KEY);
+            valid[c] = false;
+        }
+        if (valid[c]) {
+            reg[c] = static_cast<uint32_t>(key_hash(k[c]) >> shift);
+            rank[c] = atomicAdd(&cnt[reg[c]], 1u);
+        }
+    }
+    __syncthreads();
+    for (int r = threadIdx.x; r < I.regions; r += BR_THREADS)
+        if (cnt[r]) base[r] = atomicAdd(&I.cursor[r], cnt[r]);
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < BR_ITEMS; ++c) {
+        if (valid[c]) {
+            const uint32_t at = base[reg[c]] + rank[c];
+            if (at < BR_SLOTS)
+                I.table[(static_cast<int64_t>(reg[c]) << BR_BITS) + at] = bt_slot{k[c], pay[c], 0};
+            else
+                ovf_push(ovf, ovf_cnt, k[c], pay[c], ii);
+        }
+    }
+}
+
+__global__ __launch_bounds__(BR_THREADS) void batch_region_kernel(const bt_inst *__restrict__ insts, int n,
+                                                                  bt_ovf *__restrict__ ovf, uint32_t *ovf_cnt,
+                                                                  uint32_t *status)
+{
+    constexpr int PER = BR_SLOTS / BR_THREADS;
+    __shared__ unsigned long long sk[BR_SLOTS];
+    __shared__ int32_t sp[BR_SLOTS];
+    const int32_t g = static_cast<int32_t>(blockIdx.x);
+    const int ii = inst_of(n, g, [&](int i) { return insts[i].first_region; });
+    const bt_inst &I = insts[ii];
+    const int r = g - I.first_region;
+    bt_slot *slots = I.table + (static_cast<int64_t>(r) << BR_BITS);
+    const uint32_t held = I.cursor[r];
+    const int count = static_cast<int>(held < BR_SLOTS ? held : BR_SLOTS);
+    int64_t k[PER];
+    int32_t pay[PER];
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+        const int j = c * BR_THREADS + threadIdx.x;
+        k[c] = 0;
+        pay[c] = 0;
+        if (j < count) {
+            const int4 v = *reinterpret_cast<const int4 *>(&slots[j]);
+            k[c] = static_cast<int64_t>((static_cast<uint64_t>(static_cast<uint32_t>(v.y)) << 32) |
+                                        static_cast<uint32_t>(v.x));
+            pay[c] = v.z;
+        }
+        sk[j] = static_cast<unsigned long long>(BT_EMPTY);
+        sp[j] = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+        if (c * BR_THREADS + static_cast<int>(threadIdx.x) >= count) continue;
+        uint32_t s = static_cast<uint32_t>(key_hash(k[c]) >> (64 - I.log2_slots)) & (BR_SLOTS - 1);
+        for (; s < BR_SLOTS; ++s) {
+            const unsigned long long prev = atomicCAS(&sk[s], static_cast<unsigned long long>(BT_EMPTY),
+                                                      static_cast<unsigned long long>(k[c]));
+            if (prev == static_cast<unsigned long long>(BT_EMPTY)) {
+                sp[s] = pay[c];
+                break;
+            }
+            if (prev == static_cast<unsigned long long>(k[c])) {
+                inst_raise(I, status, GQ_ERR_DUPLICATE_KEY);
+                break;
+            }
+        }
+        if (s == BR_SLOTS) ovf_push(ovf, ovf_cnt, k[c], pay[c], ii);
+    }
+    __syncthreads();                                 // the copy is complete, and every key of the bin was read
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+        const int j = c * BR_THREADS + threadIdx.x;
+        const unsigned long long w = sk[j];
+        *reinterpret_cast<int4 *>(&slots[j]) =
+            make_int4(static_cast<int32_t>(w), static_cast<int32_t>(w >> 32), sp[j], 0);
+    }
+}
+
+__global__ __launch_bounds__(256) void batch_overflow_kernel(const bt_inst *__restrict__ insts,
+                                                             const bt_ovf *__restrict__ ovf, const uint32_t *ovf_cnt,
+                                                             uint32_t *status)
+{
+    const uint32_t cnt = *ovf_cnt;
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < cnt; i += gridDim.x * 256u) {
+        const bt_ovf e = ovf[i];
+        const bt_inst &I = insts[e.inst];
+        const uint64_t mask = (1ull << I.log2_slots) - 1;
+        uint64_t s = key_hash(e.key) >> (64 - I.log2_slots);
+        uint64_t p = 0;
+        for (; p <= mask; ++p) {
+            const unsigned long long prev = atomicCAS(reinterpret_cast<unsigned long long *>(&I.table[s].key),
+                                                      static_cast<unsigned long long>(BT_EMPTY),
+                                                      static_cast<unsigned long long>(e.key));
+            if (prev == static_cast<unsigned long long>(BT_EMPTY)) {
+                I.table[s].payload = e.payload;
+                break;
+            }
+            if (prev == static_cast<unsigned long long>(e.key)) {
+                inst_raise(I, status, GQ_ERR_DUPLICATE_KEY);
+                break;
+            }
+            s = (s + 1) & mask;
+        }
+        if (p > mask) inst_raise(I, status, GQ_ERR_CAPACITY);
+    }
+}
+
 // zero-probe instances still need their (empty) output count
 __global__ void batch_zero_counts_kernel(const bt_inst *insts, int n)
 {
@@ -673,6 +870,8 @@ struct bt_plan {
     size_t bytes = 0;              // workspace bytes
     size_t zero_bytes = 0;         // prefix to clear (counters, group tables)
     int probe_tile = 0;            // fact rows per probe item
+    int32_t bin_tiles = 0, regions = 0;   // of the region builds
+    bt_ovf *ovf = nullptr;         // their overflow list
 };
 
 bool valid_tuning(const gq_tuning &t)
@@ -703,6 +902,7 @@ bt_plan make_plan(const gq_instance *in, int n, const gq_tuning &t, char *base)
     std::vector<uint32_t *> ctrs(n);
     for (int i = 0; i < n; ++i) ctrs[i] = c.take<uint32_t>(4);
     pl.insts.resize(n);
+    int64_t binned = 0;
     for (int i = 0; i < n; ++i) {
         bt_inst &I = pl.insts[i];
         const int64_t cap = in[i].out.capacity;
@@ -715,6 +915,20 @@ bt_plan make_plan(const gq_instance *in, int n, const gq_tuning &t, char *base)
         I.ghi = c.take<int64_t>(gslots);
         I.gmask = gslots - 1;
         I.counters = ctrs[i];
+        int L = 6;
+        while (static_cast<double>(1ull << L) < static_cast<double>(in[i].m) / t.load_factor) ++L;
+        I.log2_slots = L;
+        I.first_tile = pl.bin_tiles;
+        I.first_region = pl.regions;
+        I.regions = 0;
+        I.cursor = nullptr;
+        if (L >= BR_MIN_LOG2 && L <= BR_MAX_LOG2 && pl.regions <= BR_MAX_GRID) {
+            I.regions = 1 << (L - BR_BITS);
+            I.cursor = c.take<uint32_t>(static_cast<size_t>(I.regions));
+            pl.bin_tiles += static_cast<int32_t>((in[i].m + BR_TILE - 1) / BR_TILE);
+            pl.regions += I.regions;
+            binned += in[i].m;
+        }
     }
     pl.zero_bytes = c.off;
     pl.insts_dev = c.take<bt_inst>(static_cast<size_t>(n));
@@ -734,16 +948,15 @@ bt_plan make_plan(const gq_instance *in, int n, const gq_tuning &t, char *base)
         I.date_hi = s.date_hi;
         I.rev_scale = s.rev_scale;
         I.out = s.out;
-        int L = 6;
-        while (static_cast<double>(1ull << L) < static_cast<double>(s.m) / t.load_factor) ++L;
-        I.log2_slots = L;
-        I.table = c.take<bt_slot>(size_t(1) << L);
-        const int64_t slots = int64_t(1) << L;
+        const int64_t slots = int64_t(1) << I.log2_slots;
+        I.table = c.take<bt_slot>(static_cast<size_t>(slots));
         const bool lds = slots <= BT_REGION_SLOTS;
-        I.init_items = lds ? 0 : static_cast<int32_t>((slots + t.init_tile - 1) / t.init_tile);
-        I.build_items = lds ? 1 : static_cast<int32_t>((s.m + t.build_tile - 1) / t.build_tile);
+        // (a table built by regions is complete before the queue starts)
+        I.init_items = lds || I.regions ? 0 : static_cast<int32_t>((slots + t.init_tile - 1) / t.init_tile);
+        I.build_items = lds ? 1 : I.regions ? 0 : static_cast<int32_t>((s.m + t.build_tile - 1) / t.build_tile);
         I.probe_items = static_cast<int32_t>((s.n + pl.probe_tile - 1) / pl.probe_tile);
     }
+    if (binned > 0) pl.ovf = c.take<bt_ovf>(static_cast<size_t>(binned));
     // queue order: setup (init + build) of instance i, then probes of instance i - lag
     auto push = [&](int kind, int i, int64_t cnt) {
         if (cnt <= 0) return;
@@ -758,6 +971,7 @@ bt_plan make_plan(const gq_instance *in, int n, const gq_tuning &t, char *base)
     };
     auto push_setup = [&](int i) {
         const bt_inst &I = pl.insts[i];
+        if (I.regions) return;
         if (I.init_items == 0) push(K_LDS_BUILD, i, 1);
         else {
             push(K_INIT, i, I.init_items);
@@ -858,6 +1072,18 @@ gq_status gq_batch_join_agg(gq_ctx *ctx, const gq_instance *inst, int n_inst, co
                                          hipMemcpyHostToDevice, s));
     GQ_TRY(gq_launch(ctx, "gq_batch_zero", batch_zero_counts_kernel, dim3((n_inst + 255) / 256), dim3(256), 0, s,
                      static_cast<const bt_inst *>(d_insts), n_inst));
+    if (pl.regions > 0) {
+        uint32_t *ovf_cnt = work + 32;                   // (cleared with the work counter)
+        GQ_TRY(gq_launch(ctx, "gq_batch_bin", batch_bin_kernel, dim3(static_cast<uint32_t>(pl.bin_tiles)),
+                         dim3(BR_THREADS), 0, s, static_cast<const bt_inst *>(d_insts), n_inst, pl.ovf, ovf_cnt,
+                         ctx->status_dev));
+        GQ_TRY(gq_launch(ctx, "gq_batch_regions", batch_region_kernel, dim3(static_cast<uint32_t>(pl.regions)),
+                         dim3(BR_THREADS), 0, s, static_cast<const bt_inst *>(d_insts), n_inst, pl.ovf, ovf_cnt,
+                         ctx->status_dev));
+        GQ_TRY(gq_launch(ctx, "gq_batch_overflow", batch_overflow_kernel, dim3(128), dim3(256), 0, s,
+                         static_cast<const bt_inst *>(d_insts), static_cast<const bt_ovf *>(pl.ovf),
+                         static_cast<const uint32_t *>(ovf_cnt), ctx->status_dev));
+    }
     if (pl.total_items > 0) {
         // three 51 KiB-LDS workgroups fit a CU by LDS, two by registers
         const uint32_t grid = static_cast<uint32_t>(std::min<int64_t>(pl.total_items, int64_t(ctx->num_cus) * 3));

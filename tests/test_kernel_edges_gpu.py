@@ -382,3 +382,52 @@ def test_two_level_groupby(ctx, n, kind):
     for f in ("key64", "key32", "count", "sum_qty", "sum_rev_lo", "sum_rev_hi"):
         if g[f] is not None:
             assert np.array_equal(g[f][o], exp[f]), f
+
+
+# tables built by regions of 8192 slots (2^15 slots and more, here at load
+# factor 0.5) beside one that is not: a bin that overflows, walks past a region
+# and past the table's end, keys that repeat inside a bin and across the
+# overflow list, the marker as a key, and errors kept to their own instance
+def test_batch_region_builds(ctx):
+    r = np.random.default_rng(11)
+
+    def unmix(h):                                                  # the inverse of fmix64
+        h = h ^ (h >> np.uint64(33))
+        h = h * np.uint64(0x9cb4b2f8129337db)
+        h = h ^ (h >> np.uint64(33))
+        h = h * np.uint64(0x4f74430c22a54005)
+        return h ^ (h >> np.uint64(33))
+
+    def keys(home, bits):                                          # distinct keys with these home slots
+        return unmix((home.astype(np.uint64) << np.uint64(64 - bits)) | np.arange(len(home), dtype=np.uint64)).view(np.int64)
+
+    spread = r.integers(-(1 << 62), 1 << 62, size=140_001)
+    crowd = keys(np.concatenate([r.integers(8192, 16384, size=12_000), np.full(2000, 16383)]), 15)
+    ends = keys(np.concatenate([np.full(300, 32767), r.integers(0, 32768, size=14_000)]), 15)
+    dup, marker = spread[:15_000].copy(), spread[:15_000].copy()
+    dup[-1] = dup[3]
+    marker[77] = np.iinfo(np.int64).min
+    crowd_dup = np.append(crowd, [crowd[5], crowd[13_999]])
+    good = [spread, spread[:8192], spread[:8193], crowd, ends, spread[:50_000]]
+    bad = {6: (dup, gq.GQ_ERR_DUPLICATE_KEY), 7: (marker, gq.GQ_ERR_INVALID_KEY), 8: (crowd_dup, gq.GQ_ERR_DUPLICATE_KEY)}
+    specs, exp = [], []
+    for key in good + [k for k, _ in bad.values()]:
+        m, n = len(key), 60_000
+        attr = r.integers(0, 20, size=m).astype(np.int32)
+        fk = np.where(r.random(n) < 0.8, key[r.integers(0, m, size=n)], r.integers(-(1 << 62), 1 << 62, size=n))
+        date = r.integers(0, 100, size=n).astype(np.int32)
+        qty, price, disc = r.integers(1, 51, size=n), r.integers(100, 10_000_001, size=n), r.integers(0, 11, size=n)
+        if len(exp) < len(good):
+            prow, pay = oracle.join(key, attr, fk, np.flatnonzero(date < 60).astype(np.int32))
+            exp.append(oracle.groupby(len(prow), qty, price, disc, rowid=prow, key32=pay))
+        specs.append({"dim_key": dev(key), "dim_attr": dev(attr), "fk": dev(fk), "date": dev(date), "qty": dev(qty),
+                      "price": dev(price), "disc": dev(disc), "date_lo": 0, "date_hi": 60,
+                      "out": gq.alloc_groups(ctx, 64, False, True)})
+    for count in (len(good), len(specs)):
+        status = torch.full((count,), -1, dtype=torch.int32, device="cuda")
+        gq.gq_batch_join_agg(ctx, gq.make_instances(specs[:count]), inst_status=status)
+        word = ctx.status()
+        assert (word == gq.GQ_OK) == (count == len(good))
+        assert status.tolist() == [gq.GQ_OK] * len(good) + [c for _, c in bad.values()][:count - len(good)]
+        for sp, e in zip(specs, exp):
+            check_groups(sp["out"], e, "key32")
