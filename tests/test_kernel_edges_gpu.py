@@ -431,3 +431,28 @@ def test_batch_region_builds(ctx):
         assert status.tolist() == [gq.GQ_OK] * len(good) + [c for _, c in bad.values()][:count - len(good)]
         for sp, e in zip(specs, exp):
             check_groups(sp["out"], e, "key32")
+
+
+# a filter over few groups: the waves' spans of 512 rows, lists that fill a
+# batch exactly, nearly and never, and rows kept by value and by position
+@pytest.mark.parametrize("n", [1, 511, 513, 8193, 2_200_003])
+@pytest.mark.parametrize("keep", [0.0, 0.01, 0.5, 1.0])
+def test_small_groupby_filter_lists(ctx, n, keep):
+    r = np.random.default_rng(n)
+    qty, price, disc = (r.integers(lo, hi, size=n).astype(np.int64) for lo, hi in ((-9, 51), (100, 10_000_001), (0, 11)))
+    price[r.random(n) < 0.01] = 1 << 58                            # revenues past 32 bits and past 64
+    key32 = r.integers(0, 40, size=n).astype(np.int32)             # some past the 32 groups that have copies
+    col = np.where(r.random(n) < keep, r.integers(-5, 5, size=n), 100).astype(np.int32)
+    used = np.flatnonzero((col >= -5) & (col < 5))
+    for k64 in (None, disc):
+        exp = oracle.groupby(len(used), qty[used], price[used], disc[used], key32=key32[used],
+                             key64=None if k64 is None else k64[used])
+        res = gq.gq_groupby_agg(ctx, dev(qty), dev(price), dev(disc), key32=dev(key32),
+                                key64=None if k64 is None else dev(k64), max_groups=512, filter_col=dev(col),
+                                filter_lo=-5, filter_hi=5)
+        assert ctx.status() == gq.GQ_OK
+        g = res.host()
+        o = np.lexsort((g["key32"], np.zeros(len(g["count"])) if k64 is None else g["key64"]))
+        for f in ("key64", "key32", "count", "sum_qty", "sum_rev_lo", "sum_rev_hi"):
+            if g[f] is not None:
+                assert np.array_equal(g[f][o], exp[f]), f
