@@ -724,8 +724,14 @@ gq_status gq_serve_single(gq_ctx *ctx, const gq_serve_tables &t, const gq_serve_
     gq_carver c(ws);
     single_ws w = single_layout(c, t, q);
     const int64_t n = t.n;
-    GQ_TRY(gq_filter(ctx, t.date, GQ_I32, n, nullptr, nullptr, INT32_MIN, q.date_hi, w.sel, &w.cnts[0], w.wf, w.bf,
-                     s));
+    // A filtered aggregate over few groups is one pass: the group-by checks
+    // the dates itself, where a filter in front of it writes row ids that the
+    // group-by reads again (40M rows, 1% kept: 120 -> 91 us; 60%: 318 -> 221).
+    // Over many groups its two passes over the rows would each check them.
+    const bool one_pass = q.kind == GQ_QUERY_FILTER_AGG && q.max_groups <= SV_MAX_AGG_GROUPS;
+    if (!one_pass)
+        GQ_TRY(gq_filter(ctx, t.date, GQ_I32, n, nullptr, nullptr, INT32_MIN, q.date_hi, w.sel, &w.cnts[0], w.wf, w.bf,
+                         s));
     if (q.kind == GQ_QUERY_FILTER_TOPK)
         return gq_topk(ctx, t.price, w.sel, n, &w.cnts[0], q.k, 1, q.out.topk_val, q.out.topk_row, q.out.topk_n,
                        w.wt, w.bt, s);
@@ -735,7 +741,12 @@ gq_status gq_serve_single(gq_ctx *ctx, const gq_serve_tables &t, const gq_serve_
     in.price = t.price;
     in.disc = t.disc;
     in.rev_scale = 100;
-    if (q.kind == GQ_QUERY_FILTER_AGG) {
+    if (one_pass) {
+        in.key64 = t.disc;
+        in.filter = t.date;
+        in.filter_lo = INT32_MIN;
+        in.filter_hi = q.date_hi;
+    } else if (q.kind == GQ_QUERY_FILTER_AGG) {
         in.n_dev = &w.cnts[0];
         in.rowid = w.sel;
         in.key64 = t.disc;
