@@ -586,13 +586,18 @@ gq_status region_build(gq_ctx *ctx, const int64_t *key, const int32_t *payload, 
 // payloads, two workgroups per CU) are the most that keep 32 waves per CU.
 // Fewer rows take fewer steps per wave, always a power of two, so that a
 // wave's stretch starts on a 4-KB boundary (4M probes: 76 us at 8 steps, 97 at
-// 6, 89 at 12): about 512 to 1024 units, and 8 steps until enough units are
-// left for a balanced tail (9M probes: 210 us at 8, 226 at 16).
+// 6, 89 at 12): about a unit per CU (1.9M probes of a 64K-key table: 52 us in
+// 928 units, 45 in 464; 200K: 17.5 in 98, 14.5 in 196; 500K: 18.6 in 245, 22 in
+// 489), and 8 steps until enough units are left for a balanced tail (9M
+// probes: 210 us at 8, 226 at 16).
 // Up to JP_TINY_ROWS rows the chip is not full either way and a call is bound
 // by one unit's chain of loads and the look-back: 512-row units (64K rows:
 // 31 -> 12 us; 100K rows 18 us at 256 rows, 13 at 512 and at 1024).
 constexpr int64_t JP_TINY_ROWS = 1 << 17;
+constexpr int64_t JP_SHORT_ROWS = 1 << 18;
 constexpr int64_t JP_LARGE_ROWS = 1 << 25;
+constexpr int JP_AHEAD = 4;
+constexpr int64_t JP_AHEAD_ROWS = 1 << 20;
 constexpr int JP_THREADS = 1024;
 constexpr int JP_TINY_THREADS = 512;
 constexpr int JP_MAX_STEPS = 16;
@@ -605,8 +610,8 @@ jp_shape jp_shape_of(int64_t n)
 {
     if (n <= JP_TINY_ROWS) return {JP_TINY_THREADS, 1};
     if (n >= JP_LARGE_ROWS) return {JP_THREADS, JP_MAX_STEPS};
-    int steps = 2;
-    while (steps < JP_MAX_STEPS / 2 && n >= 2 * int64_t(steps) * JP_THREADS * 512) steps *= 2;
+    int steps = n < JP_SHORT_ROWS ? 1 : 2;
+    while (steps < JP_MAX_STEPS / 2 && n >= 2 * int64_t(steps) * JP_THREADS * 256) steps *= 2;
     return {JP_THREADS, steps};
 }
 
@@ -632,7 +637,14 @@ probe_ws probe_layout(gq_carver &c, int64_t n)
 // chip moves about 55 G random lines/s from memory (a bare gather).  50M
 // probes of a 6M-key table (268 MB): 1.49 -> 1.09 ms, 46 G probes/s with the
 // 0.7 GB of keys and outputs streamed beside them.
-template <bool HAS_SEL, int THREADS>
+//
+// AHEAD: slots that a walk on from the home slot reads in one trip.  A call of
+// few rows is one unit per workgroup and bound by its longest walks, a chain
+// of trips to the L2; a call of many is bound by the lines themselves, and
+// slots read too far cost more (12M rows of a 50K-key table 174 us at 1, 190
+// at 4; 1M rows and 64K keys 31 and 30, the pipeline around it 167 and 163.5;
+// 200K rows 35.5 and 33).
+template <bool HAS_SEL, int THREADS, int AHEAD>
 __global__ __launch_bounds__(THREADS) void jt_probe_kernel(const void *table, const int64_t *__restrict__ fk,
                                                            int64_t n_bound, const int64_t *n_dev,
                                                            const int32_t *__restrict__ sel, int steps,
@@ -704,16 +716,24 @@ __global__ __launch_bounds__(THREADS) void jt_probe_kernel(const void *table, co
         bool hit = false;
         int32_t pay = 0;
         if (k != JT_EMPTY) {                          // the marker is no key: it matches nothing
-            for (uint64_t probes = 0; probes <= mask; ++probes) {
-                const int64_t sk =
-                    (static_cast<int64_t>(static_cast<uint32_t>(v.y)) << 32) | static_cast<uint32_t>(v.x);
-                if (sk == k) {
-                    hit = true;
-                    pay = v.z;
+            const int64_t sk = (static_cast<int64_t>(static_cast<uint32_t>(v.y)) << 32) | static_cast<uint32_t>(v.x);
+            hit = sk == k;
+            if (hit) pay = v.z;
+            bool done = hit || sk == JT_EMPTY;
+            for (uint64_t probes = 0; !done && probes < mask; probes += AHEAD, s += AHEAD) {
+                int4 u[AHEAD];
+#pragma unroll
+                for (int q = 0; q < AHEAD; ++q) u[q] = *reinterpret_cast<const int4 *>(&slots[(s + 1 + q) & mask]);
+#pragma unroll
+                for (int q = 0; q < AHEAD; ++q) {
+                    const int64_t uk =
+                        (static_cast<int64_t>(static_cast<uint32_t>(u[q].y)) << 32) | static_cast<uint32_t>(u[q].x);
+                    if (!done && uk == k) {
+                        hit = true;
+                        pay = u[q].z;
+                    }
+                    done = done || uk == k || uk == JT_EMPTY;
                 }
-                if (sk == k || sk == JT_EMPTY) break;
-                s = (s + 1) & mask;
-                v = *reinterpret_cast<const int4 *>(&slots[s]);
             }
         }
         const uint64_t b = gq_ballot(hit);
@@ -772,8 +792,12 @@ gq_status probe(const char *who, gq_ctx *ctx, const void *table, int expect_log2
                          expect_log2, prow_out, payload_out, n_out_dev, w.unit_ctr, w.status, ctx->status_dev);
     };
     if (sh.threads == JP_TINY_THREADS)
-        return sel ? launch(jt_probe_kernel<true, JP_TINY_THREADS>) : launch(jt_probe_kernel<false, JP_TINY_THREADS>);
-    return sel ? launch(jt_probe_kernel<true, JP_THREADS>) : launch(jt_probe_kernel<false, JP_THREADS>);
+        return sel ? launch(jt_probe_kernel<true, JP_TINY_THREADS, JP_AHEAD>)
+                   : launch(jt_probe_kernel<false, JP_TINY_THREADS, JP_AHEAD>);
+    if (n <= JP_AHEAD_ROWS)
+        return sel ? launch(jt_probe_kernel<true, JP_THREADS, JP_AHEAD>)
+                   : launch(jt_probe_kernel<false, JP_THREADS, JP_AHEAD>);
+    return sel ? launch(jt_probe_kernel<true, JP_THREADS, 1>) : launch(jt_probe_kernel<false, JP_THREADS, 1>);
 }
 
 }  // namespace

@@ -456,3 +456,21 @@ def test_small_groupby_filter_lists(ctx, n, keep):
         for f in ("key64", "key32", "count", "sum_qty", "sum_rev_lo", "sum_rev_hi"):
             if g[f] is not None:
                 assert np.array_equal(g[f][o], exp[f]), f
+
+
+# probes on both sides of the unit rules (2^18, 2^20, 2^21 rows) over a table
+# with long walks, some past its end
+@pytest.mark.parametrize("n", [(1 << 18) - 1, 1 << 18, (1 << 20) + 1, (1 << 21) - 1])
+def test_probe_walks(ctx, n):
+    r = np.random.default_rng(n)
+    m, slots = 14_700, 1 << 14                                     # load factor 0.897
+    key = r.permutation(np.arange(3 * m))[:m].astype(np.int64) * 1_000_003
+    pay = r.integers(-(1 << 31), 1 << 31, size=m).astype(np.int32)
+    fk = np.where(r.random(n) < 0.5, key[r.integers(0, m, size=n)], r.integers(0, 3 * m, size=n) * 1_000_003 + 1)
+    table = torch.empty(256 + slots * 16, dtype=torch.uint8, device="cuda")
+    gq.gq_join_build(ctx, dev(key), dev(pay), table=table)
+    prow, out, cnt = gq.gq_join_probe(ctx, table, dev(fk))
+    assert ctx.status() == gq.GQ_OK
+    ep, ey = oracle.join(key, pay, fk, None)
+    c = int(cnt.item())
+    assert c == len(ep) and np.array_equal(prow[:c].cpu().numpy(), ep) and np.array_equal(out[:c].cpu().numpy(), ey)
