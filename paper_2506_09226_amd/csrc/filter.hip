@@ -105,7 +105,22 @@ __global__ __launch_bounds__(FT_THREADS) void filter_kernel(const T *__restrict_
     const int64_t row0 = static_cast<int64_t>(u) * unit + static_cast<int64_t>(wave) * steps * 64 + lane;
     constexpr int FT_BATCH = HAS_SEL ? 4 : 8;               // steps whose loads overlap (gathers: 64 us at 4, 85 at 8)
     uint64_t word = 0;                                      // lane i: the matches of step i
-    for (int i0 = 0; i0 < steps; i0 += FT_BATCH) {
+    // a unit whose rows all exist goes without a bound test for each (of 29
+    // vector instructions a step; 200M rows with 59% kept 311 -> 298 us, 100M with
+    // 5% kept 138 -> 132, 3M 13.3 -> 12.5)
+    const bool full = !HAS_SEL && static_cast<int64_t>(u + 1) * unit <= n && steps % FT_BATCH == 0;
+    for (int i0 = 0; full && i0 < steps; i0 += FT_BATCH) {
+        const T *at = col + row0 + i0 * 64;
+        T v[FT_BATCH];
+#pragma unroll
+        for (int c = 0; c < FT_BATCH; ++c) v[c] = __builtin_nontemporal_load(at + c * 64);
+#pragma unroll
+        for (int c = 0; c < FT_BATCH; ++c) {
+            const uint64_t b = gq_ballot(range.test(v[c]));
+            if (lane == i0 + c) word = b;
+        }
+    }
+    for (int i0 = full ? steps : 0; i0 < steps; i0 += FT_BATCH) {
         T v[FT_BATCH];
 #pragma unroll
         for (int c = 0; c < FT_BATCH; ++c) {
