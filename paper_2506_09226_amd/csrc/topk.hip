@@ -489,13 +489,12 @@ __global__ __launch_bounds__(TK_THREADS) void topk_merge_kernel(tk_lists in, int
     }
 }
 
-// Up to TK_ONE_MERGE candidates are merged by one workgroup (16 steps, most
-// of whose keys the lists' bounds turn away); more, first in groups of
-// TK_MERGE_PER lists.
 // Candidates that one workgroup merges alone, and lists per workgroup of a
-// first merge level otherwise (128 lists of 100: 33 us at 16, 36 at 32, 41 at 48).
+// first merge level otherwise (k = 100, 128 lists: 33 us at 16, 36 at 32, 41 at
+// 48; k = 1000 of 50M rows, whose lists come with bounds: 143 us at 2, 145 at 4,
+// 150 at 8, 157 at 16; k = 2000 of 8M: 125, 132, 137).
 int64_t tk_one_merge(int k) { return k <= TK_PLAIN_K ? 8192 : 32768; }
-int tk_merge_per(int k) { return k <= TK_PLAIN_K ? 16 : 8; }
+int tk_merge_per(int k) { return k <= TK_PLAIN_K ? 16 : 2; }
 constexpr int TK_MAX_LISTS = 512;                     // two scan workgroups per CU
 static_assert(TK_MAX_LISTS <= TK_THREADS, "a merge holds one list per thread");
 
