@@ -331,7 +331,8 @@ size_t gq_topk_workspace_bytes(int64_t n, int k);
  * (descending=0) val; equal values are ordered by ascending row id; if fewer
  * than k rows are selected all of them are returned.  Output sorted.
  *   val        device int64, indexed by row id
- *   sel        nullable device int32 row ids (NULL: rows 0..n-1)
+ *   sel        nullable device int32 row ids (NULL: rows 0..n-1); a row that
+ *              is named more than once counts, and is returned, as often
  *   n, n_dev   host bound / optional device length of the selection
  *   k          1..2048
  *   val_out    device int64[k], rowid_out device int32[k]

@@ -1,9 +1,10 @@
 // Top-k with ties broken by ascending row id.
 //
-// Every selected row gets a unique 96-bit order key (ok, rk): ok maps the
-// int64 value to an unsigned word whose order is the requested order, and
-// rk = 0x7fffffff - rowid ranks smaller row ids higher; the k rows with the
-// largest keys are the answer, with no ties left to resolve.
+// Every selected row gets a 96-bit order key (ok, rk): ok maps the int64 value
+// to an unsigned word whose order is the requested order, and
+// rk = 0x7fffffff - rowid ranks smaller row ids higher; the k entries with the
+// largest keys are the answer.  Keys differ unless the selection names a row
+// more than once: it then counts as often as it is named.
 //
 // Stage 1 (many workgroups, one pass over the data): each workgroup streams a
 // contiguous chunk of the selection; rows whose key beats the workgroup's
@@ -102,10 +103,11 @@ GQ_DEV void tk_sort_count(tk_lds &L)
 // of better entries reaches the number still needed.  Once every entry
 // carrying the chosen digits is needed, those entries and all better ones are
 // exactly the best `need`: the entries whose digits under the masks are at
-// least the prefix.  Keys are unique (the row part differs), so the selection
-// always ends.  The digits that all entries share are skipped: every add of
-// such a pass would meet on one counter, and values far from 64 bits wide
-// (prices in cents) share most of theirs.  Block-wide.
+// least the prefix.  Entries of one row have equal keys: if the need-th best
+// is one of several, every digit is chosen and the entries at or above the
+// prefix are more than `need`.  The digits that all entries share are skipped:
+// every add of such a pass would meet on one counter, and values far from 64
+// bits wide (prices in cents) share most of theirs.  Block-wide.
 constexpr int TK_PER = TK_CAP / TK_THREADS;           // buffer entries per thread
 
 struct tk_prefix {
@@ -200,9 +202,10 @@ GQ_DEV uint32_t tk_entries(const tk_lds &L, uint64_t (&ok)[TK_PER], uint32_t (&r
     return valid;
 }
 
-// Keep the best k entries of the buffer (in no particular order) and raise
-// the threshold to the chosen digits followed by zero bits: no larger than the
-// k-th best key, so no key that belongs in the best k is turned away later.
+// Keep the best k entries of the buffer (in no particular order; never more
+// than k, also where equal keys lie at the k-th place) and raise the threshold
+// to the chosen digits followed by zero bits: no larger than the k-th best
+// key, so no key that belongs in the best k is turned away later.
 // Block-wide; L.count must be the same in every thread on entry.
 GQ_DEV void tk_select(tk_lds &L, int k)
 {
@@ -211,27 +214,36 @@ GQ_DEV void tk_select(tk_lds &L, int k)
     uint32_t rk[TK_PER];
     const uint32_t valid = tk_entries(L, ok, rk);
     const tk_prefix x = tk_digits(L, ok, rk, valid, static_cast<uint32_t>(k));
-    bool kp[TK_PER];
-    uint32_t keep = 0;
+    // better entries first, then those that carry the chosen digits, as many as
+    // fit (all of them, unless they are equal); both counts in one scan
+    uint32_t above = 0, equal = 0;                    // one bit per entry
 #pragma unroll
     for (int i = 0; i < TK_PER; ++i) {
         const uint64_t a = ok[i] & x.m_ok;
         const uint32_t b = rk[i] & x.m_rk;
-        kp[i] = ((valid >> i) & 1u) && (a > x.p_ok || (a == x.p_ok && b >= x.p_rk));
-        keep += kp[i] ? 1u : 0u;
+        above |= a > x.p_ok || (a == x.p_ok && b > x.p_rk) ? 1u << i : 0u;
+        equal |= a == x.p_ok && b == x.p_rk ? 1u << i : 0u;
     }
+    above &= valid;
+    equal &= valid;
+    static_assert(TK_CAP < 1 << 16, "two counts in a word");
     uint32_t total;
-    uint32_t pos = gq_block_exclusive_scan_lds<TK_THREADS>(keep, &total, L.scan);
+    const uint32_t pre = gq_block_exclusive_scan_lds<TK_THREADS>(
+        static_cast<uint32_t>(__popc(equal)) << 16 | static_cast<uint32_t>(__popc(above)), &total, L.scan);
+    uint32_t at = pre & 0xffffu, at_eq = (total & 0xffffu) + (pre >> 16);
 #pragma unroll
     for (int i = 0; i < TK_PER; ++i) {
-        if (kp[i]) {
+        const bool eq = (equal >> i) & 1u;
+        const uint32_t pos = eq ? at_eq : at;
+        if ((((above | equal) >> i) & 1u) && pos < static_cast<uint32_t>(k)) {
             L.ok[pos] = ok[i];
             L.rk[pos] = rk[i];
-            ++pos;
         }
+        at += (above >> i) & 1u;
+        at_eq += eq ? 1u : 0u;
     }
     if (threadIdx.x == 0) {
-        L.count = total;                              // k
+        L.count = static_cast<uint32_t>(k);
         L.th_ok = x.p_ok;
         L.th_rk = x.p_rk;
         L.has_th = 1;
@@ -470,15 +482,19 @@ __global__ __launch_bounds__(TK_THREADS) void topk_merge_kernel(tk_lists in, int
             rowid_out[at] = static_cast<int32_t>(0x7fffffffu - r);
         };
         if (cnt <= TK_RANKED) {
-            // a few keys: each thread counts those better than its own (keys
-            // are unique), with no barrier, where a sort has one for each of
-            // its log2(cnt)^2 / 2 stages (k = 100 of 3M rows 37.5 -> 34.2 us,
-            // k = 10 of 200K rows 21.9 -> 17.9)
+            // a few keys: each thread counts those better than its own, and
+            // equal ones before it, with no barrier, where a sort has one for
+            // each of its log2(cnt)^2 / 2 stages (k = 100 of 3M rows 37.5 ->
+            // 34.2 us, k = 10 of 200K rows 21.9 -> 17.9)
             if (tid < static_cast<int>(cnt)) {
                 const uint64_t o = L.ok[tid];
                 const uint32_t r = L.rk[tid];
                 uint32_t at = 0;
-                for (uint32_t j = 0; j < cnt; ++j) at += tk_better(L.ok[j], L.rk[j], o, r) ? 1u : 0u;
+                for (uint32_t j = 0; j < cnt; ++j) {
+                    const uint64_t jo = L.ok[j];
+                    const uint32_t jr = L.rk[j];
+                    at += tk_better(jo, jr, o, r) || (jo == o && jr == r && j < static_cast<uint32_t>(tid)) ? 1u : 0u;
+                }
                 put(at, o, r);
             }
         } else {
