@@ -125,7 +125,7 @@ size_t gq_filter_workspace_bytes(int64_t n);
  *   n          with sel_in NULL: rows of col; else: host bound on the length
  *              of sel_in, with n_dev (nullable) its device length
  *   sel_out    device int32, capacity >= n
- *   n_out_dev  device int64 scalar, receives the output length
+ *   n_out_dev  device int64 scalar, receives the output length; may be n_dev
  * Errors: GQ_ERR_INVALID_ARG (NULL col/sel_out/n_out_dev, n < 0 or > 2^31-1,
  * bad dtype), GQ_ERR_WORKSPACE. */
 gq_status gq_filter(gq_ctx *ctx, const void *col, int dtype, int64_t n, const int64_t *n_dev,

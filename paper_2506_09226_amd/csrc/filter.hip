@@ -248,7 +248,9 @@ gq_status launch_filter(gq_ctx *ctx, const void *col, const int32_t *sel_in, int
                         int64_t lo, int64_t hi, int32_t *out, int64_t *n_out, void *scratch, hipStream_t s)
 {
     const T *c = static_cast<const T *>(col);
-    if (n <= (S ? FT_TINY_SEL_ROWS : FT_TINY_ROWS)) {
+    // (a count that is narrowed in place needs the look-back: its last unit
+    // writes the count after every other one has read it)
+    if (n <= (S ? FT_TINY_SEL_ROWS : FT_TINY_ROWS) && n_out != n_dev) {
         const uint32_t grid = static_cast<uint32_t>(n > 0 ? (n + FT_THREADS - 1) / FT_THREADS : 1);
         return gq_launch(ctx, "gq_filter", filter_tiny_kernel<T, S>, dim3(grid), dim3(FT_THREADS), 0, s, c, sel_in, n,
                          n_dev, lo, hi, reinterpret_cast<uintptr_t>(col) % 16 == 0 ? 1 : 0, out, n_out);
