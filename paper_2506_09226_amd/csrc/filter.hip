@@ -260,8 +260,8 @@ gq_status launch_filter(gq_ctx *ctx, const void *col, const int32_t *sel_in, int
     GQ_TRY(gq_zero(ctx, scratch, cv.off / 4, s));     // unit counter + status words (a kernel: no memset node under capture)
     const int steps = ft_steps(n);
     const int64_t unit = static_cast<int64_t>(FT_THREADS) * steps;
-    return gq_launch(ctx, "gq_filter", filter_kernel<T, S>, dim3(static_cast<uint32_t>((n + unit - 1) / unit)),
-                     dim3(FT_THREADS), 0, s, c, sel_in, n, n_dev, lo, hi, steps, out, n_out, w.unit_ctr, w.status);
+    return gq_launch(ctx, "gq_filter", filter_kernel<T, S>,
+                     dim3(static_cast<uint32_t>(n > 0 ? (n + unit - 1) / unit : 1)), dim3(FT_THREADS), 0, s, c, sel_in, n, n_dev, lo, hi, steps, out, n_out, w.unit_ctr, w.status);
 }
 
 gq_status run_filter(gq_ctx *ctx, const void *col, int dtype, const int32_t *sel_in, int64_t n, const int64_t *n_dev,

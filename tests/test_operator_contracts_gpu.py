@@ -56,7 +56,7 @@ def test_topk_of_repeated_rows(ctx, n, k, rows):
 
 # a device count narrowed in place: n_out_dev is n_dev.  Few rows pass, so a
 # workgroup that read the new count would drop matches.
-@pytest.mark.parametrize("n", [1, 1025, 32_768, 32_769, 200_000])
+@pytest.mark.parametrize("n", [0, 1, 1025, 32_768, 32_769, 200_000])
 @pytest.mark.parametrize("with_sel", [False, True])
 def test_filter_narrows_its_count_in_place(ctx, n, with_sel):
     r = np.random.default_rng(n)
@@ -68,8 +68,8 @@ def test_filter_narrows_its_count_in_place(ctx, n, with_sel):
     col_d = dev(col[:n] if sel is None else col)
     for f in (gq.gq_filter, gq.gq_filter_noalloc):
         for _ in range(20):
-            cnt = torch.tensor([used], dtype=torch.int64, device="cuda")
-            out = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+            cnt = torch.tensor([used if n else 5], dtype=torch.int64, device="cuda")
+            out = torch.full((max(n, 1),), -1, dtype=torch.int32, device="cuda")
             f(ctx, col_d, 0, 20, sel_in=sel_d, n=n, n_dev=cnt, out=out, n_out=cnt)
             assert int(cnt.item()) == len(exp)
             assert np.array_equal(out[:len(exp)].cpu().numpy(), exp)
