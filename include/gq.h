@@ -124,7 +124,7 @@ size_t gq_filter_workspace_bytes(int64_t n);
  *   col        device, `dtype` (GQ_I32 or GQ_I64) elements, indexed by row id
  *   n          with sel_in NULL: rows of col; else: host bound on the length
  *              of sel_in, with n_dev (nullable) its device length
- *   sel_out    device int32, capacity >= n
+ *   sel_out    device int32, capacity >= n; may be sel_in
  *   n_out_dev  device int64 scalar, receives the output length; may be n_dev
  * Errors: GQ_ERR_INVALID_ARG (NULL col/sel_out/n_out_dev, n < 0 or > 2^31-1,
  * bad dtype), GQ_ERR_WORKSPACE. */

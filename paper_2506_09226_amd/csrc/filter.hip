@@ -80,13 +80,18 @@ GQ_DEV int64_t ft_rows(int64_t bound, const int64_t *n_dev)
     return d < bound ? (d > 0 ? d : 0) : bound;
 }
 
-template <typename T, bool HAS_SEL>
+// IN_PLACE: the output is the selection itself.  A unit's outputs lie at its own
+// or earlier rows, and every earlier unit has read its rows before it publishes
+// its count; so a unit keeps its row ids in LDS instead of reading them again.
+template <typename T, bool HAS_SEL, bool IN_PLACE>
 __global__ __launch_bounds__(FT_THREADS) void filter_kernel(const T *__restrict__ col,
                                                             const int32_t *__restrict__ sel_in,
                                                             int64_t n_bound, const int64_t *n_dev, int64_t lo,
                                                             int64_t hi, int steps, int32_t *__restrict__ out,
                                                             int64_t *n_out, uint32_t *unit_ctr, uint64_t *status)
 {
+    static_assert(HAS_SEL || !IN_PLACE, "without a selection there is nothing to overwrite");
+    extern __shared__ int32_t held[];                       // IN_PLACE: the unit's row ids
     __shared__ uint32_t wcnt[FT_WAVES];
     __shared__ uint32_t s_unit;
     __shared__ uint64_t s_goff;
@@ -126,8 +131,15 @@ __global__ __launch_bounds__(FT_THREADS) void filter_kernel(const T *__restrict_
         for (int c = 0; c < FT_BATCH; ++c) {
             const int64_t e = row0 + (i0 + c) * 64;
             v[c] = 0;
-            if (i0 + c < steps && e < n)
-                v[c] = HAS_SEL ? col[sel_in[e]] : __builtin_nontemporal_load(&col[e]);
+            if (i0 + c < steps && e < n) {
+                if constexpr (HAS_SEL) {
+                    const int32_t r = sel_in[e];
+                    if (IN_PLACE) held[(wave * steps + i0 + c) * 64 + lane] = r;
+                    v[c] = col[r];
+                } else {
+                    v[c] = __builtin_nontemporal_load(&col[e]);
+                }
+            }
         }
 #pragma unroll
         for (int c = 0; c < FT_BATCH; ++c) {
@@ -163,7 +175,8 @@ __global__ __launch_bounds__(FT_THREADS) void filter_kernel(const T *__restrict_
         const uint32_t pre = __builtin_amdgcn_readlane(excl, i);
         if ((b >> lane) & 1u) {
             const int64_t e = row0 + i * 64;
-            out[goff + pre + gq_mbcnt(b)] = HAS_SEL ? sel_in[e] : static_cast<int32_t>(e);
+            out[goff + pre + gq_mbcnt(b)] =
+                IN_PLACE ? held[(wave * steps + i) * 64 + lane] : HAS_SEL ? sel_in[e] : static_cast<int32_t>(e);
         }
     }
 }
@@ -248,9 +261,10 @@ gq_status launch_filter(gq_ctx *ctx, const void *col, const int32_t *sel_in, int
                         int64_t lo, int64_t hi, int32_t *out, int64_t *n_out, void *scratch, hipStream_t s)
 {
     const T *c = static_cast<const T *>(col);
-    // (a count that is narrowed in place needs the look-back: its last unit
-    // writes the count after every other one has read it)
-    if (n <= (S ? FT_TINY_SEL_ROWS : FT_TINY_ROWS) && n_out != n_dev) {
+    // (a count or a selection that is narrowed in place needs the look-back:
+    // a unit writes after every earlier one has read its own)
+    const bool in_place = S && out == sel_in;
+    if (n <= (S ? FT_TINY_SEL_ROWS : FT_TINY_ROWS) && n_out != n_dev && !in_place) {
         const uint32_t grid = static_cast<uint32_t>(n > 0 ? (n + FT_THREADS - 1) / FT_THREADS : 1);
         return gq_launch(ctx, "gq_filter", filter_tiny_kernel<T, S>, dim3(grid), dim3(FT_THREADS), 0, s, c, sel_in, n,
                          n_dev, lo, hi, reinterpret_cast<uintptr_t>(col) % 16 == 0 ? 1 : 0, out, n_out);
@@ -260,8 +274,15 @@ gq_status launch_filter(gq_ctx *ctx, const void *col, const int32_t *sel_in, int
     GQ_TRY(gq_zero(ctx, scratch, cv.off / 4, s));     // unit counter + status words (a kernel: no memset node under capture)
     const int steps = ft_steps(n);
     const int64_t unit = static_cast<int64_t>(FT_THREADS) * steps;
-    return gq_launch(ctx, "gq_filter", filter_kernel<T, S>,
-                     dim3(static_cast<uint32_t>(n > 0 ? (n + unit - 1) / unit : 1)), dim3(FT_THREADS), 0, s, c, sel_in, n, n_dev, lo, hi, steps, out, n_out, w.unit_ctr, w.status);
+    const dim3 grid(static_cast<uint32_t>(n > 0 ? (n + unit - 1) / unit : 1));
+    if constexpr (S) {
+        if (in_place)                                 // 128 KB of row ids at most
+            return gq_launch(ctx, "gq_filter", filter_kernel<T, true, true>, grid, dim3(FT_THREADS),
+                             static_cast<size_t>(unit) * sizeof(int32_t), s, c, sel_in, n, n_dev, lo, hi, steps, out,
+                             n_out, w.unit_ctr, w.status);
+    }
+    return gq_launch(ctx, "gq_filter", filter_kernel<T, S, false>, grid, dim3(FT_THREADS), 0, s, c, sel_in, n, n_dev,
+                     lo, hi, steps, out, n_out, w.unit_ctr, w.status);
 }
 
 gq_status run_filter(gq_ctx *ctx, const void *col, int dtype, const int32_t *sel_in, int64_t n, const int64_t *n_dev,

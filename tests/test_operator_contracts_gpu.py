@@ -73,3 +73,27 @@ def test_filter_narrows_its_count_in_place(ctx, n, with_sel):
             f(ctx, col_d, 0, 20, sel_in=sel_d, n=n, n_dev=cnt, out=out, n_out=cnt)
             assert int(cnt.item()) == len(exp)
             assert np.array_equal(out[:len(exp)].cpu().numpy(), exp)
+
+
+# a selection narrowed in place (sel_out is sel_in), alone and with its count;
+# units of 1024 rows, of several steps and of 32 (the most row ids held)
+@pytest.mark.parametrize("n", [1, 65, 1025, 32_768, 32_769, 262_145, 4_194_304 + 77, 9_000_001])
+@pytest.mark.parametrize("dtype", [np.int32, np.int64])
+@pytest.mark.parametrize("hi", [20, 900])
+def test_filter_narrows_a_selection_in_place(ctx, n, dtype, hi):
+    r = np.random.default_rng(n)
+    col = r.integers(0, 1000, size=n + 100).astype(dtype)
+    sel = r.permutation(n + 100)[:n].astype(np.int32)
+    col_d = dev(col)
+    for f, used in ((gq.gq_filter, n), (gq.gq_filter, n - n // 50), (gq.gq_filter_noalloc, n - n // 3)):
+        exp = oracle.filter(col, 0, hi, sel_in=sel[:used])
+        s = dev(sel)
+        if used == n:
+            cnt = torch.zeros(1, dtype=torch.int64, device="cuda")
+            f(ctx, col_d, 0, hi, sel_in=s, out=s, n_out=cnt)
+        else:
+            cnt = torch.tensor([used], dtype=torch.int64, device="cuda")
+            f(ctx, col_d, 0, hi, sel_in=s, n_dev=cnt, out=s, n_out=cnt)
+        assert int(cnt.item()) == len(exp)
+        assert np.array_equal(s[:len(exp)].cpu().numpy(), exp)
+        assert np.array_equal(s[len(exp):].cpu().numpy(), sel[len(exp):])      # nothing past the answer is touched
