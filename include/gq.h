@@ -224,8 +224,8 @@ size_t gq_join_probe_workspace_bytes(int64_t n);
  * pairs are compacted in probe order; unmatched rows are dropped.
  *   n, n_dev   host bound / optional device length of the probe (of sel, or
  *              of fk when sel is NULL)
- *   prow_out, payload_out  device int32, capacity >= n
- *   n_out_dev  device int64 scalar, receives the number of pairs
+ *   prow_out, payload_out  device int32, capacity >= n; prow_out may be sel
+ *   n_out_dev  device int64 scalar, receives the number of pairs; may be n_dev
  * Errors: GQ_ERR_INVALID_ARG, GQ_ERR_WORKSPACE. */
 gq_status gq_join_probe(gq_ctx *ctx, const void *table, const int64_t *fk,
                         int64_t n, const int64_t *n_dev, const int32_t *sel,

@@ -644,7 +644,11 @@ probe_ws probe_layout(gq_carver &c, int64_t n)
 // slots read too far cost more (12M rows of a 50K-key table 174 us at 1, 190
 // at 4; 1M rows and 64K keys 31 and 30, the pipeline around it 167 and 163.5;
 // 200K rows 35.5 and 33).
-template <bool HAS_SEL, int THREADS, int AHEAD>
+//
+// IN_PLACE: prow_out is the selection itself.  A unit's outputs lie at its own
+// or earlier rows, and every earlier unit has read its rows before it publishes
+// its count; so a unit keeps its row ids in LDS instead of reading them again.
+template <bool HAS_SEL, int THREADS, int AHEAD, bool IN_PLACE = false>
 __global__ __launch_bounds__(THREADS) void jt_probe_kernel(const void *table, const int64_t *__restrict__ fk,
                                                            int64_t n_bound, const int64_t *n_dev,
                                                            const int32_t *__restrict__ sel, int steps,
@@ -655,7 +659,9 @@ __global__ __launch_bounds__(THREADS) void jt_probe_kernel(const void *table, co
     constexpr int WAVES = THREADS / 64;
     constexpr int MAX_WORDS = WAVES * JP_MAX_STEPS;
     static_assert(MAX_WORDS <= THREADS, "one word per thread in the scan");
-    extern __shared__ int32_t pay_lds[];              // payload of each row of the unit
+    static_assert(HAS_SEL || !IN_PLACE, "without a selection there is nothing to overwrite");
+    extern __shared__ int32_t pay_lds[];              // payload of each row of the unit (then their row ids)
+    int32_t *row_lds = pay_lds + THREADS * steps;     // IN_PLACE
     __shared__ uint64_t bits[MAX_WORDS];              // matches of the unit, one bit per row
     __shared__ uint32_t wpre[MAX_WORDS];              // matches before each word
     __shared__ uint32_t scan_smem[WAVES];
@@ -701,6 +707,7 @@ __global__ __launch_bounds__(THREADS) void jt_probe_kernel(const void *table, co
     };
     auto load_key = [&](int i) {
         const int64_t e = row0 + i * 64;
+        if (IN_PLACE && i < steps) row_lds[(word0 + i) * 64 + lane] = nr;
         nk = (i < steps && e < n) ? __builtin_nontemporal_load(&fk[HAS_SEL ? static_cast<int64_t>(nr) : e]) : JT_EMPTY;
     };
     load_row(0);
@@ -760,7 +767,7 @@ __global__ __launch_bounds__(THREADS) void jt_probe_kernel(const void *table, co
         if ((b >> lane) & 1u) {
             const int64_t o = goff + wpre[word0 + i] + gq_mbcnt(b);
             const int64_t e = row0 + i * 64;
-            prow_out[o] = HAS_SEL ? sel[e] : static_cast<int32_t>(e);
+            prow_out[o] = IN_PLACE ? row_lds[(word0 + i) * 64 + lane] : HAS_SEL ? sel[e] : static_cast<int32_t>(e);
             pay_out[o] = pay_lds[(word0 + i) * 64 + lane];
         }
     }
@@ -786,11 +793,14 @@ gq_status probe(const char *who, gq_ctx *ctx, const void *table, int expect_log2
     const jp_shape sh = jp_shape_of(n);
     const int64_t unit = sh.unit();
     const uint32_t grid = static_cast<uint32_t>(n > 0 ? (n + unit - 1) / unit : 1);
-    auto launch = [&](auto kernel) {
+    auto launch = [&](auto kernel, int held = 1) {   // held: 32-bit words kept per row
         return gq_launch(ctx, "gq_join_probe", kernel, dim3(grid), dim3(static_cast<uint32_t>(sh.threads)),
-                         static_cast<size_t>(unit) * sizeof(int32_t), s, table, fk, n, n_dev, sel, sh.steps,
+                         static_cast<size_t>(unit) * held * sizeof(int32_t), s, table, fk, n, n_dev, sel, sh.steps,
                          expect_log2, prow_out, payload_out, n_out_dev, w.unit_ctr, w.status, ctx->status_dev);
     };
+    if (sel && prow_out == sel)                       // the selection is narrowed in place
+        return sh.threads == JP_TINY_THREADS ? launch(jt_probe_kernel<true, JP_TINY_THREADS, JP_AHEAD, true>, 2)
+                                             : launch(jt_probe_kernel<true, JP_THREADS, 1, true>, 2);
     if (sh.threads == JP_TINY_THREADS)
         return sel ? launch(jt_probe_kernel<true, JP_TINY_THREADS, JP_AHEAD>)
                    : launch(jt_probe_kernel<false, JP_TINY_THREADS, JP_AHEAD>);

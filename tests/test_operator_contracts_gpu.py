@@ -97,3 +97,28 @@ def test_filter_narrows_a_selection_in_place(ctx, n, dtype, hi):
         assert int(cnt.item()) == len(exp)
         assert np.array_equal(s[:len(exp)].cpu().numpy(), exp)
         assert np.array_equal(s[len(exp):].cpu().numpy(), sel[len(exp):])      # nothing past the answer is touched
+
+
+# a probe that narrows its selection in place (prow_out is sel), with its count:
+# units of 512 rows, of 1024 rows and of 16 steps
+@pytest.mark.parametrize("n", [1, 65, 513, 131_072, 131_073, 2_000_003, (1 << 25) + 5])
+@pytest.mark.parametrize("hits", [0.02, 0.9])
+def test_probe_narrows_a_selection_in_place(ctx, n, hits):
+    r = np.random.default_rng(n)
+    m = 5000
+    key = r.permutation(m * 4)[:m].astype(np.int64) * 7919
+    pay = r.integers(-(1 << 31), 1 << 31, size=m).astype(np.int32)
+    rows = min(n, 500_000) + 100
+    fk = np.where(r.random(rows) < hits, key[r.integers(0, m, size=rows)], -1)
+    sel = r.integers(0, rows, size=n).astype(np.int32)
+    table = gq.gq_join_build(ctx, dev(key), dev(pay))
+    fk_d = dev(fk)
+    for f, used in ((gq.gq_join_probe, n), (gq.gq_join_probe_partitioned, n - n // 3)):
+        ep, ey = oracle.join(key, pay, fk, sel[:used])
+        s = dev(sel)
+        cnt = torch.tensor([used], dtype=torch.int64, device="cuda")
+        _, got, _ = f(ctx, table, fk_d, sel=s, n_dev=cnt, prow=s, n_out=cnt)
+        assert ctx.status() == gq.GQ_OK
+        assert int(cnt.item()) == len(ep)
+        assert np.array_equal(s[:len(ep)].cpu().numpy(), ep) and np.array_equal(got[:len(ep)].cpu().numpy(), ey)
+        assert np.array_equal(s[len(ep):].cpu().numpy(), sel[len(ep):])        # nothing past the answer is touched
