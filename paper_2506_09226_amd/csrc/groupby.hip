@@ -30,6 +30,7 @@
 #include "gq_device.h"
 #include "gq_internal.h"
 #include "gq_ops.h"
+#include "gq_slot_hash.h"
 
 namespace {
 
@@ -513,13 +514,12 @@ struct gs_lds {
 constexpr uint32_t GS_NO_ID = 0xffffffffu;
 constexpr uint32_t GS_ID_CLAIMED = 0xfffffffeu;      // being handed out, or none left
 
-// Hash of a key for the LDS table alone (its top bits pick the home slot).
+// Hash of a key for the LDS table alone, where lds_home looks.
+template <bool K64>
 GQ_DEV uint64_t gs_hash(int64_t k64, int32_t k32)
 {
-    const uint64_t k = static_cast<uint64_t>(k64);
-    uint32_t x = static_cast<uint32_t>(k) + static_cast<uint32_t>(k >> 32) * 0x85EBCA6Bu;
-    x = x * 0x9E3779B1u + static_cast<uint32_t>(k32) * 0x9E3779B1u;
-    return static_cast<uint64_t>(x) << 8;            // where lds_home looks
+    const uint32_t x = static_cast<uint32_t>(k32);
+    return static_cast<uint64_t>(K64 ? gq_slot_hash(static_cast<uint64_t>(k64), x) : gq_slot_hash(x, 0)) << 8;
 }
 
 // Each workgroup adds its share of the rows up in LDS and writes its groups
@@ -559,7 +559,7 @@ __global__ __launch_bounds__(GS_THREADS) void gb_small_kernel(gb_args a, gtable 
             int64_t rev;
             gq_i128 wide{0, 0};
             const bool narrow = gq_revenue_narrow(act[c], pv[c], a.rev_scale, dv[c], rev, wide);
-            const int s = lds_find(T, act[c], gs_hash(k64[c], k32[c]), k64[c], k32[c]);
+            const int s = lds_find(T, act[c], gs_hash<K64>(k64[c], k32[c]), k64[c], k32[c]);
             if (act[c] && s >= 0) {
                 uint32_t id = __hip_atomic_load(&S.id[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 if (id == GS_NO_ID && atomicCAS(&S.id[s], GS_NO_ID, GS_ID_CLAIMED) == GS_NO_ID) {
@@ -792,7 +792,7 @@ __global__ __launch_bounds__(GS_THREADS) void gb_small_kernel(gb_args a, gtable 
 #pragma unroll
         for (int c = 0; c < GS_FOLD; ++c) {
             const bool act = i0 + c * GS_THREADS + threadIdx.x < parts;
-            const int sl = lds_find(T, act, gs_hash(pe[c].k64, pe[c].k32), pe[c].k64, pe[c].k32);
+            const int sl = lds_find(T, act, gs_hash<K64>(pe[c].k64, pe[c].k32), pe[c].k64, pe[c].k32);
             if (act && sl >= 0) lds_add(T, sl, pe[c].cnt, pe[c].sq, gq_i128{pe[c].lo, pe[c].hi});
             const bool over = act && sl < 0;
             if (__any(over)) {

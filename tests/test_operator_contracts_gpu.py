@@ -122,3 +122,25 @@ def test_probe_narrows_a_selection_in_place(ctx, n, hits):
         assert int(cnt.item()) == len(ep)
         assert np.array_equal(s[:len(ep)].cpu().numpy(), ep) and np.array_equal(got[:len(ep)].cpu().numpy(), ey)
         assert np.array_equal(s[len(ep):].cpu().numpy(), sel[len(ep):])        # nothing past the answer is touched
+
+
+# few groups whose keys are structured: sums of the key's words that agree, and
+# strides at which a plain product puts neighbours side by side
+@pytest.mark.parametrize("n", [513, 100_003])
+@pytest.mark.parametrize("kind", ["anti-diagonal", "grid", "key64 stride", "key32 stride"])
+def test_small_groupby_of_structured_keys(ctx, n, kind):
+    r = np.random.default_rng(n)
+    i = r.integers(0, 512, size=n)
+    k64, k32 = {"anti-diagonal": (i, 511 - i), "grid": (i % 22, i // 22 % 23), "key64 stride": (i * 10_946, None),
+                "key32 stride": (None, i * -1597)}[kind]
+    k32 = None if k32 is None else k32.astype(np.int32)
+    qty, price, disc = r.integers(-50, 50, size=n), r.integers(0, 10_000_000, size=n), r.integers(0, 11, size=n)
+    exp = oracle.groupby(n, qty, price, disc, key64=k64, key32=k32)
+    res = gq.gq_groupby_agg(ctx, dev(qty), dev(price), dev(disc), key64=None if k64 is None else dev(k64),
+                            key32=None if k32 is None else dev(k32), max_groups=512)
+    assert ctx.status() == gq.GQ_OK
+    g = res.host()
+    order = np.lexsort([g[f] for f in ("key32", "key64") if g[f] is not None])
+    for f in ("key64", "key32", "count", "sum_qty", "sum_rev_lo", "sum_rev_hi"):
+        if g[f] is not None:
+            assert np.array_equal(g[f][order], exp[f]), f
