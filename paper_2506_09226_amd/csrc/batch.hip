@@ -30,6 +30,7 @@
 
 #include "gq_device.h"
 #include "gq_internal.h"
+#include "gq_slot_hash.h"
 
 namespace {
 
@@ -180,7 +181,7 @@ GQ_DEV uint64_t group_hash(int32_t k) { return gq_fmix64(static_cast<uint64_t>(s
 // fail.  tag: the group's id + 2, or 1 when it has none (yet).
 GQ_DEV int lds_group(bt_lds &T, bool active, int32_t key, uint32_t &tag)
 {
-    uint32_t s = (static_cast<uint32_t>(key) * 0x9E3779B1u) >> (32 - 10);
+    uint32_t s = gq_slot_hash(static_cast<uint32_t>(key), 0) >> (32 - 10);
     static_assert(BT_LDS_GROUP_SLOTS == 1 << 10, "home slots are 10 hash bits");
     const unsigned long long want = static_cast<unsigned long long>(static_cast<uint32_t>(key)) << 32;
     int probes = 0, found = -1;
