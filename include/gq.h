@@ -324,7 +324,7 @@ gq_status gq_groupby_agg(gq_ctx *ctx, const gq_groupby_in *in, int64_t max_group
  * the local half of an ORDER BY ... LIMIT k before such a gather.
  * ------------------------------------------------------------------------ */
 
-/* Workspace for top-k over at most n rows. */
+/* Workspace for top-k of at most k keys over at most n rows. */
 size_t gq_topk_workspace_bytes(int64_t n, int k);
 
 /* The k selected rows with the largest (descending=1) or smallest

@@ -562,7 +562,12 @@ size_t gq_topk_workspace_bytes(int64_t n, int k)
     if (k < 1) k = 1;
     gq_carver c(nullptr);
     tk_layout(c, n, k);
-    return c.bytes();
+    if (k <= TK_PLAIN_K) return c.bytes();
+    // a workspace made for k keys serves smaller answers too (above TK_PLAIN_K
+    // more candidates are merged at once, without lists of a second level)
+    gq_carver p(nullptr);
+    tk_layout(p, n, TK_PLAIN_K);
+    return c.bytes() > p.bytes() ? c.bytes() : p.bytes();
 }
 
 gq_status gq_topk(gq_ctx *ctx, const int64_t *val, const int32_t *sel, int64_t n, const int64_t *n_dev, int k,

@@ -33,3 +33,14 @@ def test_workspace_grows_with_rows(what):
                  "groupby": lambda: L.gq_groupby_workspace_bytes(n, arg[0], arg[1], arg[2])}[what]()
             assert b >= last, (what, arg, n)
             last = b
+
+
+def test_topk_workspace_grows_with_k():
+    """One made for k keys serves smaller answers over the same rows."""
+    L = gq.lib()
+    for n in sizes():
+        last = 0
+        for k in [1, 2, 16, 64, 100, 128, 200, 255, 256, 257, 258, 300, 511, 512, 513, 1000, 1024, 1025, 2047, 2048]:
+            b = L.gq_topk_workspace_bytes(n, k)
+            assert b >= last, (n, k)
+            last = b
