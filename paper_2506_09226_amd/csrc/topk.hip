@@ -507,16 +507,27 @@ __global__ __launch_bounds__(TK_THREADS) void topk_merge_kernel(tk_lists in, int
 
 // Candidates that one workgroup merges alone, and lists per workgroup of a
 // first merge level otherwise (k = 100, 128 lists: 33 us at 16, 36 at 32, 41 at
-// 48; k = 1000 of 50M rows, whose lists come with bounds: 143 us at 2, 145 at 4,
-// 150 at 8, 157 at 16; k = 2000 of 8M: 125, 132, 137).
+// 48).  Lists with bounds are merged in pairs where the bounds leave about 2 k
+// keys (k = 1000 of 50M rows in no order: 158 us in pairs, 161 by three).  In a
+// sorted column, or one with many ties, half the lists or all of them pass the
+// bound, and the last merge, alone on the chip, walks their keys; so a group
+// takes as many lists as leave it TK_LAST_MERGE of them at most (50M rows in
+// pairs, and so: k = 1000 of a rising column 1131 and 936 us, its last rows
+// first, 252 and 214, its first rows; k = 2048 of equal values 456 and 282).
 int64_t tk_one_merge(int k) { return k <= TK_PLAIN_K ? 8192 : 32768; }
-int tk_merge_per(int k) { return k <= TK_PLAIN_K ? 16 : 2; }
+constexpr int64_t TK_LAST_MERGE = 3 << 16;
+int tk_merge_per(int64_t lists, int k)
+{
+    if (k <= TK_PLAIN_K) return 16;
+    const int64_t per = (lists * k + TK_LAST_MERGE - 1) / TK_LAST_MERGE;
+    return per > 2 ? static_cast<int>(per) : 2;
+}
 constexpr int TK_MAX_LISTS = 512;                     // two scan workgroups per CU
 static_assert(TK_MAX_LISTS <= TK_THREADS, "a merge holds one list per thread");
 
 struct tk_ws {
     tk_lists first, second;
-    int blocks, groups;
+    int blocks, groups, per;            // lists, groups of `per` lists in the first merge level (0: one merge)
     int64_t chunk;
 };
 
@@ -544,11 +555,13 @@ tk_ws tk_layout(gq_carver &c, int64_t n, int k)
     chunk = ((chunk + TK_STEP - 1) / TK_STEP) * TK_STEP;
     if (chunk < TK_STEP) chunk = TK_STEP;
     w.blocks = static_cast<int>(blocks);
-    const int per = tk_merge_per(k);
-    w.groups = blocks * k > tk_one_merge(k) ? static_cast<int>((blocks + per - 1) / per) : 0;
+    w.per = tk_merge_per(blocks, k);
+    w.groups = blocks * k > tk_one_merge(k) ? static_cast<int>((blocks + w.per - 1) / w.per) : 0;
     w.chunk = chunk;
     w.first = tk_take_lists(c, blocks, k);
-    if (w.groups > 0) w.second = tk_take_lists(c, w.groups, k);
+    // (room for the groups of the fewest lists, so that the size grows with n)
+    const int fewest = tk_merge_per(1, k);
+    if (w.groups > 0) w.second = tk_take_lists(c, (blocks + fewest - 1) / fewest, k);
     return w;
 }
 
@@ -595,7 +608,7 @@ gq_status gq_topk(gq_ctx *ctx, const int64_t *val, const int32_t *sel, int64_t n
                          w.blocks, w.blocks, k, need1, 0u, tk_lists{}, d, val_out, rowid_out, n_out_dev);
     const uint32_t need2 = tk_need(k, w.groups);
     GQ_TRY(gq_launch(ctx, "gq_topk_merge", topk_merge_kernel<false>, dim3(static_cast<uint32_t>(w.groups)),
-                     dim3(TK_THREADS), 0, s, w.first, w.blocks, tk_merge_per(k), k, need1, need2, w.second, d, val_out,
+                     dim3(TK_THREADS), 0, s, w.first, w.blocks, w.per, k, need1, need2, w.second, d, val_out,
                      rowid_out, n_out_dev));
     return gq_launch(ctx, "gq_topk_merge", topk_merge_kernel<true>, dim3(1), dim3(TK_THREADS), 0, s, w.second,
                      w.groups, w.groups, k, need2, 0u, tk_lists{}, d, val_out, rowid_out, n_out_dev);
