@@ -20,9 +20,9 @@ gq_status gq_partition_bits(gq_ctx *ctx, const int64_t *key, int64_t n, int log2
 // (start[P] = total), and start64, if given, the same as int64.  P <= 1024.
 // ws: gq_tile_offsets_workspace(ntiles, P).
 size_t gq_tile_offsets_workspace(int64_t ntiles, int P);
-// Optional: only the first ceil(min(*n_dev, n_bound) / tile_rows) of the
-// ntiles tiles hold counts (the rows arrive as a device count); the rest are
-// neither read nor written.
+// Optional: only the first ceil(rows / tile_rows) of the ntiles tiles hold
+// counts, rows being n_bound, or min(*n_dev, n_bound) when the rows arrive as a
+// device count; the rest are neither read nor written.
 struct gq_tile_count {
     const int64_t *n_dev;
     int64_t n_bound;

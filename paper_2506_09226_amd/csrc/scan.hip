@@ -43,12 +43,15 @@ int64_t to_chunk_tiles(int64_t ntiles)
     return c;
 }
 
-// Tiles that hold counts: all ntiles, or those the device row count reaches.
+// Tiles that hold counts: those that the row count (the bound, or the device
+// count within it) reaches; none of an empty input, whose one tile is not counted.
 GQ_DEV int64_t to_live_tiles(int64_t ntiles, gq_tile_count live)
 {
-    if (!live.n_dev) return ntiles;
-    int64_t n = *live.n_dev;
-    n = n < 0 ? 0 : (n < live.n_bound ? n : live.n_bound);
+    int64_t n = live.n_bound;
+    if (live.n_dev) {
+        const int64_t d = *live.n_dev;
+        n = d < 0 ? 0 : (d < n ? d : n);
+    }
     const int64_t t = (n + live.tile_rows - 1) / live.tile_rows;
     return t < ntiles ? t : ntiles;
 }
@@ -190,7 +193,7 @@ size_t gq_tile_offsets_workspace(int64_t ntiles, int P)
 gq_status gq_tile_offsets(gq_ctx *ctx, uint32_t *cnt, int64_t ntiles, int P, uint32_t *start, void *ws,
                           hipStream_t s, const char *name, const gq_tile_count *live, int64_t *start64)
 {
-    const gq_tile_count lv = live ? *live : gq_tile_count{nullptr, 0, 1};
+    const gq_tile_count lv = live ? *live : gq_tile_count{nullptr, ntiles, 1};
     if (live && live->tile_rows < 1) return gq_fail(ctx, GQ_ERR_INVALID_ARG, "gq_tile_offsets: bad tile rows");
     if (P < 1 || P > TO_MAX_P || ntiles < 1) return gq_fail(ctx, GQ_ERR_INVALID_ARG, "gq_tile_offsets: bad shape");
     gq_carver c(ws);

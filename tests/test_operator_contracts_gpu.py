@@ -144,3 +144,24 @@ def test_small_groupby_of_structured_keys(ctx, n, kind):
     for f in ("key64", "key32", "count", "sum_qty", "sum_rev_lo", "sum_rev_hi"):
         if g[f] is not None:
             assert np.array_equal(g[f][order], exp[f]), f
+
+
+# no rows, on every path (few groups, buckets, two levels), in a workspace that
+# holds anything
+@pytest.mark.parametrize("max_groups", [64, 5000, 2_000_000])
+@pytest.mark.parametrize("kind", ["key32", "key64", "both", "none"])
+@pytest.mark.parametrize("counted", [False, True])
+def test_groupby_of_no_rows(ctx, max_groups, kind, counted):
+    n = 1000 if counted else 0
+    e = torch.zeros(1000, dtype=torch.int64, device="cuda")
+    k64 = e if kind in ("key64", "both") else None
+    k32 = e.int() if kind in ("key32", "both") else None
+    has64, has32 = kind in ("key64", "both"), kind in ("key32", "both")
+    out = gq.alloc_groups(ctx, max_groups, has64, has32)
+    out.n_groups.fill_(7)
+    need = gq.lib().gq_groupby_workspace_bytes(n, max_groups, int(has64), int(has32))
+    ws = torch.full((need,), 0x5A, dtype=torch.uint8, device="cuda")
+    zero = torch.zeros(1, dtype=torch.int64, device="cuda") if counted else None
+    gq.gq_groupby_agg(ctx, e, e, e, n=n, n_dev=zero, key64=k64, key32=k32, max_groups=max_groups, out=out, ws=ws)
+    assert ctx.status() == gq.GQ_OK
+    assert int(out.n_groups.item()) == 0
