@@ -182,11 +182,16 @@ __global__ __launch_bounds__(FT_THREADS) void filter_kernel(const T *__restrict_
 }
 
 // Small inputs, bound by latency: one launch with no scratch to clear and no
-// waiting (64K rows: 16.5 -> 8.6 us a call, of which the host's share is about
-// 8; with 4-byte loads 11.7).  Workgroup t counts the matches of all rows before its own 1024
-// itself, which for up to FT_TINY_ROWS rows is a few loads per thread.
-constexpr int64_t FT_TINY_ROWS = 1 << 16;
-constexpr int64_t FT_TINY_SEL_ROWS = 1 << 15;       // (two dependent loads per row with a selection)
+// waiting (64K rows: 16.4 -> 5.7 us a call; with 4-byte loads 3 more).
+// Workgroup t counts the matches of all rows before its own 1024 itself, so the
+// line lies where the last one's reads take as long as the second launch and the
+// look-back: one-launch and look-back form, us a call, 4-byte rows 5.7 and 8.9 at
+// 64K, 7.3 and 8.9 at 128K, 9.6 and 9.7 at 192K; 8-byte rows 6.5 and 8.9 at 64K,
+// 8.3 and 8.9 at 96K, 10.1 and 8.9 at 128K.  A selection's rows take two
+// dependent loads, in no order: 6.0 and 8.9 at 8K, 7.3 and 8.8 at 16K, 8.9 and
+// 8.9 at 20K, 13.5 and 8.9 at 32K.
+constexpr int64_t FT_TINY_BYTES = 1 << 19;          // of the column
+constexpr int64_t FT_TINY_SEL_ROWS = 1 << 14;
 
 template <typename T, bool HAS_SEL>
 __global__ __launch_bounds__(FT_THREADS) void filter_tiny_kernel(const T *__restrict__ col,
@@ -264,7 +269,7 @@ gq_status launch_filter(gq_ctx *ctx, const void *col, const int32_t *sel_in, int
     // (a count or a selection that is narrowed in place needs the look-back:
     // a unit writes after every earlier one has read its own)
     const bool in_place = S && out == sel_in;
-    if (n <= (S ? FT_TINY_SEL_ROWS : FT_TINY_ROWS) && n_out != n_dev && !in_place) {
+    if (n <= (S ? FT_TINY_SEL_ROWS : FT_TINY_BYTES / int64_t(sizeof(T))) && n_out != n_dev && !in_place) {
         const uint32_t grid = static_cast<uint32_t>(n > 0 ? (n + FT_THREADS - 1) / FT_THREADS : 1);
         return gq_launch(ctx, "gq_filter", filter_tiny_kernel<T, S>, dim3(grid), dim3(FT_THREADS), 0, s, c, sel_in, n,
                          n_dev, lo, hi, reinterpret_cast<uintptr_t>(col) % 16 == 0 ? 1 : 0, out, n_out);

@@ -165,3 +165,16 @@ def test_groupby_of_no_rows(ctx, max_groups, kind, counted):
     gq.gq_groupby_agg(ctx, e, e, e, n=n, n_dev=zero, key64=k64, key32=k32, max_groups=max_groups, out=out, ws=ws)
     assert ctx.status() == gq.GQ_OK
     assert int(out.n_groups.item()) == 0
+
+
+# both sides of the line between the filter's one-launch and look-back forms
+@pytest.mark.parametrize("dtype,n,with_sel", [(np.int32, 131_072, False), (np.int32, 131_073, False),
+                                              (np.int64, 65_536, False), (np.int64, 65_537, False),
+                                              (np.int32, 16_384, True), (np.int64, 16_385, True)])
+def test_filter_forms_meet(ctx, dtype, n, with_sel):
+    r = np.random.default_rng(n)
+    col = r.integers(-50, 50, size=n).astype(dtype)
+    sel = r.permutation(n).astype(np.int32) if with_sel else None
+    exp = oracle.filter(col, -20, 30, sel_in=sel)
+    out, cnt = gq.gq_filter(ctx, dev(col), -20, 30, sel_in=None if sel is None else dev(sel))
+    assert int(cnt.item()) == len(exp) and np.array_equal(out[:len(exp)].cpu().numpy(), exp)
