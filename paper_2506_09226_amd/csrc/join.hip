@@ -641,9 +641,9 @@ probe_ws probe_layout(gq_carver &c, int64_t n)
 // AHEAD: slots that a walk on from the home slot reads in one trip.  A call of
 // few rows is one unit per workgroup and bound by its longest walks, a chain
 // of trips to the L2; a call of many is bound by the lines themselves, and
-// slots read too far cost more (12M rows of a 50K-key table 174 us at 1, 190
-// at 4; 1M rows and 64K keys 31 and 30, the pipeline around it 167 and 163.5;
-// 200K rows 35.5 and 33).
+// slots read too far cost more.  At 1 and at 4, us: 500K keys, 400K rows 19.5
+// and 17.2, 2^20 rows 31.3 and 28.1, 1.5M 42.6 and 43.8, 3M 69 and 75; 50K keys,
+// 200K rows 11.9 and 11.4, 2^20 22.1 and 21.5, 1.5M 32.6 and 34.5, 12M 159 and 173.
 //
 // IN_PLACE: prow_out is the selection itself.  A unit's outputs lie at its own
 // or earlier rows, and every earlier unit has read its rows before it publishes

@@ -112,8 +112,13 @@ struct gq_server {
     int64_t n_done = 0, n_batches = 0, max_seen = 0, n_reruns = 0;
 
     // A shared scan pays for itself only from a few queries of one template
-    // on (measured on MI355X over 1.6 billion rows): with fewer queued, the
-    // head query runs alone as the plain operator chain.
+    // on: with fewer queued, the head query runs alone as the plain operator
+    // chain.  400M rows, shared and one by one, ms: filter-aggregates that keep
+    // 1% to 60% of the rows, 2: 4.6 and 3.8, 3: 4.7 and 5.6, 4: 4.8 and 7.4, and
+    // that keep 5%, 3: 4.3 and 3.7, 4: 4.4 and 4.9; two-join aggregates, 2: 19.3
+    // and 18.5, 3: 19.8 and 27.7, 4: 20.1 and 36.7, that keep 5%, 3: 11.1 and
+    // 10.2, 4: 11.2 and 13.5; one-join aggregates over 1M groups, 2: 13.4 and
+    // 14.8, that keep 5%, 2: 4.1 and 5.6.  (40M rows: the same lines.)
     static int min_shared(int kind)
     {
         switch (kind) {
