@@ -1173,6 +1173,18 @@ std::vector<gq_tuning> axis_points(const gq_tuning &base, int axis)
 }
 constexpr int TUNE_AXES = 5;
 
+// Whether this axis changes anything: the lag orders the queue's builds, of
+// which a batch built by regions has none, and the build tile cuts those by
+// device compare-and-swap, of tables between the LDS and the region builds.
+bool axis_matters(const gq_instance *in, int n, const gq_tuning &t, int axis)
+{
+    if (axis != 2 && axis != 4) return true;
+    const bt_plan pl = make_plan(in, n, t, nullptr);
+    for (const bt_seg &sg : pl.segs)
+        if (sg.kind == K_BUILD || (axis == 2 && sg.kind != K_PROBE)) return true;
+    return false;
+}
+
 bool cache_lookup(const char *path, uint64_t sig, gq_tuning *t, double *ms)
 {
     if (!path) return false;
@@ -1257,6 +1269,7 @@ gq_status gq_batch_autotune(gq_ctx *ctx, const gq_instance *inst, int n_inst, co
         bool moved = false;
         for (int axis = 0; axis < TUNE_AXES && rc == GQ_OK; ++axis) {
             const gq_tuning from = bt;
+            if (!axis_matters(inst, n_inst, from, axis)) continue;
             for (const gq_tuning &t : axis_points(from, axis)) {
                 if (same_tuning(t, from)) continue;
                 double ms = 0.0;

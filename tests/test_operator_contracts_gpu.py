@@ -178,3 +178,24 @@ def test_filter_forms_meet(ctx, dtype, n, with_sel):
     exp = oracle.filter(col, -20, 30, sel_in=sel)
     out, cnt = gq.gq_filter(ctx, dev(col), -20, 30, sel_in=None if sel is None else dev(sel))
     assert int(cnt.item()) == len(exp) and np.array_equal(out[:len(exp)].cpu().numpy(), exp)
+
+
+def batch_of(r, sizes):
+    specs = []
+    for m, n in sizes:
+        key = r.permutation(np.arange(m) * 7919).astype(np.int64)
+        specs.append({"dim_key": dev(key), "dim_attr": dev(r.integers(0, 20, size=m).astype(np.int32)),
+                      "fk": dev(key[r.integers(0, m, size=n)]), "date": dev(r.integers(0, 100, size=n).astype(np.int32)),
+                      "qty": dev(r.integers(1, 50, size=n)), "price": dev(r.integers(0, 10_000_000, size=n)),
+                      "disc": dev(r.integers(0, 11, size=n)), "date_lo": 0, "date_hi": 60})
+    return specs
+
+
+def test_autotune_leaves_what_changes_nothing(ctx):
+    """Tables that are built by regions at every load factor leave no builds in
+    the queue: lag and build tile stay at the search's starting point."""
+    specs = [dict(s, out=gq.alloc_groups(ctx, 64, False, True))
+             for s in batch_of(np.random.default_rng(1), [(40_000, 60_000), (50_000, 40_001)])]
+    best, ms = gq.gq_batch_autotune(ctx, gq.make_instances(specs))
+    assert ctx.status() == gq.GQ_OK
+    assert ms > 0 and (best.lag, best.build_tile) == (4, gq.gq_default_tuning().build_tile)
