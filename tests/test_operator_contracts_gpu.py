@@ -199,3 +199,16 @@ def test_autotune_leaves_what_changes_nothing(ctx):
     best, ms = gq.gq_batch_autotune(ctx, gq.make_instances(specs))
     assert ctx.status() == gq.GQ_OK
     assert ms > 0 and (best.lag, best.build_tile) == (4, gq.gq_default_tuning().build_tile)
+
+
+# the library's scratch after a larger call: both later ones use it too
+@pytest.mark.parametrize("dtype", [np.int32, np.int64])
+def test_noalloc_clears_its_scratch(ctx, dtype):
+    r = np.random.default_rng(17)
+    for n in (3_000_001, 200_001, 140_000, 3_000_001):
+        col = r.integers(0, 2557, size=n).astype(dtype)
+        out = torch.empty(n, dtype=torch.int32, device="cuda")
+        cnt = torch.zeros(1, dtype=torch.int64, device="cuda")
+        gq.gq_filter_noalloc(ctx, dev(col), 100, 900, out, cnt)
+        exp = oracle.filter(col, 100, 900)
+        assert int(cnt.item()) == len(exp) and np.array_equal(out[:len(exp)].cpu().numpy(), exp)
