@@ -93,13 +93,14 @@ GQ_DEV uint32_t load_acquire(const uint32_t *p)
 
 // Wait until *ctr >= target, for at most `limit` polls (each after a short
 // sleep): relaxed polls, then one acquire.  An acquire invalidates cache lines
-// that the running probes use, and a release writes the L2 back: with one per
-// poll, and a fence beside every count, 48 instances of 1K to 100K keys took
-// 1.91 ms against 0.73.  Returns false, in every thread, when the bound ran out: the
-// caller then skips its work (its inputs are incomplete) and reports
-// GQ_ERR_TIMEOUT, so the kernel still drains its queue and exits.  Every
-// wait here is for items dequeued earlier, so the bound is only reached
-// through a bug, or when the host sets a tiny bound to test this path.
+// that the running probes use, and a release writes the L2 back: with an
+// acquire per poll and a fence beside every count, 48 instances of 1K to 100K
+// keys take 1212 us, 617 so, and 64 of 1K to 2M 5.32 ms, 4.64 so.  Returns false, in
+// every thread, when the bound ran out: the caller then skips its work (its
+// inputs are incomplete) and reports GQ_ERR_TIMEOUT, so the kernel still drains
+// its queue and exits.  Every wait here is for items dequeued earlier, so the
+// bound is only reached through a bug, or when the host sets a tiny bound to
+// test this path.
 GQ_DEV bool wait_for(const uint32_t *ctr, uint32_t target, int64_t limit, uint32_t *s_ok)
 {
     if (threadIdx.x == 0) {
@@ -422,15 +423,15 @@ __device__ void item_build(const bt_inst &I, int64_t tile, int build_tile, uint3
 }
 
 // Fused filter -> probe -> aggregate over one tile of fact rows, walked in
-// chunks of 8 rows per thread; groups accumulate in LDS for the whole tile
-// and are merged into the instance's global group table at its end.  Each
-// chunk runs in phases over its 8 rows (dates; foreign keys of the kept
+// chunks of BT_CHUNK_ITEMS rows per thread; groups accumulate in LDS for the
+// whole tile and are merged into the instance's global group table at its end.
+// Each chunk runs in phases over its rows (dates; foreign keys of the kept
 // rows; table slots; value columns of the matches; LDS aggregation), so a
 // phase's loads are all in flight together.
 constexpr int BT_CHUNK_ITEMS = 4;
 constexpr int BT_CHUNK = BT_THREADS * BT_CHUNK_ITEMS;
 constexpr int BT_MIN_TILE = 2 * BT_CHUNK;      // the finest probe tile a batch is cut into
-constexpr int64_t BT_GRID = 768;               // three workgroups on each of 256 CUs
+constexpr int64_t BT_GRID = 768;               // probe tiles that keep the chip busy (512 and 1536: the same)
 
 __device__ void item_probe(const bt_inst &I, int64_t tile, int tile_rows, bt_lds &T, uint32_t *status)
 {
@@ -1086,7 +1087,8 @@ gq_status gq_batch_join_agg(gq_ctx *ctx, const gq_instance *inst, int n_inst, co
                          static_cast<const uint32_t *>(ovf_cnt), ctx->status_dev));
     }
     if (pl.total_items > 0) {
-        // three 51 KiB-LDS workgroups fit a CU by LDS, two by registers
+        // three workgroups per CU: two are resident (107 registers; 51 KiB of
+        // LDS would let three), the rest start as those run out of items
         const uint32_t grid = static_cast<uint32_t>(std::min<int64_t>(pl.total_items, int64_t(ctx->num_cus) * 3));
         const int nsegs = static_cast<int>(pl.segs.size());
         GQ_TRY(gq_launch(ctx, "gq_batch", batch_kernel, dim3(grid), dim3(BT_THREADS), 0, s,

@@ -269,7 +269,7 @@ GQ_DEV uint64_t tk_order(int64_t v, bool desc)
 // Up to this k the merges take every candidate: recording and ranking the
 // lists' bounds costs more than it saves (128 lists of 100 keys: 33 us in two
 // merges, 39 us in one with bounds, and 5 us more in the scan).  At k = 1000
-// and 512 lists the merges took 126 us without bounds and take 66 with them.
+// and 512 lists the merges took 126 us without bounds and take 56 with them.
 constexpr int TK_PLAIN_K = 256;
 
 // Candidate lists: list i holds cnt[i] <= k keys from i * k, and a bound that

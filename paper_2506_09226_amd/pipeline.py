@@ -5,9 +5,10 @@
     ->  float64 averages  [->  top-k of price over the selection]
 
 The probe is gq_join_probe, or gq_join_probe_partitioned, which also checks
-the table's size; both give the same output.  "auto" takes the partitioned
-form when the fact table was radix-partitioned, "tune" times both on the first
-step's data (HIP events, one host wait) and keeps the faster.
+the table's size; both run the same kernel and give the same output.  "auto"
+takes the partitioned form when the fact table was radix-partitioned.  "tune"
+times both on the first step's data (HIP events, one host wait) and keeps the
+faster, for programs that read those times; it can gain only the noise.
 
 All buffers and workspaces are allocated once, so a step allocates nothing and
 never waits for the host: every count travels on the device.
@@ -64,10 +65,7 @@ class PlainPipeline:
             raise ValueError(f"probe must be auto, tune, ordered or partitioned, not {probe!r}")
         self.probe = probe
         self.probe_ms = None                     # with "tune": each form's time on the first step
-        self.ws_probe = {}
-        for form in (("ordered", "partitioned") if probe == "tune" else (probe,)):
-            self.ws_probe[form] = ctx.workspace(L.gq_join_probe_partitioned_workspace_bytes(n)
-                                                if form == "partitioned" else L.gq_join_probe_workspace_bytes(n))
+        self.ws_probe = ctx.workspace(L.gq_join_probe_workspace_bytes(n))       # (of either form)
         self.groups = alloc_groups(ctx, max_groups, False, True)
         self.ws_gb = ctx.workspace(L.gq_groupby_workspace_bytes(n, max_groups, 0, 1))
         if topk:
@@ -96,10 +94,10 @@ class PlainPipeline:
         if form == "partitioned":
             gq_join_probe_partitioned(ctx, self.table, fk, sel=self.sel, n=self.n, n_dev=self.n_sel,
                                       log2_fanout=self.log2p if self.partition else 0, prow=self.prow,
-                                      payload=self.pay, n_out=self.n_join, ws=self.ws_probe[form])
+                                      payload=self.pay, n_out=self.n_join, ws=self.ws_probe)
         else:
             gq_join_probe(ctx, self.table, fk, sel=self.sel, n=self.n, n_dev=self.n_sel, prow=self.prow,
-                          payload=self.pay, n_out=self.n_join, ws=self.ws_probe[form])
+                          payload=self.pay, n_out=self.n_join, ws=self.ws_probe)
 
     def _tune_probe(self, fk, stream):
         """Run both probe forms (same output), time each, keep the faster."""
