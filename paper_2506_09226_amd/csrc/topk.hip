@@ -29,7 +29,7 @@ constexpr int TK_CAP = 4096;                          // LDS candidates
 constexpr int TK_MAX_K = TK_CAP - TK_STEP;            // 2048
 constexpr uint64_t TK_SIGN = 0x8000000000000000ull;
 constexpr uint32_t TK_RANKED = 256;                   // keys of an answer that are ranked by counting
-static_assert(TK_RANKED <= TK_THREADS, "one key per thread");
+static_assert(TK_RANKED <= TK_THREADS && TK_RANKED <= 256, "one key per thread, one counter per place");
 
 struct tk_entry {
     uint64_t ok;
@@ -214,33 +214,44 @@ GQ_DEV void tk_select(tk_lds &L, int k)
     uint32_t rk[TK_PER];
     const uint32_t valid = tk_entries(L, ok, rk);
     const tk_prefix x = tk_digits(L, ok, rk, valid, static_cast<uint32_t>(k));
-    // better entries first, then those that carry the chosen digits, as many as
-    // fit (all of them, unless they are equal); both counts in one scan
-    uint32_t above = 0, equal = 0;                    // one bit per entry
+    bool kp[TK_PER];
+    uint32_t keep = 0;
 #pragma unroll
     for (int i = 0; i < TK_PER; ++i) {
         const uint64_t a = ok[i] & x.m_ok;
         const uint32_t b = rk[i] & x.m_rk;
-        above |= a > x.p_ok || (a == x.p_ok && b > x.p_rk) ? 1u << i : 0u;
-        equal |= a == x.p_ok && b == x.p_rk ? 1u << i : 0u;
+        kp[i] = ((valid >> i) & 1u) && (a > x.p_ok || (a == x.p_ok && b >= x.p_rk));
+        keep += kp[i] ? 1u : 0u;
     }
-    above &= valid;
-    equal &= valid;
-    static_assert(TK_CAP < 1 << 16, "two counts in a word");
     uint32_t total;
-    const uint32_t pre = gq_block_exclusive_scan_lds<TK_THREADS>(
-        static_cast<uint32_t>(__popc(equal)) << 16 | static_cast<uint32_t>(__popc(above)), &total, L.scan);
-    uint32_t at = pre & 0xffffu, at_eq = (total & 0xffffu) + (pre >> 16);
+    uint32_t pos = gq_block_exclusive_scan_lds<TK_THREADS>(keep, &total, L.scan);
+    // equal keys at the k-th place: those past the k best go behind them, where
+    // the next candidates overwrite them
+    const bool tie = total > static_cast<uint32_t>(k);
+    if (__builtin_expect(tie, 0)) {
+        uint32_t eq = 0, all;
 #pragma unroll
-    for (int i = 0; i < TK_PER; ++i) {
-        const bool eq = (equal >> i) & 1u;
-        const uint32_t pos = eq ? at_eq : at;
-        if ((((above | equal) >> i) & 1u) && pos < static_cast<uint32_t>(k)) {
-            L.ok[pos] = ok[i];
-            L.rk[pos] = rk[i];
+        for (int i = 0; i < TK_PER; ++i) eq += kp[i] && ok[i] == x.p_ok && rk[i] == x.p_rk ? 1u : 0u;
+        const uint32_t r = gq_block_exclusive_scan_lds<TK_THREADS>(eq, &all, L.scan);
+        uint32_t better = pos - r, last = total - all + r;         // places of this thread's better and equal keys
+#pragma unroll
+        for (int i = 0; i < TK_PER; ++i) {
+            if (kp[i]) {
+                const bool e = ok[i] == x.p_ok && rk[i] == x.p_rk;
+                const uint32_t at = e ? last++ : better++;
+                L.ok[at] = ok[i];
+                L.rk[at] = rk[i];
+            }
         }
-        at += (above >> i) & 1u;
-        at_eq += eq ? 1u : 0u;
+    } else {
+#pragma unroll
+        for (int i = 0; i < TK_PER; ++i) {
+            if (kp[i]) {
+                L.ok[pos] = ok[i];
+                L.rk[pos] = rk[i];
+                ++pos;
+            }
+        }
     }
     if (threadIdx.x == 0) {
         L.count = static_cast<uint32_t>(k);
@@ -482,20 +493,18 @@ __global__ __launch_bounds__(TK_THREADS) void topk_merge_kernel(tk_lists in, int
             rowid_out[at] = static_cast<int32_t>(0x7fffffffu - r);
         };
         if (cnt <= TK_RANKED) {
-            // a few keys: each thread counts those better than its own, and
-            // equal ones before it, with no barrier, where a sort has one for
-            // each of its log2(cnt)^2 / 2 stages (k = 100 of 3M rows 37.5 ->
-            // 34.2 us, k = 10 of 200K rows 21.9 -> 17.9)
+            // a few keys: each thread counts those better than its own, with no
+            // barrier in between, where a sort has one for each of its
+            // log2(cnt)^2 / 2 stages (k = 100 of 3M rows 37.5 -> 34.2 us, k = 10
+            // of 200K rows 21.9 -> 17.9); equal ones take the places from there on
+            if (tid < static_cast<int>(TK_RANKED)) L.hist[0][tid] = 0;
+            gq_lds_barrier();
             if (tid < static_cast<int>(cnt)) {
                 const uint64_t o = L.ok[tid];
                 const uint32_t r = L.rk[tid];
                 uint32_t at = 0;
-                for (uint32_t j = 0; j < cnt; ++j) {
-                    const uint64_t jo = L.ok[j];
-                    const uint32_t jr = L.rk[j];
-                    at += tk_better(jo, jr, o, r) || (jo == o && jr == r && j < static_cast<uint32_t>(tid)) ? 1u : 0u;
-                }
-                put(at, o, r);
+                for (uint32_t j = 0; j < cnt; ++j) at += tk_better(L.ok[j], L.rk[j], o, r) ? 1u : 0u;
+                put(at + atomicAdd(&L.hist[0][at], 1u), o, r);
             }
         } else {
             tk_sort_count(L);                                      // the answer, best first
