@@ -4,9 +4,9 @@
 // one dequeue; each wave owns a contiguous stretch of the unit and tests it 64
 // rows at a time, keeping the ballot of step i in lane i.  The unit's match
 // count goes through a decoupled look-back over units, which gives its global
-// offset; each wave then writes its matching row ids step by step, at its
-// offset plus the ballot's lane prefix, so neither bits nor row ids pass
-// through LDS.  Small inputs skip the look-back (filter_tiny_kernel).
+// offset; each wave then writes its matching row ids there, through an LDS stage
+// of its own or, if most of its rows match, step by step at its offset plus the
+// ballot's lane prefix.  Small inputs skip the look-back (filter_tiny_kernel).
 #include <algorithm>
 #include <limits>
 #include <type_traits>
@@ -14,16 +14,22 @@
 #include "gq_device.h"
 #include "gq_internal.h"
 
+// v_writelane_b32 (clang has no builtin for it): `old` with one lane's value
+// replaced.  value and lane are the same in every lane.
+extern "C" __device__ int gq_writelane(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
+
 namespace {
 
 // Bound by memory: 4 (or 8) bytes a row in, 4 bytes a match out.  1024-thread
-// workgroups at 32 registers put 32 waves on a CU.  A unit is up to 32 steps
+// workgroups at 38 registers put 32 waves on a CU.  A unit is up to 32 steps
 // of its 16 waves (32K rows): each unit costs a dequeue (atomics on one
 // address take turns at about 20 ns) and a look-back that reads words other
 // XCDs write; smaller inputs take fewer steps, for 128 to 256 units (3M rows:
-// 14.6 us at 128 units, 20.5 at 600).  200M rows, 58.7% kept: 0.31 ms, 4.1
-// TB/s, as the staged form it replaces; 25M gathered rows 81 -> 65 us; 1M rows
-// 16 -> 10 us.
+// 14.6 us at 128 units, 20.5 at 600).  A step is a load, two instructions of
+// test and two that put its ballot into lanes (with the ballot selected into
+// its lane, and every step written by itself, 200M 4-byte rows took 214, 245,
+// 265, 295 and 331 us at 0, 5, 30, 58 and 100% kept; so, 184, 198, 239, 289 and
+// 325: 4.3 TB/s read with nothing kept, 4.9 TB/s read and written with all).
 constexpr int FT_THREADS = 1024;
 constexpr int FT_WAVES = FT_THREADS / 64;
 constexpr int FT_MAX_STEPS = 32;                    // steps of a wave per unit (the ballots of 32 lanes)
@@ -36,6 +42,13 @@ int ft_steps(int64_t n)                             // a power of two: a wave's 
     while (steps < FT_MAX_STEPS && n >= 2 * steps * FT_THREADS * FT_UNITS) steps *= 2;
     return steps;
 }
+
+// A wave's matches go through LDS when the unit has FT_STAGE_STEPS steps or
+// more (fewer write so little that the detour costs 0.3 us of 9) and three
+// quarters or fewer of its rows match; the stage holds half of them (64 KB for
+// the largest unit, two workgroups a CU).
+constexpr int FT_STAGE_STEPS = 8;
+__host__ __device__ constexpr int ft_stage(int steps) { return steps >= FT_STAGE_STEPS ? steps * 32 : 0; }
 
 struct filter_ws {
     uint32_t *unit_ctr;
@@ -91,28 +104,30 @@ __global__ __launch_bounds__(FT_THREADS) void filter_kernel(const T *__restrict_
                                                             int64_t *n_out, uint32_t *unit_ctr, uint64_t *status)
 {
     static_assert(HAS_SEL || !IN_PLACE, "without a selection there is nothing to overwrite");
-    extern __shared__ int32_t held[];                       // IN_PLACE: the unit's row ids
+    extern __shared__ int32_t held[];                       // the waves' stages (IN_PLACE: the unit's row ids)
     __shared__ uint32_t wcnt[FT_WAVES];
     __shared__ uint32_t s_unit;
     __shared__ uint64_t s_goff;
     const ft_range<T> range(lo, hi);
     const int64_t n = ft_rows(n_bound, n_dev);
+    const int64_t unit = static_cast<int64_t>(FT_THREADS) * steps;
+    const int64_t nunits = (n + unit - 1) / unit;
+    if (static_cast<int64_t>(blockIdx.x) >= nunits) {       // as many workgroups take a unit as there are units
+        if (blockIdx.x == 0 && threadIdx.x == 0) *n_out = 0;
+        return;
+    }
     if (threadIdx.x == 0) s_unit = atomicAdd(unit_ctr, 1u);
     __syncthreads();
     const uint32_t u = s_unit;
-    const int64_t unit = static_cast<int64_t>(FT_THREADS) * steps;
-    const int64_t nunits = (n + unit - 1) / unit;
-    if (static_cast<int64_t>(u) >= nunits) {
-        if (u == 0 && threadIdx.x == 0) *n_out = 0;
-        return;
-    }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t row0 = static_cast<int64_t>(u) * unit + static_cast<int64_t>(wave) * steps * 64 + lane;
     constexpr int FT_BATCH = HAS_SEL ? 4 : 8;               // steps whose loads overlap (gathers: 64 us at 4, 85 at 8)
-    uint64_t word = 0;                                      // lane i: the matches of step i
-    // a unit whose rows all exist goes without a bound test for each (of 29
-    // vector instructions a step; 200M rows with 59% kept 311 -> 298 us, 100M with
-    // 5% kept 138 -> 132, 3M 13.3 -> 12.5)
+    uint32_t wlo = 0, whi = 0;                              // lane i: the matches of step i
+    auto keep = [&](uint64_t b, int i) {
+        wlo = static_cast<uint32_t>(gq_writelane(static_cast<int>(b), i, static_cast<int>(wlo)));
+        whi = static_cast<uint32_t>(gq_writelane(static_cast<int>(b >> 32), i, static_cast<int>(whi)));
+    };
+    // a unit whose rows all exist goes without a bound test for each
     const bool full = !HAS_SEL && static_cast<int64_t>(u + 1) * unit <= n && steps % FT_BATCH == 0;
     for (int i0 = 0; full && i0 < steps; i0 += FT_BATCH) {
         const T *at = col + row0 + i0 * 64;
@@ -120,10 +135,7 @@ __global__ __launch_bounds__(FT_THREADS) void filter_kernel(const T *__restrict_
 #pragma unroll
         for (int c = 0; c < FT_BATCH; ++c) v[c] = __builtin_nontemporal_load(at + c * 64);
 #pragma unroll
-        for (int c = 0; c < FT_BATCH; ++c) {
-            const uint64_t b = gq_ballot(range.test(v[c]));
-            if (lane == i0 + c) word = b;
-        }
+        for (int c = 0; c < FT_BATCH; ++c) keep(gq_ballot(range.test(v[c])), i0 + c);
     }
     for (int i0 = full ? steps : 0; i0 < steps; i0 += FT_BATCH) {
         T v[FT_BATCH];
@@ -144,11 +156,10 @@ __global__ __launch_bounds__(FT_THREADS) void filter_kernel(const T *__restrict_
 #pragma unroll
         for (int c = 0; c < FT_BATCH; ++c) {
             const int64_t e = row0 + (i0 + c) * 64;
-            const uint64_t b = gq_ballot(i0 + c < steps && e < n && range.test(v[c]));
-            if (lane == i0 + c) word = b;
+            keep(gq_ballot(i0 + c < steps && e < n && range.test(v[c])), i0 + c);
         }
     }
-    const uint32_t mine = static_cast<uint32_t>(__popcll(word));
+    const uint32_t mine = static_cast<uint32_t>(__popc(wlo) + __popc(whi));
     const uint32_t incl = gq_wave_inclusive_scan(mine);
     if (lane == 63) wcnt[wave] = incl;
     __syncthreads();
@@ -168,7 +179,39 @@ __global__ __launch_bounds__(FT_THREADS) void filter_kernel(const T *__restrict_
     __syncthreads();
     const uint32_t excl = before + incl - mine;             // lane i: matches of the unit before step i
     const int64_t goff = static_cast<int64_t>(s_goff);
-    const uint32_t wlo = static_cast<uint32_t>(word), whi = static_cast<uint32_t>(word >> 32);
+    const uint32_t found = __builtin_amdgcn_readlane(incl, 63);
+    if (!IN_PLACE && steps >= FT_STAGE_STEPS && found <= static_cast<uint32_t>(steps * 48)) {
+        // The wave's matches through its LDS stage, so that they leave it 64 at a
+        // time: lane l takes `per` consecutive rows, one match at a time; a wave
+        // with more matches than the stage holds takes two rounds.
+        const int cap = ft_stage(steps);
+        int32_t *stage = held + wave * cap;
+        const int per = found <= static_cast<uint32_t>(cap) ? steps : steps / 2;
+        uint32_t done = 0;
+        for (int r0 = 0; r0 < steps * 64; r0 += per * 64) {
+            const int pos = r0 + lane * per, sh = pos & 31;
+            const uint32_t lo32 = __shfl(wlo, pos >> 6, 64), hi32 = __shfl(whi, pos >> 6, 64);
+            const uint32_t below = (1u << sh) - 1u;
+            const bool upper = pos & 32;
+            uint32_t bits = (upper ? hi32 : lo32) >> sh;
+            if (per < 32) bits &= (1u << per) - 1u;
+            uint32_t at = __shfl(incl - mine, pos >> 6, 64) - done +
+                          (upper ? __popc(lo32) + __popc(hi32 & below) : __popc(lo32 & below));
+            const int64_t first = row0 - lane + pos;
+            while (bits) {
+                const int64_t e = first + __builtin_ctz(bits);
+                bits &= bits - 1;
+                stage[at++] = HAS_SEL ? sel_in[e] : static_cast<int32_t>(e);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            // (the place after the last lane's matches: the count of this round)
+            const uint32_t count = __builtin_amdgcn_readlane(at, 63);
+            for (uint32_t q = lane; q < count; q += 64) out[goff + before + done + q] = stage[q];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            done += count;
+        }
+        return;
+    }
     for (int i = 0; i < steps; ++i) {
         const uint32_t blo = __builtin_amdgcn_readlane(wlo, i), bhi = __builtin_amdgcn_readlane(whi, i);
         const uint64_t b = (static_cast<uint64_t>(bhi) << 32) | blo;
@@ -280,14 +323,14 @@ gq_status launch_filter(gq_ctx *ctx, const void *col, const int32_t *sel_in, int
     const int steps = ft_steps(n);
     const int64_t unit = static_cast<int64_t>(FT_THREADS) * steps;
     const dim3 grid(static_cast<uint32_t>(n > 0 ? (n + unit - 1) / unit : 1));
-    if constexpr (S) {
-        if (in_place)                                 // 128 KB of row ids at most
-            return gq_launch(ctx, "gq_filter", filter_kernel<T, true, true>, grid, dim3(FT_THREADS),
-                             static_cast<size_t>(unit) * sizeof(int32_t), s, c, sel_in, n, n_dev, lo, hi, steps, out,
-                             n_out, w.unit_ctr, w.status);
-    }
-    return gq_launch(ctx, "gq_filter", filter_kernel<T, S, false>, grid, dim3(FT_THREADS), 0, s, c, sel_in, n, n_dev,
-                     lo, hi, steps, out, n_out, w.unit_ctr, w.status);
+    auto launch = [&](auto kernel, int entries) {     // entries of LDS per wave
+        return gq_launch(ctx, "gq_filter", kernel, grid, dim3(FT_THREADS),
+                         static_cast<size_t>(FT_WAVES) * entries * sizeof(int32_t), s, c, sel_in, n, n_dev, lo, hi,
+                         steps, out, n_out, w.unit_ctr, w.status);
+    };
+    if constexpr (S)
+        if (in_place) return launch(filter_kernel<T, true, true>, steps * 64);
+    return launch(filter_kernel<T, S, false>, ft_stage(steps));
 }
 
 gq_status run_filter(gq_ctx *ctx, const void *col, int dtype, const int32_t *sel_in, int64_t n, const int64_t *n_dev,

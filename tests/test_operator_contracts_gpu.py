@@ -212,3 +212,24 @@ def test_noalloc_clears_its_scratch(ctx, dtype):
         gq.gq_filter_noalloc(ctx, dev(col), 100, 900, out, cnt)
         exp = oracle.filter(col, 100, 900)
         assert int(cnt.item()) == len(exp) and np.array_equal(out[:len(exp)].cpu().numpy(), exp)
+
+
+# waves whose matches go through the stage in one round and in two (up to half
+# and three quarters of their rows), and waves that write step by step; units
+# of 8, 16 and 32 steps; densities that change within a unit
+@pytest.mark.parametrize("n", [1_048_576, 2_097_152 + 77, 4_194_304 + 31 * 1024 + 5])
+@pytest.mark.parametrize("dtype", [np.int32, np.int64])
+@pytest.mark.parametrize("keep", [0.002, 0.25, 0.5, 0.74, 0.76, 1.0, None])
+def test_filter_stage(ctx, n, dtype, keep):
+    r = np.random.default_rng(n)
+    col = r.integers(0, 1000, size=n).astype(dtype)
+    if keep is None:                                           # another density every 512 rows
+        thr = np.repeat(r.integers(0, 1001, size=n // 512 + 1), 512)[:n]
+        col = np.where(col < thr, 0, 999).astype(dtype)
+    hi = 500 if keep is None else int(keep * 1000)
+    sel = r.permutation(n).astype(np.int32)[:n - 3] if keep in (0.25, 0.74) else None
+    exp = oracle.filter(col, 0, hi, sel_in=sel)
+    out = torch.full((n + 4096,), -1, dtype=torch.int32, device="cuda")
+    _, cnt = gq.gq_filter(ctx, dev(col), 0, hi, sel_in=None if sel is None else dev(sel), out=out)
+    assert int(cnt.item()) == len(exp) and np.array_equal(out[:len(exp)].cpu().numpy(), exp)
+    assert bool((out[len(exp):] == -1).all())
