@@ -46,6 +46,9 @@ constexpr int GS_IDS = 32;                           // groups of a workgroup wh
 constexpr int GS_COPIES = 32;                        // copies of their sums, one per lane of a half wave
 constexpr int GS_FOLD = 4;                           // partial groups per thread whose loads overlap in the final fold
 constexpr int64_t GS_MIN_ROWS = 8192;                // rows per workgroup below which none is added
+constexpr int64_t GS_FEW_GROUPS = 64;                // bound up to which workgroups take fewer:
+constexpr int64_t GS_FEW_ROWS = 2048;                //   this many, while half the chip is idle
+constexpr int64_t GS_TILE = 64 * GS_SPAN * GS_WAVES; // rows of the filter column a workgroup takes at a time
 constexpr int GB_BUCKET_THREADS = 1024;
 constexpr int GB_LDS_PROBES = 64;
 
@@ -500,9 +503,11 @@ struct gb_part {
 // 60M rows by a date filter into 11 groups: 687 -> 316 us (3.4 TB/s; 4 rows
 // per thread in flight 353, 8 rows 378 us: at 72 KB of LDS two workgroups fit
 // a CU, and the lookups, not the loads, fill their time).  617K rows into 25
-// groups: 110 -> 36 us, bound by a workgroup's passes and the final fold.
-// Workgroups take at least GS_MIN_ROWS rows: with 4096 rows the fold of twice
-// the partial groups costs more than the shorter passes save (43 us).
+// groups: 110 -> 36 us, bound by a workgroup's passes and the final fold of the
+// partial groups.  400 groups take 49 us of 200K rows at 8192 rows per
+// workgroup, 63 at 4096, 101 at 2048; 3 groups 25, 20 and 18, and 58, 35 and 25
+// with rows gathered in no order; 25 groups of 600K rows 31, 31 and 40.  So a
+// bound of few groups gives workgroups GS_FEW_ROWS rows, up to 128 of them.
 template <bool K64, bool K32>
 struct gs_lds {
     lds_table<GB_SMALL_SLOTS, K64, K32> T;
@@ -1933,6 +1938,7 @@ uint64_t next_pow2(uint64_t x)
 struct gb_plan {
     bool small;
     uint32_t small_blocks;  // workgroups of the small path
+    uint32_t scan_blocks;   // the same for a filtered scan (no row ids), never more
     uint32_t small_cap;     // partial groups each of them may leave (a power of two)
     int P;                  // buckets of the large path
     bool wide;              // P > GB_MAX_P: two levels (GB_P1 super-buckets, then P / GB_P1 each)
@@ -1977,8 +1983,17 @@ gb_plan make_plan(int64_t n, int64_t max_groups, bool k64, bool k32)
     pl.ntiles = n > 0 ? (n + pl.chunk_rows - 1) / pl.chunk_rows : 1;
     pl.words = k64 ? 3 : 2;
     static_assert(2 * GB_CUS <= GS_THREADS, "the final fold holds one workgroup per thread");
-    pl.small_blocks = static_cast<uint32_t>(
-        std::min<int64_t>(std::max<int64_t>((n + GS_MIN_ROWS - 1) / GS_MIN_ROWS, 1), 2 * GB_CUS));
+    // GS_MIN_ROWS rows per workgroup; with few groups, which cost the final fold
+    // little, shorter passes pay until the chip is half full.  The waves of a
+    // filtered scan take GS_TILE rows of the column at a time, whole tiles each.
+    const auto blocks_of = [&](int64_t rows) { return std::max<int64_t>((n + rows - 1) / rows, 1); };
+    int64_t blocks = blocks_of(GS_MIN_ROWS), scan_blocks = blocks;
+    if (max_groups <= GS_FEW_GROUPS) {
+        blocks = std::max(blocks, std::min<int64_t>(blocks_of(GS_FEW_ROWS), GB_CUS / 2));
+        if (blocks_of(GS_TILE) <= GB_CUS / 2) scan_blocks = blocks_of(GS_TILE);
+    }
+    pl.small_blocks = static_cast<uint32_t>(std::min<int64_t>(blocks, 2 * GB_CUS));
+    pl.scan_blocks = static_cast<uint32_t>(std::min<int64_t>(scan_blocks, 2 * GB_CUS));
     pl.small_cap = static_cast<uint32_t>(next_pow2(static_cast<uint64_t>(std::max<int64_t>(max_groups, 64))));
     if (!pl.small) {
         // about 40% of a bucket's LDS table for the expected groups: the
@@ -2104,7 +2119,8 @@ gq_status run_groupby(gq_ctx *ctx, const gb_args &a, const gb_plan &pl, const gb
                       hipStream_t s)
 {
     if (pl.small) {
-        return gq_launch(ctx, "gq_groupby_local", gb_small_kernel<K64, K32>, dim3(pl.small_blocks),
+        return gq_launch(ctx, "gq_groupby_local", gb_small_kernel<K64, K32>,
+                         dim3(a.filter && !a.rowid ? pl.scan_blocks : pl.small_blocks),
                          dim3(GS_THREADS), 0, s, a, w.g, w.side_cnt, w.pcnt, static_cast<gb_part *>(w.part),
                          pl.small_cap, out, ctx->status_dev);
     }
