@@ -36,7 +36,7 @@ constexpr int FT_MAX_STEPS = 32;                    // steps of a wave per unit 
 constexpr int64_t FT_UNITS = 128;                   // units that smaller inputs are cut into
 constexpr int64_t FT_MAX_SMALL_UNITS = 2 * FT_UNITS; // their most, just before the steps double
 
-int ft_steps(int64_t n)                             // a power of two: a wave's stretch starts on a 4-KB boundary
+int ft_steps(int64_t n)                             // a power of two: a lane's rows in the stage lie in one word
 {
     int steps = 1;
     while (steps < FT_MAX_STEPS && n >= 2 * steps * FT_THREADS * FT_UNITS) steps *= 2;

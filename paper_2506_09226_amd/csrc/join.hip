@@ -595,23 +595,23 @@ gq_status region_build(gq_ctx *ctx, const int64_t *key, const int32_t *payload, 
 // other XCDs write, over the same path as the slot lines: with 4096-row units
 // the same lookups took 1.29-1.50 ms.  16K rows (64 KB of LDS for their
 // payloads, two workgroups per CU) are the most that keep 32 waves per CU.
-// Fewer rows take fewer steps per wave, always a power of two, so that a
-// wave's stretch starts on a 4-KB boundary (4M probes: 76 us at 8 steps, 97 at
-// 6, 89 at 12): about a unit per CU (1.9M probes of a 64K-key table: 52 us in
-// 928 units, 45 in 464; 200K: 17.5 in 98, 14.5 in 196; 500K: 18.6 in 245, 22 in
-// 489), and 8 steps until enough units are left for a balanced tail (9M
-// probes: 210 us at 8, 226 at 16).
+// So 512 units run at a time, and a few more than that run a round of their
+// own: calls of more than JP_ROUND_ROWS rows take the fewest steps that do in
+// as many rounds (64K keys, units of 8 steps and so, us: 2.2M rows in 269 and
+// 430 units 57 and 45, 4.3M in 525 and 467 100 and 69, 9M in 1075 and 977 158 and
+// 135, 25M 374 and 333).  Below 1M rows half the chip's places are enough, a unit
+// per CU (500K rows: 18.6 us in 245, 22 in 489; 1M in 489 and 245: 27 and 22).
 // Up to JP_TINY_ROWS rows the chip is not full either way and a call is bound
 // by one unit's chain of loads and the look-back: 512-row units (64K rows:
 // 31 -> 12 us; 100K rows 18 us at 256 rows, 13 at 512 and at 1024).
 constexpr int64_t JP_TINY_ROWS = 1 << 17;
-constexpr int64_t JP_SHORT_ROWS = 1 << 18;
-constexpr int64_t JP_LARGE_ROWS = 1 << 25;
 constexpr int JP_AHEAD = 4;
 constexpr int64_t JP_AHEAD_ROWS = 1 << 20;
 constexpr int JP_THREADS = 1024;
 constexpr int JP_TINY_THREADS = 512;
 constexpr int JP_MAX_STEPS = 16;
+constexpr int JP_SHORT_STEPS = 4;                   // with a unit per CU
+constexpr int64_t JP_ROUND_ROWS = int64_t(512) * JP_THREADS;   // rows of a step of all resident units
 struct jp_shape {
     int threads, steps;
     int64_t unit() const { return static_cast<int64_t>(threads) * steps; }
@@ -620,10 +620,11 @@ struct jp_shape {
 jp_shape jp_shape_of(int64_t n)
 {
     if (n <= JP_TINY_ROWS) return {JP_TINY_THREADS, 1};
-    if (n >= JP_LARGE_ROWS) return {JP_THREADS, JP_MAX_STEPS};
-    int steps = n < JP_SHORT_ROWS ? 1 : 2;
-    while (steps < JP_MAX_STEPS / 2 && n >= 2 * int64_t(steps) * JP_THREADS * 256) steps *= 2;
-    return {JP_THREADS, steps};
+    const int64_t short_steps = (n + JP_ROUND_ROWS / 2 - 1) / (JP_ROUND_ROWS / 2);
+    if (short_steps <= JP_SHORT_STEPS) return {JP_THREADS, static_cast<int>(short_steps)};
+    const int64_t rounds = (n + JP_ROUND_ROWS * JP_MAX_STEPS - 1) / (JP_ROUND_ROWS * JP_MAX_STEPS);
+    const int64_t steps = (n + JP_ROUND_ROWS * rounds - 1) / (JP_ROUND_ROWS * rounds);
+    return {JP_THREADS, static_cast<int>(std::max<int64_t>(steps, JP_SHORT_STEPS))};
 }
 
 struct probe_ws {
@@ -637,7 +638,7 @@ probe_ws probe_layout(gq_carver &c, int64_t n)
     const int64_t rows = jp_shape_of(n).unit();
     int64_t units = (n + rows - 1) / rows;
     // a workspace made for n rows serves every smaller call too (the units of
-    // a smaller call can be more: at most 1024, or one per 8192 rows)
+    // a smaller call can be more: at most 512 a round, rounds of 8.4M rows)
     if (n > JP_TINY_ROWS) units = n / (JP_THREADS * JP_MAX_STEPS / 2) + 1024;
     w.unit_ctr = c.take<uint32_t>(64);
     w.status = c.take<uint64_t>(static_cast<size_t>(units > 0 ? units : 1));

@@ -233,3 +233,20 @@ def test_filter_stage(ctx, n, dtype, keep):
     _, cnt = gq.gq_filter(ctx, dev(col), 0, hi, sel_in=None if sel is None else dev(sel), out=out)
     assert int(cnt.item()) == len(exp) and np.array_equal(out[:len(exp)].cpu().numpy(), exp)
     assert bool((out[len(exp):] == -1).all())
+
+
+# both sides of the probe's shape rule: 1 to 4 steps with a unit per CU, then the
+# fewest steps that keep the rounds (4, 5; 16 and, a round more, 9)
+@pytest.mark.parametrize("n", [262_145, 524_289, 786_433, 1_048_577, 2_097_153, 8_388_608, 8_388_609])
+def test_probe_rounds(ctx, n):
+    r = np.random.default_rng(n)
+    m = 3000
+    key = r.permutation(m * 3)[:m].astype(np.int64) * 7919
+    pay = r.integers(-(1 << 31), 1 << 31, size=m).astype(np.int32)
+    fk = np.where(r.random(n) < 0.6, key[r.integers(0, m, size=n)], -1)
+    ep, ey = oracle.join(key, pay, fk, None)
+    table = gq.gq_join_build(ctx, dev(key), dev(pay))
+    prow, got, cnt = gq.gq_join_probe(ctx, table, dev(fk))
+    assert ctx.status() == gq.GQ_OK
+    assert int(cnt.item()) == len(ep)
+    assert np.array_equal(prow[:len(ep)].cpu().numpy(), ep) and np.array_equal(got[:len(ep)].cpu().numpy(), ey)
