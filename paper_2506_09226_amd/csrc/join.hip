@@ -84,21 +84,23 @@ __global__ void jt_init_kernel(void *table, int log2_slots)
 }
 
 // Keys beyond the region build's reach (too few, a selection or a device
-// count), one per thread.  A small build is bound by the longest walk of any
-// key, a chain of compare-and-swaps through the fabric (25 slots and more in
-// a table half full), a large one by their number.  Most walks end within
-// JT_NEAR slots of the home slot, which are tried one by one; from there on
-// JT_AHEAD slots are looked at in one trip (8: the same).  One by one, looking
-// ahead from the home slot, and so, us: 50K keys at load factor 0.25 10.8, 12.4
-// and 11.2, at 0.5 17.3, 14.0 and 13.3, at 0.9 53, 31 and 30; 3M selected keys
-// at 0.5 222, 231 and 218.
+// count), one per thread.  Walks on from the home slot look at JT_AHEAD slots
+// in one trip (8: the same).  A build of up to JT_NEAR_KEYS keys is bound by the
+// longest walk of any key, a chain of compare-and-swaps through the fabric (25
+// slots and more in a table half full); most walks end within JT_NEAR slots of
+// the home slot, which it tries one by one first.  A larger one is bound by the
+// compare-and-swaps' number, of which looking first makes fewer.  One by one,
+// looking from the home slot on, and from JT_NEAR on, us: 20K keys at load
+// factor 0.25 8.6, 9.3 and 8.6, at 0.5 10.0, 11.0 and 9.9, 120K keys at 0.5
+// 22.7, 20.6 and 19.9; 1.2M keys at 0.5 97, 78 and 97, 3M at 0.9 396, 213 and 281.
 constexpr int JT_NEAR = 2;
+constexpr int64_t JT_NEAR_KEYS = 1 << 18;
 constexpr int JT_AHEAD = 4;
 
 __global__ __launch_bounds__(256) void jt_insert_kernel(void *table, int log2_slots, const int64_t *__restrict__ key,
                                                         const int32_t *__restrict__ payload, int64_t m_bound,
                                                         const int64_t *n_dev, const int32_t *__restrict__ sel,
-                                                        uint32_t *status)
+                                                        int near, uint32_t *status)
 {
     int64_t m = m_bound;
     if (n_dev) {
@@ -117,14 +119,14 @@ __global__ __launch_bounds__(256) void jt_insert_kernel(void *table, int log2_sl
             continue;
         }
         uint64_t s = gq_fmix64(static_cast<uint64_t>(k)) >> (64 - log2_slots);
-        // the home slot and JT_NEAR on are tried at once; a walk on from there
+        // the home slot and `near` on are tried at once; a walk on from there
         // reads JT_AHEAD slots together and tries those found empty
         const unsigned long long want = static_cast<unsigned long long>(k);
         const unsigned long long none = static_cast<unsigned long long>(JT_EMPTY);
         unsigned long long prev = atomicCAS(reinterpret_cast<unsigned long long *>(&slots[s].key), none, want);
         bool done = prev == none || prev == want;
         uint64_t probes = 0;
-        for (int q = 0; q < JT_NEAR && !done; ++q) {
+        for (int q = 0; q < near && !done; ++q) {
             s = (s + 1) & mask;
             ++probes;
             prev = atomicCAS(reinterpret_cast<unsigned long long *>(&slots[s].key), none, want);
@@ -878,7 +880,7 @@ gq_status gq_join_build(gq_ctx *ctx, const int64_t *key, const int32_t *payload,
     uint64_t ib = (static_cast<uint64_t>(m) + 255) / 256;
     if (ib > 65536) ib = 65536;
     return gq_launch(ctx, "gq_join_build_insert", jt_insert_kernel, dim3(static_cast<uint32_t>(ib)), dim3(256), 0, s, table,
-                     L, key, payload, m, n_dev, sel, ctx->status_dev);
+                     L, key, payload, m, n_dev, sel, m <= JT_NEAR_KEYS ? JT_NEAR : 0, ctx->status_dev);
 }
 
 size_t gq_join_probe_workspace_bytes(int64_t n)

@@ -29,7 +29,7 @@ constexpr int TK_CAP = 4096;                          // LDS candidates
 constexpr int TK_MAX_K = TK_CAP - TK_STEP;            // 2048
 constexpr uint64_t TK_SIGN = 0x8000000000000000ull;
 constexpr uint32_t TK_RANKED = 256;                   // keys of an answer that are ranked by counting
-static_assert(TK_RANKED <= TK_THREADS && TK_RANKED <= 256, "one key per thread, one counter per place");
+static_assert(TK_RANKED <= TK_THREADS, "one key per thread");
 
 struct tk_entry {
     uint64_t ok;
@@ -419,7 +419,9 @@ __global__ __launch_bounds__(TK_THREADS) void topk_merge_kernel(tk_lists in, int
 {
     __shared__ tk_lds L;
     __shared__ uint32_t pre[TK_THREADS];
+    __shared__ uint32_t placed[TK_RANKED];                         // keys of the answer put at each place
     const int tid = threadIdx.x;
+    if (LAST && tid < static_cast<int>(TK_RANKED)) placed[tid] = 0;
     const int b0 = static_cast<int>(blockIdx.x) * per;
     const int lists = nlists - b0 < per ? nlists - b0 : per;       // nlists <= TK_THREADS
     uint32_t total;
@@ -497,14 +499,12 @@ __global__ __launch_bounds__(TK_THREADS) void topk_merge_kernel(tk_lists in, int
             // barrier in between, where a sort has one for each of its
             // log2(cnt)^2 / 2 stages (k = 100 of 3M rows 37.5 -> 34.2 us, k = 10
             // of 200K rows 21.9 -> 17.9); equal ones take the places from there on
-            if (tid < static_cast<int>(TK_RANKED)) L.hist[0][tid] = 0;
-            gq_lds_barrier();
             if (tid < static_cast<int>(cnt)) {
                 const uint64_t o = L.ok[tid];
                 const uint32_t r = L.rk[tid];
                 uint32_t at = 0;
                 for (uint32_t j = 0; j < cnt; ++j) at += tk_better(L.ok[j], L.rk[j], o, r) ? 1u : 0u;
-                put(at + atomicAdd(&L.hist[0][at], 1u), o, r);
+                put(at + atomicAdd(&placed[at], 1u), o, r);
             }
         } else {
             tk_sort_count(L);                                      // the answer, best first
