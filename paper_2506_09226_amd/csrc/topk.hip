@@ -280,7 +280,7 @@ GQ_DEV uint64_t tk_order(int64_t v, bool desc)
 // Up to this k the merges take every candidate: recording and ranking the
 // lists' bounds costs more than it saves (128 lists of 100 keys: 33 us in two
 // merges, 39 us in one with bounds, and 5 us more in the scan).  At k = 1000
-// and 512 lists the merges took 126 us without bounds and take 56 with them.
+// and 512 lists the merges took 126 us without bounds and take 51 with them.
 constexpr int TK_PLAIN_K = 256;
 
 // Candidate lists: list i holds cnt[i] <= k keys from i * k, and a bound that
@@ -520,9 +520,9 @@ __global__ __launch_bounds__(TK_THREADS) void topk_merge_kernel(tk_lists in, int
 // keys (k = 1000 of 50M rows in no order: 158 us in pairs, 161 by three).  In a
 // sorted column, or one with many ties, half the lists or all of them pass the
 // bound, and the last merge, alone on the chip, walks their keys; so a group
-// takes as many lists as leave it TK_LAST_MERGE of them at most (50M rows in
-// pairs, and so: k = 1000 of a rising column 1131 and 936 us, its last rows
-// first, 252 and 214, its first rows; k = 2048 of equal values 456 and 282).
+// takes as many lists as leave it TK_LAST_MERGE of them at most (50M rows, in
+// pairs and in such groups, us: the 1000 largest values of a rising column 1131
+// and 936, its 1000 smallest 252 and 214, 2048 of equal values 456 and 282).
 int64_t tk_one_merge(int k) { return k <= TK_PLAIN_K ? 8192 : 32768; }
 constexpr int64_t TK_LAST_MERGE = 3 << 16;
 int tk_merge_per(int64_t lists, int k)
