@@ -1939,6 +1939,7 @@ struct gb_plan {
     bool small;
     uint32_t small_blocks;  // workgroups of the small path
     uint32_t scan_blocks;   // the same for a filtered scan (no row ids), never more
+    uint32_t few_blocks;    // small_blocks of a bound of GS_FEW_GROUPS groups or fewer
     uint32_t small_cap;     // partial groups each of them may leave (a power of two)
     int P;                  // buckets of the large path
     bool wide;              // P > GB_MAX_P: two levels (GB_P1 super-buckets, then P / GB_P1 each)
@@ -1988,13 +1989,16 @@ gb_plan make_plan(int64_t n, int64_t max_groups, bool k64, bool k32)
     // filtered scan take GS_TILE rows of the column at a time, whole tiles each.
     const auto blocks_of = [&](int64_t rows) { return std::max<int64_t>((n + rows - 1) / rows, 1); };
     int64_t blocks = blocks_of(GS_MIN_ROWS), scan_blocks = blocks;
+    const int64_t few_blocks = std::max(blocks, std::min<int64_t>(blocks_of(GS_FEW_ROWS), GB_CUS / 2));
     if (max_groups <= GS_FEW_GROUPS) {
-        blocks = std::max(blocks, std::min<int64_t>(blocks_of(GS_FEW_ROWS), GB_CUS / 2));
+        blocks = few_blocks;
         if (blocks_of(GS_TILE) <= GB_CUS / 2) scan_blocks = blocks_of(GS_TILE);
     }
     pl.small_blocks = static_cast<uint32_t>(std::min<int64_t>(blocks, 2 * GB_CUS));
     pl.scan_blocks = static_cast<uint32_t>(std::min<int64_t>(scan_blocks, 2 * GB_CUS));
-    pl.small_cap = static_cast<uint32_t>(next_pow2(static_cast<uint64_t>(std::max<int64_t>(max_groups, 64))));
+    pl.small_cap = static_cast<uint32_t>(next_pow2(static_cast<uint64_t>(std::max<int64_t>(max_groups, GS_FEW_GROUPS))));
+    // (a workspace made for more groups serves a bound of few too)
+    pl.few_blocks = static_cast<uint32_t>(std::min<int64_t>(few_blocks, 2 * GB_CUS));
     if (!pl.small) {
         // about 40% of a bucket's LDS table for the expected groups: the
         // bucket pass waits on the longest probe chain of 64 lanes, so short
@@ -2085,8 +2089,10 @@ gb_ws gb_layout(gq_carver &c, const gb_plan &pl, int64_t n, bool k64, bool k32)
     w.g.hi = c.take<int64_t>(S);
     w.g.mask = S - 1;
     if (pl.small) {
-        w.pcnt = c.take<uint32_t>(pl.small_blocks);
-        w.part = c.take<char>(static_cast<size_t>(pl.small_blocks) * pl.small_cap * sizeof(gb_part));
+        const size_t parts = std::max(static_cast<size_t>(pl.small_blocks) * pl.small_cap,
+                                      static_cast<size_t>(pl.few_blocks) * GS_FEW_GROUPS);
+        w.pcnt = c.take<uint32_t>(std::max(pl.small_blocks, pl.few_blocks));
+        w.part = c.take<char>(parts * sizeof(gb_part));
     }
     if (!pl.small) {
         const size_t rows = static_cast<size_t>(n > 0 ? n : 1);

@@ -44,3 +44,15 @@ def test_topk_workspace_grows_with_k():
             b = L.gq_topk_workspace_bytes(n, k)
             assert b >= last, (n, k)
             last = b
+
+
+@pytest.mark.parametrize("k64,k32", [(1, 0), (0, 1), (1, 1)])
+def test_groupby_workspace_grows_with_groups(k64, k32):
+    """One made for a bound of max_groups serves lower bounds over the same rows."""
+    L = gq.lib()
+    for n in sizes():
+        last = 0
+        for g in [1, 2, 25, 32, 63, 64, 65, 100, 127, 128, 129, 256, 257, 511, 512, 513, 1000, 100_000, 1_500_000]:
+            b = L.gq_groupby_workspace_bytes(n, g, k64, k32)
+            assert b >= last, (n, g)
+            last = b
